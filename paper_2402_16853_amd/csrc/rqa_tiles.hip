@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdlib>
 #include <cstring>
 #include <limits>
@@ -95,7 +96,11 @@ constexpr int kStitchBatch = 8;   // strips whose summaries a stitch thread load
 constexpr int kStitchCapV = 2048; // stitch LDS bins for vertical lengths < kStitchCapV (the
                                   // stitch joins the runs that cross strip edges: long ones)
 constexpr int kStatThreads = 256;
-constexpr int kStatMaxBlocks = 64;
+constexpr int kStatMaxBlocks = 60;
+constexpr int kStatLengths = 2048;   // lengths per statistics block (8 per thread: the blocks'
+                                     // loops are chains of dependent loads)
+constexpr int kPrepareBlocks = 64;   // k_prepare blocks per job
+constexpr int kCounters = 64;        // work counters of a launch
 // Column boxes (exact pruning of the predicate, see tile_bits): per 64-column
 // tile one record of kBoxStride floats holding (lo_k, hi_k) for the first
 // kBoxK coordinates.  The box array of a job starts with a header of
@@ -147,6 +152,8 @@ struct JobDesc {
     int32_t stitch_block0;     // first stitch block of this job
     int32_t mins[3];           // lmin, vmin, wmin
     int32_t stat_blocks;       // blocks of the statistics kernels for this job
+    uint8_t *nonfinite;        // kPrepareBlocks bytes: k_prepare block b saw a non-finite value
+    uint32_t *stat_done;       // statistics blocks of this job that have finished
     JobStats *stats;           // device statistics record
     double *ent_part;          // [3][kStatMaxBlocks] entropy partial sums
     float *box;                // column boxes (header + records), nullptr if none
@@ -637,15 +644,21 @@ __device__ float box_lo(float cmin, float b) {
 }
 
 // ---------------------------------------------------------------------------
-// Kernel 1: per-job preparation -- zero the histograms, flag non-finite input,
-// build the zero-padded tail of the last column tile, reset work counters.
-// grid.y = job index.
+// Kernel 1: per-job preparation -- zero the histograms, the statistics and the
+// flag, reset the work counters, look for non-finite input, build the
+// zero-padded tail of the last column tile.  grid = (kPrepareBlocks, jobs).
+// Non-finite input is noted per block (a plain store: the flag itself is being
+// cleared by block 0 of this kernel) and enters the flag in the statistics.
 // ---------------------------------------------------------------------------
-__global__ void k_prepare(const JobDesc *__restrict__ jobs) {
-    const JobDesc &j = jobs[blockIdx.y];
+__device__ __forceinline__ void prepare_job(const JobDesc &j, int *counters) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t hl = (int64_t)j.hmax + 1;
+    if (blockIdx.y == 0 && tid < kCounters) counters[tid] = 0;
+    if (tid == 0) {
+        *j.flag = 0;
+        *j.stat_done = 0u;
+    }
     for (int64_t t = tid; t < hl; t += stride) {
         j.hd[t] = 0ull;
         j.hv[t] = 0ull;
@@ -653,17 +666,35 @@ __global__ void k_prepare(const JobDesc *__restrict__ jobs) {
     }
     if (tid < (int64_t)(sizeof(JobStats) / 8))
         reinterpret_cast<unsigned long long *>(j.stats)[tid] = 0ull;
-    if (j.mode == kModeMatrix) return;   // a given matrix has no series
     bool bad = false;
-    for (int64_t t = tid; t < j.n_points; t += stride) bad |= !__builtin_isfinite(j.s[t]);
-    if (j.mode == kModeCross)
-        for (int64_t t = tid; t < j.n_points_b; t += stride) bad |= !__builtin_isfinite(j.sb[t]);
-    if (bad) atomicOr(j.flag, 1);   // bit 0: non-finite input
-    // Column coordinates of the last tile, from the columns' series.
-    const int64_t base = (int64_t)j.c_last * 64;
-    float *tail = const_cast<float *>(j.tail);
-    for (int64_t t = tid; t < j.tail_len; t += stride)
-        tail[t] = base + t < j.n_points_b ? j.sb[base + t] : 0.0f;
+    if (j.mode != kModeMatrix) {   // a given matrix has no series
+        for (int64_t t = tid; t < j.n_points; t += stride) bad |= !__builtin_isfinite(j.s[t]);
+        if (j.mode == kModeCross)
+            for (int64_t t = tid; t < j.n_points_b; t += stride) bad |= !__builtin_isfinite(j.sb[t]);
+        // Column coordinates of the last tile, from the columns' series.
+        const int64_t base = (int64_t)j.c_last * 64;
+        float *tail = const_cast<float *>(j.tail);
+        for (int64_t t = tid; t < j.tail_len; t += stride)
+            tail[t] = base + t < j.n_points_b ? j.sb[base + t] : 0.0f;
+    }
+    const int any = __syncthreads_or(bad ? 1 : 0);
+    if (threadIdx.x == 0) j.nonfinite[blockIdx.x] = any ? 1 : 0;
+}
+
+__global__ void k_prepare(const JobDesc *__restrict__ jobs, int *counters) {
+    prepare_job(jobs[blockIdx.y], counters);
+}
+
+// The same for a launch of one job, whose descriptors come as kernel arguments
+// and are written to device memory here: nothing to stage on the host, and no
+// copy in front of the first kernel.
+__global__ void k_prepare_one(const JobDesc d, const GroupDesc g, JobDesc *ddesc, GroupDesc *dgroups,
+                              int *counters) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *ddesc = d;
+        *dgroups = g;
+    }
+    prepare_job(d, counters);
 }
 
 // Column boxes of every column tile of a job (grid.y = job; one thread per
@@ -735,22 +766,6 @@ __global__ void __launch_bounds__(kProbeThreads) k_box_probe(const JobDesc *__re
         reinterpret_cast<int *>(j.box)[0] = (sampled > 0 && 64 * decided >= sampled) ? 1 : 0;
 }
 
-// Reset the non-finite flags and the work counters (runs before k_prepare).
-__global__ void k_reset(const JobDesc *__restrict__ jobs, int njobs, int *counters, int ncounters) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < njobs) *jobs[t].flag = 0;
-    if (t < ncounters) counters[t] = 0;
-}
-
-// Write the descriptors of a one-job launch from kernel arguments (the launch
-// path that may not copy from host memory: nothing to stage, nothing to free).
-__global__ void k_setup(const JobDesc d, const GroupDesc g, JobDesc *ddesc, GroupDesc *dgroups) {
-    if (threadIdx.x == 0) {
-        *ddesc = d;
-        *dgroups = g;
-    }
-}
-
 // Move a one-job launch to row band b: its strips [b K, min((b+1) K, S)), the
 // origin of their summary slots, the band's work items, and a fresh work
 // counter (K strips per band, S strips in all).
@@ -817,18 +832,18 @@ __device__ __forceinline__ void publish_counter(int *ctr, int value) {
 }
 
 __device__ void flush_bins(const StripLds &L, const JobDesc &j) {
-    const int hl = j.hmax + 1;
-    for (int t = threadIdx.x; t < kCapW; t += blockDim.x) {
+    const int bins = j.hmax + 1 < kCapW ? j.hmax + 1 : kCapW;   // no line is longer than hmax
+    for (int t = threadIdx.x; t < bins; t += blockDim.x) {
         if (t < kCapD) {
             const uint32_t v = L.bd[t];
-            if (v) { if (t < hl) g_add(j.hd + t, (unsigned long long)v); L.bd[t] = 0; }
+            if (v) { g_add(j.hd + t, (unsigned long long)v); L.bd[t] = 0; }
         }
         if (t < kCapV) {
             const uint32_t v = L.bv[t];
-            if (v) { if (t < hl) g_add(j.hv + t, (unsigned long long)v); L.bv[t] = 0; }
+            if (v) { g_add(j.hv + t, (unsigned long long)v); L.bv[t] = 0; }
         }
         const uint32_t v = L.bw[t];
-        if (v) { if (t < hl) g_add(j.hw + t, (unsigned long long)v); L.bw[t] = 0; }
+        if (v) { g_add(j.hw + t, (unsigned long long)v); L.bw[t] = 0; }
     }
 }
 
@@ -1728,38 +1743,42 @@ __global__ void __launch_bounds__(kStitchThreads) k_stitch(const JobDesc *__rest
                                                            int njobs) {
     __shared__ StitchLds L;
     static_assert(kStitchCapV <= kCapW, "bins are cleared and flushed in one pass over kCapW");
-    for (int t = threadIdx.x; t < kCapW; t += blockDim.x) {
-        if (t < kCapD) L.bd[t] = 0;
-        if (t < kStitchCapV) L.bv[t] = 0;
-        L.bw[t] = 0;
-    }
-    __syncthreads();
     int lo = 0, hi = njobs - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (jobs[mid].stitch_block0 <= (int)blockIdx.x) lo = mid; else hi = mid - 1;
     }
     const JobDesc &j = jobs[lo];
-    const int n = j.n;
+    // No line is longer than hmax, so a short job clears and flushes few bins.
+    const int bins = j.hmax + 1 < kCapW ? j.hmax + 1 : kCapW;
+    for (int t = threadIdx.x; t < bins; t += blockDim.x) {
+        if (t < kCapD) L.bd[t] = 0;
+        if (t < kStitchCapV) L.bv[t] = 0;
+        L.bw[t] = 0;
+    }
+    __syncthreads();
     const int64_t line = (int64_t)(blockIdx.x - j.stitch_block0) * blockDim.x + threadIdx.x;
     if (j.mode != kModeAuto) stitch_full(L, j, line);
     else stitch_auto(L, j, line);
     __syncthreads();
-    const int hl = n + 1;
-    for (int t = threadIdx.x; t < kCapW; t += blockDim.x) {
-        if (t < kCapD && L.bd[t] && t < hl) g_add(j.hd + t, (unsigned long long)L.bd[t]);
-        if (t < kStitchCapV && L.bv[t] && t < hl) g_add(j.hv + t, (unsigned long long)L.bv[t]);
-        if (L.bw[t] && t < hl) g_add(j.hw + t, (unsigned long long)L.bw[t]);
+    for (int t = threadIdx.x; t < bins; t += blockDim.x) {
+        if (t < kCapD && L.bd[t]) g_add(j.hd + t, (unsigned long long)L.bd[t]);
+        if (t < kStitchCapV && L.bv[t]) g_add(j.hv + t, (unsigned long long)L.bv[t]);
+        if (L.bw[t]) g_add(j.hw + t, (unsigned long long)L.bw[t]);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Kernels 4-6: statistics of the finished histograms (the inputs of the RQA
+// Kernels 4 and 5: statistics of the finished histograms (the inputs of the RQA
 // measures), so that a result fetch needs only a few hundred bytes.  Integer
 // moments are exact (u64); the entropy partial sums use a fixed reduction
 // order, so a job's statistics depend only on its own histograms.
-// grid = (kStatMaxBlocks, jobs); block b of a job covers one contiguous chunk of
-// lengths.
+// grid = (blocks of the largest job, jobs); block b of a job covers one
+// contiguous chunk of lengths.  A job of one block (up to kStatLengths lengths)
+// has its moments, its entropies and its flag done by k_stats_moments alone:
+// short calls are made of launches, and three kernels of ~10 us (n = 2,000: 14 +
+// 8 + 4 us and the gaps between them) become one.  For longer jobs
+// k_stats_entropy's last block to finish adds the partial sums up.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void chunk_of(const JobDesc &j, int b, int64_t &lo, int64_t &hi) {
     const int64_t len = (int64_t)j.hmax + 1;
@@ -1768,91 +1787,178 @@ __device__ __forceinline__ void chunk_of(const JobDesc &j, int b, int64_t &lo, i
     hi = lo + per < len ? lo + per : len;
 }
 
+constexpr int kStatPer = kStatLengths / kStatThreads;   // lengths a thread takes at a time
+
+// This thread's kStatPer entries of the three histograms from length `base` on,
+// all loads issued together (one memory latency; a loop that loads and adds
+// pays one per entry: 14 us instead of 5 for a 2,000-point job).
+struct StatCounts {
+    unsigned long long c[3][kStatPer];
+};
+__device__ __forceinline__ void load_counts(const JobDesc &j, int64_t base, int64_t hi, StatCounts &s) {
+    const unsigned long long *hs[3] = {j.hd, j.hv, j.hw};
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+#pragma unroll
+        for (int u = 0; u < kStatPer; ++u) {
+            const int64_t l = base + threadIdx.x + u * kStatThreads;
+            s.c[h][u] = l < hi && l > 0 ? *glb(hs[h] + l) : 0ull;
+        }
+}
+
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
+}
+__device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const unsigned long long o = __shfl_xor(v, d, 64);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
+// This thread's share of -sum p ln p over its loaded lengths >= least.
+__device__ __forceinline__ double entropy_part(const unsigned long long *c, int64_t base, int64_t least,
+                                               unsigned long long total) {
+    double acc = 0.0;
+    const double C = (double)total;
+#pragma unroll
+    for (int u = 0; u < kStatPer; ++u) {
+        if (base + threadIdx.x + u * kStatThreads < least || c[u] == 0) continue;
+        const double p = (double)c[u] / C;
+        acc -= p * log(p);
+    }
+    return acc;
+}
+
+// Sums of three values over the workgroup in a fixed order: lanes by butterfly,
+// then the waves (every thread returns with the sums).
+__device__ __forceinline__ void block_sums(double (&v)[3], double (*red)[3]) {
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) v[h] = v[h] + __shfl_xor(v[h], d, 64);
+    if ((threadIdx.x & 63) == 0)
+        for (int h = 0; h < 3; ++h) red[threadIdx.x >> 6][h] = v[h];
+    __syncthreads();
+    for (int h = 0; h < 3; ++h) {
+        v[h] = 0.0;
+        for (int w = 0; w < kStatThreads / 64; ++w) v[h] = v[h] + red[w][h];
+    }
+}
+
+// Bit 0 of the flag: non-finite input.  Called by one whole wave.
+__device__ __forceinline__ void finish_flag(const JobDesc &j) {
+    static_assert(kPrepareBlocks == 64, "one k_prepare block per lane");
+    if (__ballot(*glb(j.nonfinite + (threadIdx.x & 63)) != 0) != 0ull && (threadIdx.x & 63) == 0)
+        g_or(j.flag, 1);
+}
+
 __global__ void __launch_bounds__(kStatThreads) k_stats_moments(const JobDesc *__restrict__ jobs) {
     const JobDesc &j = jobs[blockIdx.y];
     if ((int)blockIdx.x >= j.stat_blocks) return;
-    __shared__ unsigned long long red[5][kStatThreads];
+    const bool alone = j.stat_blocks == 1;
+    __shared__ unsigned long long part[kStatThreads / 64][15];
+    __shared__ double red[kStatThreads / 64][3];
     int64_t lo, hi;
     chunk_of(j, blockIdx.x, lo, hi);
-    const unsigned long long *hs[3] = {j.hd, j.hv, j.hw};
-    for (int h = 0; h < 3; ++h) {
-        unsigned long long ca = 0, ma = 0, cm = 0, mm = 0, lg = 0;
-        for (int64_t l = lo + threadIdx.x; l < hi; l += kStatThreads) {
-            const unsigned long long c = hs[h][l];
-            if (l == 0 || c == 0) continue;
-            ca += c;
-            ma += c * (unsigned long long)l;
-            if (l >= j.mins[h]) {
-                cm += c;
-                mm += c * (unsigned long long)l;
+    // per histogram: count, mass, count and mass from the minimum, longest
+    unsigned long long v[3][5] = {};
+    StatCounts s;
+    for (int64_t base = lo; base < hi; base += kStatLengths) {
+        load_counts(j, base, hi, s);
+#pragma unroll
+        for (int h = 0; h < 3; ++h)
+#pragma unroll
+            for (int u = 0; u < kStatPer; ++u) {
+                const unsigned long long l = (unsigned long long)base + threadIdx.x + u * kStatThreads;
+                const unsigned long long c = s.c[h][u];
+                if (c == 0) continue;
+                v[h][0] += c;
+                v[h][1] += c * l;
+                if (l >= (unsigned long long)j.mins[h]) {
+                    v[h][2] += c;
+                    v[h][3] += c * l;
+                }
+                v[h][4] = l;
             }
-            lg = (unsigned long long)l;
-        }
-        red[0][threadIdx.x] = ca;
-        red[1][threadIdx.x] = ma;
-        red[2][threadIdx.x] = cm;
-        red[3][threadIdx.x] = mm;
-        red[4][threadIdx.x] = lg;
-        __syncthreads();
-        for (int s = kStatThreads / 2; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) {
-                for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + s];
-                red[4][threadIdx.x] = red[4][threadIdx.x] > red[4][threadIdx.x + s]
-                                          ? red[4][threadIdx.x] : red[4][threadIdx.x + s];
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            JobStats *st = j.stats;
-            if (red[0][0]) atomicAdd(&st->cnt_all[h], red[0][0]);
-            if (red[1][0]) atomicAdd(&st->mass_all[h], red[1][0]);
-            if (red[2][0]) atomicAdd(&st->cnt_min[h], red[2][0]);
-            if (red[3][0]) atomicAdd(&st->mass_min[h], red[3][0]);
-            if (red[4][0]) atomicMax(&st->longest[h], red[4][0]);
-        }
-        __syncthreads();
     }
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const unsigned long long r = q < 4 ? wave_sum(v[h][q]) : wave_max(v[h][q]);
+            if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][h * 5 + q] = r;
+        }
+    __syncthreads();
+    if (threadIdx.x < 15) {
+        const int h = threadIdx.x / 5, q = threadIdx.x % 5;
+        unsigned long long r = 0;
+        for (int w = 0; w < kStatThreads / 64; ++w) {
+            const unsigned long long o = part[w][threadIdx.x];
+            r = q < 4 ? r + o : (o > r ? o : r);
+        }
+        part[0][threadIdx.x] = r;
+        // JobStats: the five moments are rows of three u64, in the order above.
+        static_assert(offsetof(JobStats, longest) == 12 * sizeof(uint64_t), "moment rows");
+        unsigned long long *dst = reinterpret_cast<unsigned long long *>(j.stats) + q * 3 + h;
+        if (alone) *dst = r;
+        else if (r && q < 4) atomicAdd(dst, r);
+        else if (r) atomicMax(dst, r);
+    }
+    if (!alone) return;
+    __syncthreads();
+    double e[3];
+#pragma unroll
+    for (int h = 0; h < 3; ++h) e[h] = entropy_part(s.c[h], lo, j.mins[h], part[0][h * 5 + 2]);
+    block_sums(e, red);
+    if (threadIdx.x == 0)
+        for (int h = 0; h < 3; ++h) j.stats->ent[h] = e[h];
+    if (threadIdx.x < 64) finish_flag(j);
 }
 
 __global__ void __launch_bounds__(kStatThreads) k_stats_entropy(const JobDesc *__restrict__ jobs) {
     const JobDesc &j = jobs[blockIdx.y];
-    if ((int)blockIdx.x >= j.stat_blocks) return;
-    __shared__ double red[kStatThreads];
+    if (j.stat_blocks == 1 || (int)blockIdx.x >= j.stat_blocks) return;
+    __shared__ double red[kStatThreads / 64][3];
     int64_t lo, hi;
     chunk_of(j, blockIdx.x, lo, hi);
-    const unsigned long long *hs[3] = {j.hd, j.hv, j.hw};
-    for (int h = 0; h < 3; ++h) {
-        const unsigned long long total = j.stats->cnt_min[h];
-        double acc = 0.0;
-        if (total) {
-            const double C = (double)total;
-            const int64_t from = lo > j.mins[h] ? lo : (int64_t)j.mins[h];
-            for (int64_t l = from + threadIdx.x; l < hi; l += kStatThreads) {
-                const unsigned long long c = hs[h][l];
-                if (l == 0 || c == 0) continue;
-                const double p = (double)c / C;
-                acc -= p * log(p);
-            }
-        }
-        red[threadIdx.x] = acc;
-        __syncthreads();
-        for (int s = kStatThreads / 2; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) j.ent_part[h * kStatMaxBlocks + blockIdx.x] = red[0];
-        __syncthreads();
+    double e[3] = {};
+    for (int64_t base = lo; base < hi; base += kStatLengths) {
+        StatCounts s;
+        load_counts(j, base, hi, s);
+#pragma unroll
+        for (int h = 0; h < 3; ++h)
+            e[h] = e[h] + entropy_part(s.c[h], base, j.mins[h], j.stats->cnt_min[h]);
     }
-}
-
-__global__ void k_stats_final(const JobDesc *__restrict__ jobs, int njobs) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 3 * njobs) return;
-    const JobDesc &j = jobs[t / 3];
-    const int h = t % 3;
-    double e = 0.0;
-    for (int b = 0; b < j.stat_blocks; ++b) e = e + j.ent_part[h * kStatMaxBlocks + b];
-    j.stats->ent[h] = e;
+    block_sums(e, red);
+    if (threadIdx.x >= 64) return;
+    // The last block's first wave adds the partial sums up, one block per lane,
+    // in a fixed order.
+    uint32_t done = 0;
+    if (threadIdx.x == 0) {
+        for (int h = 0; h < 3; ++h)
+            __hip_atomic_store(j.ent_part + h * kStatMaxBlocks + blockIdx.x, e[h], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        done = __hip_atomic_fetch_add(j.stat_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
+    if (done + 1u != (uint32_t)j.stat_blocks) return;
+    static_assert(kStatMaxBlocks <= 64, "one statistics block per lane");
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+        e[h] = (int)threadIdx.x < j.stat_blocks
+                   ? __hip_atomic_load(j.ent_part + h * kStatMaxBlocks + threadIdx.x, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT)
+                   : 0.0;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) e[h] = e[h] + __shfl_xor(e[h], d, 64);
+        if (threadIdx.x == 0) j.stats->ent[h] = e[h];
+    }
+    finish_flag(j);
 }
 
 // ---------------------------------------------------------------------------
@@ -2042,7 +2148,7 @@ struct Layout {
     int64_t dentries;      // diagonal summary entries per array, one band
     int64_t tail_len;
     int64_t box_floats;    // column boxes (header + records), 0 if none
-    size_t off_tail, off_lead, off_vf, off_vl, off_df, off_dl, off_ent, off_hf, off_hl, off_box,
+    size_t off_tail, off_lead, off_vf, off_vl, off_df, off_dl, off_ent, off_nf, off_hf, off_hl, off_box,
         off_cs, off_ds, bytes;
 };
 
@@ -2156,7 +2262,11 @@ Layout layout_of(const Job &jb) {
     L.off_vl = off; off += a256(sizeof(uint16_t) * (size_t)L.ventries);
     L.off_df = off; off += a256(sizeof(uint16_t) * (size_t)L.dentries);
     L.off_dl = off; off += a256(sizeof(uint16_t) * (size_t)L.dentries);
-    L.off_ent = off; off += a256(sizeof(double) * 3 * kStatMaxBlocks);
+    // Statistics: entropy partial sums, the count of finished blocks, and
+    // k_prepare's non-finite notes.
+    L.off_ent = off;
+    L.off_nf = off + sizeof(double) * 3 * kStatMaxBlocks;
+    off += a256(sizeof(double) * 3 * kStatMaxBlocks + sizeof(uint32_t) + kPrepareBlocks);
     L.off_hf = off; off += a256(sizeof(uint32_t) * (size_t)L.hentries);
     L.off_hl = off; off += a256(sizeof(uint32_t) * (size_t)L.hentries);
     // Boxes for the modes with a predicate and the embedding dimensions whose
@@ -2236,9 +2346,10 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
     d.mins[0] = kp.lmin;
     d.mins[1] = kp.vmin;
     d.mins[2] = kp.wmin;
-    // 2,048 lengths (8 per thread) per statistics block: the blocks' loops
-    // are chains of dependent loads, so short chains finish sooner.
-    d.stat_blocks = (int32_t)std::min<int64_t>(kStatMaxBlocks, std::max<int64_t>(1, (hlen + 2047) / 2048));
+    d.stat_blocks = (int32_t)std::min<int64_t>(
+        kStatMaxBlocks, std::max<int64_t>(1, (hlen + kStatLengths - 1) / kStatLengths));
+    d.stat_done = reinterpret_cast<uint32_t *>(scr + lay.off_nf);
+    d.nonfinite = reinterpret_cast<uint8_t *>(d.stat_done + 1);
     d.stats = jb.stats ? reinterpret_cast<JobStats *>(jb.stats)
                        : reinterpret_cast<JobStats *>(reinterpret_cast<char *>(jb.flag) + 8);
     d.ent_part = reinterpret_cast<double *>(scr + lay.off_ent);
@@ -2252,6 +2363,13 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
     d.spin_limit = inject ? 64 : (int32_t)kSpinLimit;
     d.wait_bias = inject ? (1 << 30) : 0;
     return d;
+}
+
+// Statistics of njobs jobs, the largest of which has `blocks` statistics blocks.
+void launch_stats(const JobDesc *jobs, int blocks, int njobs, hipStream_t st) {
+    hipLaunchKernelGGL(k_stats_moments, dim3(blocks, njobs), dim3(kStatThreads), 0, st, jobs);
+    if (blocks > 1)
+        hipLaunchKernelGGL(k_stats_entropy, dim3(blocks, njobs), dim3(kStatThreads), 0, st, jobs);
 }
 
 // Blocks of k_box_bounds for one job: one thread per box entry, at most 128
@@ -2359,13 +2477,18 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         return jobs_in[a].n_vec > jobs_in[b].n_vec;
     });
 
-    // The previous launch that used `staging` must have consumed it.
-    if (staging_free && hipEventSynchronize(staging_free) != hipSuccess) return RQA_EDEVICE;
+    // The descriptors of a launch of one job travel as kernel arguments; those
+    // of several are staged and copied.  The previous launch that used
+    // `staging` must have consumed it.
+    std::vector<JobDesc> one_desc(njobs == 1 ? 1 : 0);
+    std::vector<GroupDesc> one_group(njobs == 1 ? 64 : 0);
+    if (njobs > 1 && staging_free && hipEventSynchronize(staging_free) != hipSuccess) return RQA_EDEVICE;
 
     char *dbase = static_cast<char *>(launch_scratch);
-    JobDesc *hdesc = static_cast<JobDesc *>(staging);
-    GroupDesc *hgroups = reinterpret_cast<GroupDesc *>(static_cast<char *>(staging) +
-                                                       a256(sizeof(JobDesc) * njobs));
+    JobDesc *hdesc = njobs == 1 ? one_desc.data() : static_cast<JobDesc *>(staging);
+    GroupDesc *hgroups = njobs == 1 ? one_group.data()
+                                    : reinterpret_cast<GroupDesc *>(static_cast<char *>(staging) +
+                                                                    a256(sizeof(JobDesc) * njobs));
     JobDesc *ddesc = reinterpret_cast<JobDesc *>(dbase);
     GroupDesc *dgroups = reinterpret_cast<GroupDesc *>(dbase + a256(sizeof(JobDesc) * njobs));
     int *dcounters = reinterpret_cast<int *>(dbase + a256(sizeof(JobDesc) * njobs) +
@@ -2402,15 +2525,19 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
     }
     hgroups[ngroups - 1].items = strip_acc;
 
-    const size_t desc_bytes = a256(sizeof(JobDesc) * njobs) + a256(sizeof(GroupDesc) * 64);
-    if (hipMemcpyAsync(dbase, staging, desc_bytes, hipMemcpyHostToDevice, st) != hipSuccess)
-        return RQA_EDEVICE;
-    if (staging_free && hipEventRecord(staging_free, st) != hipSuccess) return RQA_EDEVICE;
+    if (njobs > 1) {
+        const size_t desc_bytes = a256(sizeof(JobDesc) * njobs) + a256(sizeof(GroupDesc) * 64);
+        if (hipMemcpyAsync(dbase, staging, desc_bytes, hipMemcpyHostToDevice, st) != hipSuccess)
+            return RQA_EDEVICE;
+        if (staging_free && hipEventRecord(staging_free, st) != hipSuccess) return RQA_EDEVICE;
+    }
 
     if (phases) hipEventRecord(phases->ev[0], st);
-    hipLaunchKernelGGL(k_reset, dim3((std::max(njobs, 64) + 255) / 256), dim3(256), 0, st, ddesc,
-                       njobs, dcounters, 64);
-    hipLaunchKernelGGL(k_prepare, dim3(64, njobs), dim3(256), 0, st, ddesc);
+    if (njobs == 1)
+        hipLaunchKernelGGL(k_prepare_one, dim3(kPrepareBlocks), dim3(256), 0, st, hdesc[0], hgroups[0],
+                           ddesc, dgroups, dcounters);
+    else
+        hipLaunchKernelGGL(k_prepare, dim3(kPrepareBlocks, njobs), dim3(256), 0, st, ddesc, dcounters);
     hipLaunchKernelGGL(k_box_bounds, dim3(box_grid, njobs), dim3(256), 0, st, ddesc);
     hipLaunchKernelGGL(k_box_probe, dim3(njobs), dim3(kProbeThreads), 0, st, ddesc);
 
@@ -2442,9 +2569,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
                 hipLaunchKernelGGL(k_stitch, dim3((unsigned)((lines + kStitchThreads - 1) / kStitchThreads)),
                                    dim3(kStitchThreads), 0, st, ddesc, 1);
         }
-        hipLaunchKernelGGL(k_stats_moments, dim3(stat_grid, 1), dim3(kStatThreads), 0, st, ddesc);
-        hipLaunchKernelGGL(k_stats_entropy, dim3(stat_grid, 1), dim3(kStatThreads), 0, st, ddesc);
-        hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, st, ddesc, 1);
+        launch_stats(ddesc, stat_grid, 1, st);
         if (phases) hipEventRecord(phases->ev[3], st);
         return hipGetLastError() == hipSuccess ? RQA_OK : RQA_EDEVICE;
     }
@@ -2488,9 +2613,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
     if (phases) hipEventRecord(phases->ev[2], st);
     if (stitch_blocks > 0)
         hipLaunchKernelGGL(k_stitch, dim3(stitch_blocks), dim3(kStitchThreads), 0, st, ddesc, njobs);
-    hipLaunchKernelGGL(k_stats_moments, dim3(stat_grid, njobs), dim3(kStatThreads), 0, st, ddesc);
-    hipLaunchKernelGGL(k_stats_entropy, dim3(stat_grid, njobs), dim3(kStatThreads), 0, st, ddesc);
-    hipLaunchKernelGGL(k_stats_final, dim3((3 * njobs + 255) / 256), dim3(256), 0, st, ddesc, njobs);
+    launch_stats(ddesc, stat_grid, njobs, st);
     if (phases) hipEventRecord(phases->ev[3], st);
     return hipGetLastError() == hipSuccess ? RQA_OK : RQA_EDEVICE;
 }
@@ -2516,9 +2639,8 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     const Layout lay = layout_of(jb);
     const JobDesc d = make_desc(jb, lay, 0, 0);
     const GroupDesc g{0, 1, lay.items, 0};
-    hipLaunchKernelGGL(k_setup, dim3(1), dim3(64), 0, st, d, g, ddesc, dgroups);
-    hipLaunchKernelGGL(k_reset, dim3(1), dim3(256), 0, st, ddesc, 1, dcounters, 64);
-    hipLaunchKernelGGL(k_prepare, dim3(64, 1), dim3(256), 0, st, ddesc);
+    hipLaunchKernelGGL(k_prepare_one, dim3(kPrepareBlocks), dim3(256), 0, st, d, g, ddesc, dgroups,
+                       dcounters);
     hipLaunchKernelGGL(k_box_bounds, dim3(box_blocks_of(lay), 1), dim3(256), 0, st, ddesc);
     hipLaunchKernelGGL(k_box_probe, dim3(1), dim3(kProbeThreads), 0, st, ddesc);
     if (lay.items > 0) {
@@ -2533,9 +2655,7 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
                            dcounters);
     }
     hipLaunchKernelGGL(k_stitch, dim3(stitch_blocks_of(jb)), dim3(kStitchThreads), 0, st, ddesc, 1);
-    hipLaunchKernelGGL(k_stats_moments, dim3(d.stat_blocks, 1), dim3(kStatThreads), 0, st, ddesc);
-    hipLaunchKernelGGL(k_stats_entropy, dim3(d.stat_blocks, 1), dim3(kStatThreads), 0, st, ddesc);
-    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, st, ddesc, 1);
+    launch_stats(ddesc, d.stat_blocks, 1, st);
     return hipGetLastError() == hipSuccess ? RQA_OK : RQA_EDEVICE;
 }
 
