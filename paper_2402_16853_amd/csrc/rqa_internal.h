@@ -151,6 +151,8 @@ int engine_launch(const std::vector<Job> &jobs, void *launch_scratch, void *stag
 // (jb.hist, stride jb.hist_stride) and flag (jb.flag) are the caller's.  No
 // allocation, no host-to-device copy.
 size_t engine_static_bytes(const Job &jb);
+size_t engine_static_charge(const Job &jb);   // of which this counts against the limit
+constexpr size_t kStaticExtraBytes = size_t(1) << 20;   // room for the rest
 int engine_launch_static(Job jb, void *scratch, hipStream_t stream);
 
 // Recurrence plot: the masked matrix of series a (b == nullptr) or the cross

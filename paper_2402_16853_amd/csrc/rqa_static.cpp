@@ -1,8 +1,8 @@
 // rqa_run_static: the whole RQA of one device series with no allocation of any
 // kind.  Every byte of device scratch the kernels need (launch descriptors,
-// work counters, the statistics record, the tail copy, the row-lead records
-// and the strip-edge summaries) lies in one file-scope device array of
-// RQA_STATIC_SCRATCH_BYTES, which each GPU the library runs on holds until the
+// work counters, the statistics record, the tail copy, the row-lead records,
+// the strip-edge summaries and their masks, the boxes) lies in one file-scope
+// device array of RQA_STATIC_SCRATCH_BYTES and a MiB, which each GPU the library runs on holds until the
 // process ends; the caller passes the series and the output histograms and
 // flag.  Calls that overlap on one GPU share the array and race.
 #include <hip/hip_runtime.h>
@@ -13,7 +13,8 @@
 
 // The scratch array.  In host code its name is only a stand-in: the device
 // address comes from hipGetSymbolAddress, per device.
-static __device__ __align__(256) unsigned char scratch[RQA_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char
+    scratch[RQA_STATIC_SCRATCH_BYTES + rqa::kStaticExtraBytes];
 
 namespace {
 
@@ -67,7 +68,9 @@ extern "C" int rqa_run_static(const rqa_params *p, const float *d_series, int64_
     jb.hist = d_hist;
     jb.hist_stride = hist_len;
     jb.flag = reinterpret_cast<int *>(d_flag);
-    if (engine_static_bytes(jb) > RQA_STATIC_SCRATCH_BYTES) return RQA_EBUDGET;
+    if (engine_static_charge(jb) > RQA_STATIC_SCRATCH_BYTES ||
+        engine_static_bytes(jb) > RQA_STATIC_SCRATCH_BYTES + kStaticExtraBytes)
+        return RQA_EBUDGET;
     void *base = nullptr;
     rc = scratch_on_current_device(&base);
     if (rc != RQA_OK) return rc;

@@ -18,9 +18,10 @@
 // A workgroup of W waves owns a strip of H = 64*W consecutive rows; wave w owns
 // rows R = R0 + 64w .. R+63, one row per lane, and walks the 64-column tiles
 // c = c0 .. c_last of its strip left to right.  The waves run as a pipeline:
-// wave w consumes the carries that wave w-1 produced for the same tile, through
-// an LDS ring per wave pair with produced / consumed counters (no workgroup
-// barrier per tile; a wave may run up to kRing tiles ahead of the one below).
+// wave w takes the open runs of a tile's columns and diagonals as wave w-1 left
+// them, from state rings in LDS (no workgroup barrier per tile; wave 0 may run
+// up to kRing tiles ahead of the last wave).  An open run is kept as the position
+// where it began, so a tile that changes no run's colour needs no work at all.
 //
 // Full-matrix lines from U:
 //  * a diagonal k >= w' of U and its mirror -k: each run counted twice;
@@ -89,10 +90,14 @@ constexpr int kCapD = 1024;    // LDS bins for diagonal lengths < kCapD
 constexpr int kCapV = 1024;    // LDS bins for vertical lengths < kCapV
 constexpr int kCapW = 6016;    // LDS bins for white-vertical lengths < kCapW
 constexpr int kMaxM = 6;       // embedding dimensions held in registers
-constexpr int kRing = 4;       // carry slots per pair of consecutive waves (tiles in flight)
+constexpr int kRing = 32;      // column-state slots: tiles wave 0 may run ahead of the last wave
+constexpr int kDiagRing = 64;  // diagonal-state slots (of 64 diagonals each); at most
+                               // kRing + kMaxWaves of them are live at once
+constexpr int kGroup = 8;      // column tiles classified at a time
 constexpr uint32_t kSpinLimit = 1u << 20;   // polls (~28 ms) before a neighbour wait gives up
 constexpr int kStitchThreads = 512;
 constexpr int kStitchBatch = 8;   // strips whose summaries a stitch thread loads at once
+static_assert(32 % kStitchBatch == 0, "a batch lies in one word of the masks");
 constexpr int kStitchCapV = 2048; // stitch LDS bins for vertical lengths < kStitchCapV (the
                                   // stitch joins the runs that cross strip edges: long ones)
 constexpr int kStatThreads = 256;
@@ -101,15 +106,15 @@ constexpr int kStatLengths = 2048;   // lengths per statistics block (8 per thre
                                      // loops are chains of dependent loads)
 constexpr int kPrepareBlocks = 64;   // k_prepare blocks per job
 constexpr int kCounters = 64;        // work counters of a launch
-// Column boxes (exact pruning of the predicate, see tile_bits): per 64-column
-// tile one record of kBoxStride floats holding (lo_k, hi_k) for the first
-// kBoxK coordinates.  The box array of a job starts with a header of
-// kBoxHeader floats whose first word tells whether the job uses the boxes (set
-// by k_box_probe).
+// Boxes (exact pruning of the predicate, see classify): of every kBoxVecs
+// consecutive delay vectors the smallest and the largest of each of the first
+// kBoxK coordinates, in planes (minimum, maximum of coordinate 0, 1, 2).  Jobs
+// of fewer than kBoxMinTiles column tiles take none: there the predicate is a
+// small part of a tile's time.
 constexpr int kBoxK = 3;
-constexpr int kBoxStride = 8;
-constexpr int kBoxHeader = 64;
-constexpr int kProbeThreads = 256;   // sampled (row block, tile) pairs per job
+constexpr int kBoxVecs = 8;
+constexpr int kBoxMinTiles = 128;
+constexpr int kBoxStride = 8;        // recurrence plot: floats per column tile's record
 
 // Device-side description of one job (one series or window).
 struct JobDesc {
@@ -156,7 +161,15 @@ struct JobDesc {
     uint32_t *stat_done;       // statistics blocks of this job that have finished
     JobStats *stats;           // device statistics record
     double *ent_part;          // [3][kStatMaxBlocks] entropy partial sums
-    float *box;                // column boxes (header + records), nullptr if none
+    float *boxr, *boxc;        // boxes of the rows' and the columns' vectors (one series:
+                               // the same), nullptr if none
+    int32_t ncr, ncc;          // entries per plane
+    uint32_t *vmask;           // which summaries were written (process_strip): per column
+    uint32_t *dfmask;          // tile, and per block of 64 diagonals at a strip's top edge and
+    uint32_t *dlmask;          // at its bottom edge, a bit per strip of the row band
+    int32_t mask_words;        // words per tile or block
+    int32_t kb_off;            // entry of diagonal block 0
+    int64_t mask_total;        // words of the three masks, which lie one after the other
     int32_t spin_limit;        // polls before a neighbour wait gives up (kSpinLimit)
     int32_t wait_bias;         // added to every wait target: 0, or (fault injection
                                // for tests) a bias no counter reaches
@@ -251,21 +264,27 @@ __device__ __forceinline__ void rotr64(uint32_t &lo, uint32_t &hi, uint32_t r) {
 
 // ---------------------------------------------------------------------------
 // Run state machine.  A line is cut into segments; `Run` is the open run at the
-// current position: colour (1 = recurrent), length so far, and whether it is the
+// current position: colour (1 = recurrent), where it began, and whether it is the
 // first run of the current segment (then it is recorded instead of counted).
+// Keeping the start rather than the length makes a tile without colour changes
+// free: nothing is added up for it.
 // ---------------------------------------------------------------------------
 struct Run {
     uint32_t color;
-    uint32_t len;
+    uint32_t start;     // position where the run began: column (rows of U), or row within the
+                        // strip (columns and diagonals: at most 64 * kMaxWaves, 10 bits)
     uint32_t first;
 };
 
-__device__ __forceinline__ uint32_t pack_run(const Run &r) {
-    return (r.len & 0xFFFFu) | (r.color << 16) | (r.first << 17);
+// Column and diagonal states in LDS: 16 bits.
+__device__ __forceinline__ uint16_t pack_run(const Run &r) {
+    return (uint16_t)((r.start & 0x3FFu) | (r.first << 14) | (r.color << 15));
 }
 __device__ __forceinline__ Run unpack_run(uint32_t v) {
-    return Run{(v >> 16) & 1u, v & 0xFFFFu, (v >> 17) & 1u};
+    return Run{(v >> 15) & 1u, v & 0x3FFu, (v >> 14) & 1u};
 }
+constexpr uint32_t kFreshColumn = 1u << 14;   // white from row 0 of the strip, the first run
+constexpr uint32_t kNoDiagonal = 0u;          // white, not first: nothing to record or count
 
 // Global-memory access through address-space-1 pointers.  The kernels reach
 // HBM through pointers held in the job descriptor, which the compiler cannot
@@ -283,105 +302,116 @@ __device__ __forceinline__ void g_or(int *p, int v) {
     __hip_atomic_fetch_or(glb(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// LDS bins, one after the other: diagonal (kCapD), vertical (kCapV), white
+// vertical (kCapW) lengths.
 struct Bins {
     uint32_t *d, *v, *w;
 };
 
-// Count `wt` lines of length len: LDS bin below the cap, else the global
-// histogram.  A length beyond the histogram (n) cannot occur for a correct run
-// and is reported through bit 1 of the job flag instead of being written.
-__device__ __forceinline__ void emit(uint32_t *bins, int cap, unsigned long long *glob, uint32_t len,
-                                     uint32_t wt, uint32_t n, int *flag) {
-    if (len < (uint32_t)cap && len <= n)
-        atomicAdd(bins + len, wt);
-    else if (len <= n)
-        g_add(glob + len, (unsigned long long)wt);
-    else
-        g_or(flag, 2);
-}
-
-enum LineKind { kHoriz = 0, kVert = 1, kDiag = 2 };
-
-struct LineCtx {
-    const JobDesc *jd;
-    Bins bins;
-    int64_t sum_idx;    // summary index of this line in this strip (vert / diag)
-    bool sum_ok;        // summary slot exists (diagonal inside the strip's range)
-    uint32_t row;       // row index (horizontal)
-};
-
-// A run of colour `c` and length `len` has ended.  DW: how many lines a
-// diagonal run stands for (2 in the upper triangle of a symmetric matrix, whose
-// mirror diagonal repeats it; 1 in a full matrix).
-template <int KIND, int DW = 2>
-__device__ __forceinline__ void finish_run(const LineCtx &lc, uint32_t c, uint32_t len, uint32_t first) {
-    const JobDesc &j = *lc.jd;
-    if (KIND == kDiag) {
-        if (first) {
-            if (lc.sum_ok) *glb(j.dfirst + lc.sum_idx) = (uint16_t)(c ? len : 0u);
-        } else if (c) {
-            emit(lc.bins.d, kCapD, j.hd, len, (uint32_t)DW, (uint32_t)j.hmax, j.flag);
-        }
-    } else if (KIND == kVert) {
-        if (first)
-            *glb(j.vfirst + lc.sum_idx) = (uint16_t)(len | (c << 15));
-        else if (c)
-            emit(lc.bins.v, kCapV, j.hv, len, 1u, (uint32_t)j.hmax, j.flag);
-        else
-            emit(lc.bins.w, kCapW, j.hw, len, 1u, (uint32_t)j.hmax, j.flag);
-    } else {
-        if (first) {
-            if (lc.sum_ok) *glb(j.hfirst + lc.sum_idx) = len | (c << 31);   // a row piece
-            else *glb(j.lead + lc.row) = len | (c << 31);
-        } else if (c)
-            emit(lc.bins.v, kCapV, j.hv, len, 1u, (uint32_t)j.hmax, j.flag);
-        else
-            emit(lc.bins.w, kCapW, j.hw, len, 1u, (uint32_t)j.hmax, j.flag);
-    }
-}
-
-// A run that starts and ends inside one window: 1 <= len <= 63, never the
-// first run of a segment, below every LDS bin cap and every histogram length.
-template <int KIND, int DW>
-__device__ __forceinline__ void emit_inner(const LineCtx &lc, uint32_t c, uint32_t len) {
-    if (KIND == kDiag) {
-        if (c) atomicAdd(lc.bins.d + len, (uint32_t)DW);
-    } else {
-        atomicAdd((c ? lc.bins.v : lc.bins.w) + len, 1u);
-    }
+// A length beyond the LDS bins goes to the global histogram; one beyond the
+// histogram cannot occur for a correct run and is reported through bit 1 of the
+// job flag instead of being written.
+__device__ __forceinline__ void emit_global(unsigned long long *glob, uint32_t len, uint32_t wt,
+                                            uint32_t n, int *flag) {
+    if (len <= n) g_add(glob + len, (unsigned long long)wt);
+    else g_or(flag, 2);
 }
 
 // Index of the lowest set bit of a non-zero 64-bit word.
 __device__ __forceinline__ uint32_t low_bit(uint64_t t) { return (uint32_t)__builtin_ctzll(t); }
 
-// Advance `st` over the bits [lo, hi) of x (win = mask of those bits),
-// finishing every run that ends there.  The colour changes are the set bits
-// of x ^ (x shifted by one, with the open run's colour entering at lo).  The
-// first change ends the open run (which may be a segment's first run or carry a
-// long length); every later run lies inside the window.
-template <int KIND, int DW = 2>
-__device__ __forceinline__ void run_segment(uint64_t x, uint64_t win, uint32_t lo, uint32_t hi,
-                                            Run &st, const LineCtx &lc) {
-    if (lo >= hi) return;
-    const uint64_t prev = ((x << 1) & ~(1ull << lo)) | ((uint64_t)st.color << lo);
-    uint64_t t = (x ^ prev) & win;
-    if (t == 0) {
-        st.len += hi - lo;
-        return;
-    }
-    uint32_t p = low_bit(t);
-    finish_run<KIND, DW>(lc, st.color, st.len + (p - lo), st.first);
-    uint32_t c = st.color ^ 1u;
-    uint32_t sp = p;
-    t &= t - 1ull;
+// Colour changes of x inside win, a window that begins at bit lo: the set bits of
+// x ^ (x shifted by one, with the open run's colour entering at lo).
+__device__ __forceinline__ uint64_t changes(uint64_t x, uint64_t win, uint32_t lo, uint32_t color) {
+    const uint64_t at = 1ull << (lo & 63u);
+    const uint64_t prev = ((x << 1) & ~at) | (color ? at : 0ull);
+    return (x ^ prev) & win;
+}
+
+// Runs between the changes t of one word (the first of them, at bit sp, begins a
+// run of colour c): each lies inside the word, is never a segment's first, and
+// is shorter than 64.  Returns the last change and the colour after it.
+__device__ __forceinline__ void inner_runs(const Bins &bins, uint64_t t, uint32_t &sp, uint32_t &c) {
     while (t) {
-        p = low_bit(t);
-        emit_inner<KIND, DW>(lc, c, p - sp);
+        const uint32_t p = low_bit(t);
+        atomicAdd((c ? bins.v : bins.w) + (p - sp), 1u);
         c ^= 1u;
         sp = p;
         t &= t - 1ull;
     }
-    st = Run{c, hi - sp, 0u};
+}
+
+// Advance the open run `st` of a column over the bits of y inside win (from bit 0;
+// bit p is row base + p of the strip), counting every run that ends there; the
+// strip's first run is recorded in *first (this lane's slot) instead.  Runs of
+// a strip are at most 64 * kMaxWaves = 512 long, so every one has an LDS bin
+// (after a neighbour wait has given up, states are arbitrary: the mask keeps the
+// index inside the bins).
+__device__ __forceinline__ void column_runs(const Bins &bins, uint64_t y, uint64_t win, uint32_t base,
+                                            Run &st, uint16_t *first, uint32_t lane) {
+    uint64_t t = changes(y, win, 0u, st.color);
+    if (t == 0) return;
+    uint32_t p = low_bit(t);
+    const uint32_t len = (base + p - st.start) & (kCapV - 1);
+    if (st.first) glb(first)[lane] = (uint16_t)(len | (st.color << 15));
+    else atomicAdd((st.color ? bins.v : bins.w) + len, 1u);
+    uint32_t c = st.color ^ 1u;
+    t &= t - 1ull;
+    inner_runs(bins, t, p, c);
+    st = Run{c, base + p, 0u};
+}
+
+// A run of a row of U has ended.  Such runs may be long.  A piece's first run is
+// recorded in slot[off] instead of counted.
+__device__ __forceinline__ void finish_row(const JobDesc &j, const Bins &bins, uint32_t color,
+                                           uint32_t len, uint32_t first, uint32_t *slot, uint32_t off) {
+    if (first) {
+        glb(slot)[off] = len | (color << 31);
+    } else if (len < (color ? (uint32_t)kCapV : (uint32_t)kCapW)) {
+        atomicAdd((color ? bins.v : bins.w) + len, 1u);
+    } else {
+        emit_global(color ? j.hv : j.hw, len, 1u, (uint32_t)j.hmax, j.flag);
+    }
+}
+
+// As column_runs, for a part of a diagonal: bits of d inside win, from bit lo.  White runs are not counted (and never a first
+// run), so one trip takes a whole black run.  DW: how many lines a diagonal run
+// stands for (2 in the upper triangle of a symmetric matrix, whose mirror
+// diagonal repeats it; 1 in a full matrix).
+template <int DW>
+__device__ __forceinline__ void diagonal_runs(const Bins &bins, uint64_t d, uint64_t win, uint32_t lo,
+                                              uint32_t base, Run &st, uint16_t *first, uint32_t lane,
+                                              bool slot_ok) {
+    const uint64_t t = changes(d, win, lo, st.color);
+    if (t == 0) return;
+    uint64_t starts = t & d, ends = t & ~d;
+    uint32_t s = st.start;                 // where the open or the next black run began
+    if (!st.color) {
+        s = base + low_bit(starts);        // (t's first change begins a black run)
+        starts &= starts - 1ull;
+    }
+    uint32_t f = st.first;
+    bool open = true;
+    while (ends) {
+        const uint32_t len = (base + low_bit(ends) - s) & (kCapD - 1);
+        if (f) { if (slot_ok) glb(first)[lane] = (uint16_t)len; }
+        else atomicAdd(bins.d + len, (uint32_t)DW);
+        f = 0u;
+        ends &= ends - 1ull;
+        open = starts != 0ull;
+        s = base + low_bit(starts | (1ull << 63));
+        starts &= starts - 1ull;
+    }
+    st = Run{open ? 1u : 0u, open ? s : 0u, open ? f : 0u};
+}
+
+// A black run of a diagonal that ends at a border.
+template <int DW>
+__device__ __forceinline__ void end_diagonal(const Bins &bins, uint32_t len, uint32_t f, uint16_t *first,
+                                             uint32_t lane, bool slot_ok) {
+    len &= kCapD - 1;
+    if (f) { if (slot_ok) glb(first)[lane] = (uint16_t)len; }
+    else atomicAdd(bins.d + len, (uint32_t)DW);
 }
 
 // Series pointer in the constant address space: loads through it with a
@@ -511,101 +541,180 @@ __device__ __forceinline__ bool box_decides(ConstF rec, const float *xr) {
     return __builtin_amdgcn_ballot_w64(!out) == 0ull;
 }
 
+// Recurrence of eight columns for this lane's row: bit b of the result is set when
+// column b of the chunk at `cb` is NOT recurrent (on top of acc << 8).
+// m >= 5 takes the first coordinate's differences first: when no lane of the
+// wave has |d_0| <= thr0, all 8 x 64 pairs are non-recurrent and the other
+// coordinates are not evaluated.  (Their 40-48 column coordinates do not fit
+// the SGPRs left otherwise, and without the loads pinned ahead of the test the
+// compiler rebuilt their addresses with long chains of 64-bit scalar adds:
+// measured 29% slower on the L1, m = 5 windows.)
+template <int NORM, int M>
+__device__ __forceinline__ uint32_t chunk_nonrec(uint32_t acc, ConstF cb, int tau, const float *xr,
+                                                 const float *__restrict__ rowp, int m, float thr,
+                                                 float thr0) {
+    if (M >= 5) {
+        // All of the chunk's coordinates are loaded up front (the empty asm
+        // keeps the compiler from sinking the loads of the other coordinates
+        // into the branch, which would add a second wait).
+        float d0[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            d0[b] = cb[b] - xr[0];
+#pragma unroll
+            for (int k = 1; k < (M > 0 ? M : 1); ++k) {
+                const float ck = cb[b + k * tau];
+                asm volatile("" ::"s"(ck));
+            }
+        }
+        const float near =
+            fminf(fminf(fminf(fabsf(d0[0]), fabsf(d0[1])), fminf(fabsf(d0[2]), fabsf(d0[3]))),
+                  fminf(fminf(fabsf(d0[4]), fabsf(d0[5])), fminf(fabsf(d0[6]), fabsf(d0[7]))));
+        if (__builtin_amdgcn_ballot_w64(near <= thr0) == 0ull) return (acc << 8) | 0xFFu;
+#pragma unroll
+        for (int b = 7; b >= 0; --b)
+            acc = __builtin_amdgcn_alignbit(acc, nonrec_sign_d0<NORM, M>(d0[b], cb + b, tau, xr, thr), 31);
+    } else if (M > 0) {
+        // One uniform pointer per coordinate: each coordinate's 8 columns are
+        // then one s_load_dwordx8 at a fixed offset (indexing cb[b + k*tau]
+        // instead made the compiler build 8*m addresses with 64-bit adds).
+        ConstF ck[M > 0 ? M : 1];
+#pragma unroll
+        for (int k = 0; k < (M > 0 ? M : 1); ++k) ck[k] = cb + k * tau;
+#pragma unroll
+        for (int b = 7; b >= 0; --b)
+            acc = __builtin_amdgcn_alignbit(acc, nonrec_sign_rows<NORM, M>(ck, b, xr, thr), 31);
+    } else {
+        for (int b = 7; b >= 0; --b)
+            acc = __builtin_amdgcn_alignbit(acc, nonrec_sign_dyn<NORM>(cb + b, rowp, m, tau, thr), 31);
+    }
+    return acc;
+}
+
+// The thresholds are uniform, but as scalar operands they would make the
+// subtraction and the compare read an SGPR too; VALU instructions with only
+// VGPR operands issue faster on gfx950 (measured: the six-instruction
+// L-infinity column sustains ~1.5 instead of ~1.2 wave-instructions per clock
+// per CU).  The empty asm pins the copies in VGPRs.
+__device__ __forceinline__ float in_vgpr(float v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Recurrence bits of one 64x64 tile for this lane's row: bit b <-> column
 // jbase + b.  `cols` points at the coordinate of column jbase (uniform).  The 64
 // columns are taken in eight chunks of 8 (highest first), each fully unrolled,
 // so that at most 8*m column coordinates are live in SGPRs (chunks of 16 left
 // too few SGPRs for the rest of the kernel, which then spilled into VGPR lanes;
 // measured 10% slower).
-// Exact pruning, two variants:
-//  * `box` (this tile's box record, or nullptr): when the box decides every
-//    row of the wave, the tile has no recurrent cell and no column is
-//    evaluated.  Otherwise every pair is evaluated: a box test per 8-column
-//    chunk decides far more chunks on smooth series (Lorenz: 64% of the chunks
-//    of undecided tiles, against 24% for the first-coordinate test), but its
-//    record took SGPRs the kernel did not have (spills) and measured slower
-//    than evaluating the chunk;
-//  * m >= 5 (the first-coordinate test): each chunk first takes the first
-//    coordinate's differences; when no lane of the wave has |d_0| <= thr0 in
-//    the chunk, all 8 x 64 pairs are non-recurrent and the other coordinates
-//    are not evaluated.
 template <int NORM, int M>
 __device__ __forceinline__ void tile_bits(ConstF cols, int tau, const float *xr,
                                           const float *__restrict__ rowp, int m, float thr_s,
-                                          float thr0_s, ConstF box, uint32_t &lo, uint32_t &hi) {
-    // The thresholds are uniform, but as scalar operands they would make the
-    // subtraction and the compare read an SGPR too; VALU instructions with only
-    // VGPR operands issue faster on gfx950 (measured: the six-instruction
-    // L-infinity column sustains ~1.5 instead of ~1.2 wave-instructions per
-    // clock per CU).  The empty asm pins the copies in VGPRs.
-    float thr = thr_s, thr0 = thr0_s;
-    asm volatile("" : "+v"(thr), "+v"(thr0));
-    if (M > 0 && box != nullptr && box_decides<M>(box, xr)) {
-        lo = 0u;
-        hi = 0u;
-        return;
-    }
+                                          float thr0_s, uint32_t &lo, uint32_t &hi) {
+    const float thr = in_vgpr(thr_s), thr0 = in_vgpr(thr0_s);
 #pragma unroll 1
     for (int half = 1; half >= 0; --half) {
         uint32_t acc = 0;
 #pragma unroll 1
-        for (int sub = 3; sub >= 0; --sub) {
-            const int b0 = half * 32 + sub * 8;
-            ConstF cb = cols + b0;
-            if (M > 0) {
-                // Embedding dimensions of 5 and 6 always take the first-
-                // coordinate path: their 40-48 column coordinates do not fit
-                // the SGPRs left, and without the loads pinned ahead of the
-                // test the compiler rebuilt their addresses with long chains
-                // of 64-bit scalar adds (measured 29% slower on the L1, m = 5
-                // windows).
-                if (M >= 5) {
-                    // All of the chunk's coordinates are loaded up front (the
-                    // empty asm keeps the compiler from sinking the loads of
-                    // the other coordinates into the branch, which would add a
-                    // second wait); the first coordinate's differences decide
-                    // whether the rest is evaluated.
-                    float d0[8];
+        for (int sub = 3; sub >= 0; --sub)
+            acc = chunk_nonrec<NORM, M>(acc, cols + half * 32 + sub * 8, tau, xr, rowp, m, thr, thr0);
+        if (half) hi = ~acc; else lo = ~acc;
+    }
+}
+
+// Bytes 0..3 = 0xFF where bit 0..3 of `four` is set.
+__device__ __forceinline__ uint32_t spread4(uint32_t four) {
+    return ((four * 0x00204081u) & 0x01010101u) * 0xFFu;
+}
+
+// The same for the chunks in `eval` only (bit q: columns 8q .. 8q+7); all pairs of
+// the chunks in `ones` are recurrent, and those of the other chunks are not.
+template <int NORM, int M>
+__device__ __forceinline__ void tile_bits_some(ConstF cols, int tau, const float *xr,
+                                               const float *__restrict__ rowp, int m, float thr_s,
+                                               float thr0_s, uint32_t eval, uint32_t ones,
+                                               uint32_t &lo, uint32_t &hi) {
+    const float thr = in_vgpr(thr_s), thr0 = in_vgpr(thr0_s);
+    uint32_t nlo = ~spread4(ones & 15u), nhi = ~spread4(ones >> 4);   // not recurrent
+#pragma unroll 1
+    while (eval) {
+        const int q = __builtin_ctz(eval);
+        eval &= eval - 1u;
+        // eight bits on top of ones, turned to the chunk's place
+        const uint32_t non = chunk_nonrec<NORM, M>(0xFFFFFFu, cols + q * 8, tau, xr, rowp, m, thr, thr0);
+        const uint32_t turned = __builtin_amdgcn_alignbit(non, non, (uint32_t)(32 - 8 * q) & 31u);
+        if (q < 4) nlo &= turned; else nhi &= turned;
+    }
+    lo = ~nlo;
+    hi = ~nhi;
+}
+
+// Exact classes of the kGroup column tiles of group cg against the 64 rows of
+// block rb, from the boxes: bit 8*i + q of `act` is clear when no pair of the
+// block's rows and columns 8q .. 8q+7 of the group's tile i can be recurrent,
+// bit 8*i + q of `full` is set when every such pair is (the predicate need not be
+// evaluated for either).  One lane per 8-column box; the block's rows are eight
+// boxes of 8 rows, read as scalars.
+// Why it is exact: with y in [yn, yx] and x in [xn, xx], FP32 subtraction being
+// monotone in each operand, |fl(y - x)| is at least max(fl(yn - xx),
+// fl(xn - yx), 0) and at most max(|fl(yn - xx)|, |fl(yx - xn)|); sums, products
+// and maxima of such bounds, rounded in the predicate's own order, bound the
+// accumulated distance on the same side.  A lower bound over the first
+// min(m, kBoxK) coordinates bounds the whole distance (later terms are not
+// negative); the upper bound takes every coordinate, so m <= kBoxK only.
+// Cost: about 90 VALU instructions per 8 tiles.  On the 1M-point Lorenz series
+// 2.0 of 8 chunks per tile are left to evaluate (4.6 with one box per 64
+// columns), on the 1M-point sine 0.6.
+template <int NORM, int M>
+__device__ __forceinline__ void classify(const JobDesc &j, int rb, int cg, int lane, uint64_t &act,
+                                         uint64_t &full) {
+    constexpr int K = M < kBoxK ? M : kBoxK;
+    float yn[K], yx[K];
+    const auto pc = glb(j.boxc) + (int64_t)cg * (kGroup * 8) + lane;
 #pragma unroll
-                    for (int b = 0; b < 8; ++b) {
-                        d0[b] = cb[b] - xr[0];
+    for (int k = 0; k < K; ++k) {
+        yn[k] = pc[(int64_t)(2 * k) * j.ncc];
+        yx[k] = pc[(int64_t)(2 * k + 1) * j.ncc];
+    }
+    const ConstF pr = to_const(j.boxr) + (int64_t)rb * 8;
+    const int64_t ncr = j.ncr;
+    float best = INFINITY, worst = 0.0f;
+#pragma unroll 1
+    for (int r0 = 0; r0 < 8; r0 += 4) {
+        float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                        for (int k = 1; k < (M > 0 ? M : 1); ++k) {
-                            const float ck = cb[b + k * tau];
-                            asm volatile("" ::"s"(ck));
-                        }
-                    }
-                    const float near =
-                        fminf(fminf(fminf(fabsf(d0[0]), fabsf(d0[1])), fminf(fabsf(d0[2]), fabsf(d0[3]))),
-                              fminf(fminf(fabsf(d0[4]), fabsf(d0[5])), fminf(fabsf(d0[6]), fabsf(d0[7]))));
-                    if (__builtin_amdgcn_ballot_w64(near <= thr0) == 0ull) {
-                        acc = (acc << 8) | 0xFFu;
-                    } else {
+        for (int k = 0; k < K; ++k) {
 #pragma unroll
-                        for (int b = 7; b >= 0; --b)
-                            acc = __builtin_amdgcn_alignbit(
-                                acc, nonrec_sign_d0<NORM, M>(d0[b], cb + b, tau, xr, thr), 31);
-                    }
-                } else {
-                    // One uniform pointer per coordinate: each coordinate's 8
-                    // columns are then one s_load_dwordx8 at a fixed offset
-                    // (indexing cb[b + k*tau] instead made the compiler build
-                    // 8*m addresses with 64-bit scalar adds).
-                    ConstF ck[M > 0 ? M : 1];
-#pragma unroll
-                    for (int k = 0; k < (M > 0 ? M : 1); ++k) ck[k] = cb + k * tau;
-#pragma unroll
-                    for (int b = 7; b >= 0; --b)
-                        acc = __builtin_amdgcn_alignbit(
-                            acc, nonrec_sign_rows<NORM, M>(ck, b, xr, thr), 31);
-                }
-            } else {
-                for (int b = 7; b >= 0; --b)
-                    acc = __builtin_amdgcn_alignbit(
-                        acc, nonrec_sign_dyn<NORM>(cb + b, rowp, m, tau, thr), 31);
+            for (int r = 0; r < 4; ++r) {
+                const float xn = pr[(2 * k) * ncr + r0 + r], xx = pr[(2 * k + 1) * ncr + r0 + r];
+                const float g = fmaxf(fmaxf(yn[k] - xx, xn - yx[k]), NORM == RQA_NORM_LINF ? a[r] : 0.0f);
+                if (NORM == RQA_NORM_LINF) a[r] = g;
+                else if (NORM == RQA_NORM_L1) a[r] = a[r] + g;
+                else a[r] = a[r] + g * g;
             }
         }
-        if (half) hi = ~acc; else lo = ~acc;
+        best = fminf(fminf(best, fminf(a[0], a[1])), fminf(a[2], a[3]));
+        if (M <= kBoxK) worst = fmaxf(fmaxf(worst, fmaxf(a[0], a[1])), fmaxf(a[2], a[3]));
+    }
+    const float thr = j.thr;
+    act = __builtin_amdgcn_ballot_w64(best <= thr);
+    full = 0ull;
+    if (M <= kBoxK && __builtin_amdgcn_ballot_w64(worst <= thr) != 0ull) {
+        float a = 0.0f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            float bn = INFINITY, bx = -INFINITY;   // the whole block's range
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                bn = fminf(bn, pr[(2 * k) * ncr + r]);
+                bx = fmaxf(bx, pr[(2 * k + 1) * ncr + r]);
+            }
+            const float g = fmaxf(fabsf(yn[k] - bx), fabsf(yx[k] - bn));
+            if (NORM == RQA_NORM_LINF) a = fmaxf(a, g);
+            else if (NORM == RQA_NORM_L1) a = a + g;
+            else a = a + g * g;
+        }
+        full = __builtin_amdgcn_ballot_w64(worst <= thr && a <= thr);
     }
 }
 
@@ -650,6 +759,30 @@ __device__ float box_lo(float cmin, float b) {
 // Non-finite input is noted per block (a plain store: the flag itself is being
 // cleared by block 0 of this kernel) and enters the flag in the statistics.
 // ---------------------------------------------------------------------------
+// Boxes of `count` delay vectors: one thread per (box, coordinate).  Boxes
+// without a vector (the planes are padded to whole groups) get an empty range,
+// which every test takes as "no pair recurs".
+__device__ __forceinline__ void make_boxes(float *box, int entries, const float *s, int count, int m,
+                                           int tau, int64_t tid, int64_t stride) {
+    const int K = m < kBoxK ? m : kBoxK;
+    for (int64_t t = tid; t < (int64_t)entries * K; t += stride) {
+        const int k = (int)(t / entries);
+        const int64_t q = t - (int64_t)k * entries;
+        float lo = INFINITY, hi = -INFINITY;
+        const auto x = glb(s) + (int64_t)k * tau;
+#pragma unroll
+        for (int u = 0; u < kBoxVecs; ++u) {
+            const int64_t i = q * kBoxVecs + u;
+            if (i < count) {
+                lo = fminf(lo, x[i]);
+                hi = fmaxf(hi, x[i]);
+            }
+        }
+        glb(box)[(int64_t)(2 * k) * entries + q] = lo;
+        glb(box)[(int64_t)(2 * k + 1) * entries + q] = hi;
+    }
+}
+
 __device__ __forceinline__ void prepare_job(const JobDesc &j, int *counters) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -666,6 +799,7 @@ __device__ __forceinline__ void prepare_job(const JobDesc &j, int *counters) {
     }
     if (tid < (int64_t)(sizeof(JobStats) / 8))
         reinterpret_cast<unsigned long long *>(j.stats)[tid] = 0ull;
+    for (int64_t t = tid; t < j.mask_total; t += stride) j.vmask[t] = 0u;
     bool bad = false;
     if (j.mode != kModeMatrix) {   // a given matrix has no series
         for (int64_t t = tid; t < j.n_points; t += stride) bad |= !__builtin_isfinite(j.s[t]);
@@ -676,6 +810,10 @@ __device__ __forceinline__ void prepare_job(const JobDesc &j, int *counters) {
         float *tail = const_cast<float *>(j.tail);
         for (int64_t t = tid; t < j.tail_len; t += stride)
             tail[t] = base + t < j.n_points_b ? j.sb[base + t] : 0.0f;
+    }
+    if (j.boxc != nullptr) {
+        make_boxes(j.boxc, j.ncc, j.sb, j.nb, j.m, j.tau, tid, stride);
+        if (j.boxr != j.boxc) make_boxes(j.boxr, j.ncr, j.s, j.n, j.m, j.tau, tid, stride);
     }
     const int any = __syncthreads_or(bad ? 1 : 0);
     if (threadIdx.x == 0) j.nonfinite[blockIdx.x] = any ? 1 : 0;
@@ -697,81 +835,15 @@ __global__ void k_prepare_one(const JobDesc d, const GroupDesc g, JobDesc *ddesc
     prepare_job(d, counters);
 }
 
-// Column boxes of every column tile of a job (grid.y = job; one thread per
-// (tile, coordinate)).  Only columns < nb count.
-__global__ void k_box_bounds(const JobDesc *__restrict__ jobs) {
-    const JobDesc &j = jobs[blockIdx.y];
-    if (j.box == nullptr) return;
-    const int K = j.m < kBoxK ? j.m : kBoxK;
-    const int64_t total = (int64_t)(j.c_last + 1) * K;
-    const float b = j.thr0;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(t % K);
-        const int64_t c = t / K;
-        const int64_t j0 = c * 64;
-        const int64_t j1 = j0 + 64 < j.nb ? j0 + 64 : j.nb;
-        float cmin = INFINITY, cmax = -INFINITY;
-        const float *col = j.sb + (int64_t)k * j.tau;
-        for (int64_t q = j0; q < j1; ++q) {
-            const float v = col[q];
-            cmin = fminf(cmin, v);
-            cmax = fmaxf(cmax, v);
-        }
-        float *rec = j.box + kBoxHeader + c * kBoxStride;
-        rec[2 * k] = box_lo(cmin, b);
-        rec[2 * k + 1] = box_hi(cmax, b);
-    }
-}
-
-// Whether a job uses its boxes: one block per job samples kProbeThreads
-// (64-row block, column tile) pairs of the evaluated region and counts the
-// tiles whose box decides all 64 rows.  A decided tile saves its whole
-// predicate, an undecided one costs the test (one scalar load and a compare
-// per coordinate), so the boxes are used when at least 1 in 64 sampled tiles
-// is decided.  Only speed depends on this.
-__global__ void __launch_bounds__(kProbeThreads) k_box_probe(const JobDesc *__restrict__ jobs) {
-    const JobDesc &j = jobs[blockIdx.x];
-    if (j.box == nullptr) return;
-    __shared__ int decided, sampled;
-    if (threadIdx.x == 0) { decided = 0; sampled = 0; }
-    __syncthreads();
-    const int K = j.m < kBoxK ? j.m : kBoxK;
-    // splitmix64 of (job, thread): the sample position
-    uint64_t z = ((uint64_t)blockIdx.x << 32) + threadIdx.x + 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    const int blocks = (j.n + 63) / 64;
-    const int r0 = (int)((z & 0xFFFFFFFFull) % (uint64_t)blocks) * 64;
-    const int cmin_tile = j.mode == kModeAuto ? (r0 + j.wp) / 64 : 0;
-    if (cmin_tile <= j.c_last) {
-        const int c = cmin_tile + (int)((z >> 32) % (uint64_t)(j.c_last - cmin_tile + 1));
-        const float *rec = j.box + kBoxHeader + (int64_t)c * kBoxStride;
-        bool all = true;
-        for (int i = r0; i < r0 + 64 && all; ++i) {
-            const int ii = i < j.n ? i : j.n - 1;
-            bool out = false;
-            for (int k = 0; k < K; ++k) {
-                const float x = j.s[ii + (int64_t)k * j.tau];
-                out = out || x < rec[2 * k] || x > rec[2 * k + 1];
-            }
-            all = out;
-        }
-        if (all) atomicAdd(&decided, 1);
-        atomicAdd(&sampled, 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        reinterpret_cast<int *>(j.box)[0] = (sampled > 0 && 64 * decided >= sampled) ? 1 : 0;
-}
-
 // Move a one-job launch to row band b: its strips [b K, min((b+1) K, S)), the
 // origin of their summary slots, the band's work items, and a fresh work
-// counter (K strips per band, S strips in all).
+// counter (K strips per band, S strips in all); and clear the masks.
 __global__ void k_band(JobDesc *jobs, GroupDesc *groups, int *counters, int b) {
-    if (threadIdx.x != 0) return;
     JobDesc &j = jobs[0];
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < j.mask_total;
+         t += (int64_t)gridDim.x * blockDim.x)
+        j.vmask[t] = 0u;
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
     const int lo = b * j.band_strips;
     const int hi = lo + j.band_strips < j.nstrips ? lo + j.band_strips : j.nstrips;
     j.s_lo = lo;
@@ -785,46 +857,57 @@ __global__ void k_band(JobDesc *jobs, GroupDesc *groups, int *counters, int b) {
 // Kernel 2: the fused tile pass.  Persistent workgroups pull (job, strip) work
 // items of one (norm, m) group from a counter.
 // ---------------------------------------------------------------------------
-// LDS of a tile workgroup (dynamic shared memory): privatised histogram bins;
-// for each pair of consecutive waves a ring of kRing carry slots (vertical and
-// diagonal states of one tile, one u32 per lane); the produced / consumed tile
-// counters of those rings; the current work item.  Sized for the launch's wave
-// count (48 KB for 8 waves).  The kernel is compiled for six waves per SIMD (at
-// most 80 VGPRs, no spills), i.e. three 8-wave workgroups per CU.
+// LDS of a tile workgroup (dynamic shared memory): privatised histogram bins; the
+// state rings, written in place by one wave after the other:
+//  * vst: open runs of the columns of tile c, in slot c mod kRing,
+//  * dst: open runs of the 64 diagonals of block k (diagonals 64k .. 64k+63), in
+//    slot k mod kDiagRing.  Wave w meets block k as the upper part of tile k + rb
+//    (rb its row block) and as the lower part of the tile after; then the block
+//    is wave w+1's;
+// of wave w, in entry w + 1 of each: the number of tiles it is done with, a note
+// per slot on what the states it leaves there hold (kHas*; entry 0 is what wave 0
+// finds: fresh columns); which summaries of the 32 tiles at hand were written; the
+// current work item.  44 KB.  The kernel is compiled for six waves per SIMD (at
+// most 80 VGPRs), i.e. three 8-wave workgroups per CU.
 struct StripLds {
     uint32_t *bd, *bv, *bw;
-    uint32_t *vslot;    // [kRing][waves][64]
-    uint32_t *dslot;    // [kRing][waves][64]
-    int *prod;          // [kMaxWaves]: tiles whose carries wave w has written
-    int *cons;          // [kMaxWaves]: tiles whose carries wave w+1 has read
+    uint16_t *vst;      // [kRing][64]
+    uint16_t *dst;      // [kDiagRing][64]
+    int *prog;          // [kMaxWaves + 1]
+    uint8_t *note;      // [kMaxWaves + 1][kRing]
+    uint32_t *words;    // columns, top-edge diagonals, bottom-edge diagonals
     int *item;
-    int nw;
-    __device__ uint32_t &vs(int buf, int w, int lane) { return vslot[(buf * nw + w) * 64 + lane]; }
-    __device__ uint32_t &ds(int buf, int w, int lane) { return dslot[(buf * nw + w) * 64 + lane]; }
+    int *bad;           // a wait gave up in this item: its bins are not counted
+    __device__ uint16_t &vs(int c, int lane) { return vst[(c & (kRing - 1)) * 64 + lane]; }
+    __device__ uint16_t &ds(int k, int lane) { return dst[(k & (kDiagRing - 1)) * 64 + lane]; }
 };
 
-__host__ __device__ constexpr size_t strip_lds_bytes(int waves) {
-    return sizeof(uint32_t) * ((size_t)kCapD + kCapV + kCapW + 2 * (size_t)kRing * waves * 64 +
-                               2 * kMaxWaves) + 16;
-}
+// Notes on a tile's states as a wave leaves them to the wave below: some column
+// or (outgoing) diagonal run is open and black / white; some column state is not
+// kFreshColumn any more.
+constexpr uint32_t kHasBlack = 1u, kHasWhite = 2u, kStored = 4u;
 
-// Wait (wave-uniform) until the counter reaches `target`.  Each wait is bounded:
-// past `limit` polls it gives up and returns false, so a wave never hangs.
-__device__ __forceinline__ bool wait_counter(int *ctr, int target, const JobDesc &j) {
+constexpr size_t kStripLdsBytes =
+    sizeof(uint32_t) * ((size_t)kCapD + kCapV + kCapW) + sizeof(uint16_t) * 64 * (kRing + kDiagRing) +
+    sizeof(int) * (kMaxWaves + 1) + (size_t)(kMaxWaves + 1) * kRing + 3 * sizeof(uint32_t) + 16;
+
+// Wait (wave-uniform) until the counter reaches `target`; returns its value.  Each
+// wait is bounded: past j.spin_limit polls it gives up (ok = false), so a wave
+// never hangs.
+__device__ __forceinline__ int wait_counter(int *ctr, int target, const JobDesc &j, bool &ok) {
     int v = __builtin_amdgcn_readfirstlane(
         __hip_atomic_load(ctr, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-    if (v >= target) return true;
-    // The bound is read only when the first poll fails (most waits need none;
-    // reading it, and the target's bias, from the descriptor on every wait
-    // cost 2.5 ms of 74 on the 1M-point workload).
+    if (v >= target) return v;
+    // The bound is read only when the first poll fails (most waits need none).
     const uint32_t limit = (uint32_t)j.spin_limit;
     for (uint32_t spin = 0; spin < limit; ++spin) {
         __builtin_amdgcn_s_sleep(1);
         v = __builtin_amdgcn_readfirstlane(
             __hip_atomic_load(ctr, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-        if (v >= target) return true;
+        if (v >= target) return v;
     }
-    return false;
+    ok = false;
+    return v;
 }
 
 __device__ __forceinline__ void publish_counter(int *ctr, int value) {
@@ -832,27 +915,40 @@ __device__ __forceinline__ void publish_counter(int *ctr, int value) {
 }
 
 __device__ void flush_bins(const StripLds &L, const JobDesc &j) {
-    const int bins = j.hmax + 1 < kCapW ? j.hmax + 1 : kCapW;   // no line is longer than hmax
+    // No line is longer than hmax.  (Where a wait gave up, the job is flagged as
+    // failed, and bins may hold any length: all are cleared.)
+    const int bins = j.hmax + 1 < kCapW && !*L.bad ? j.hmax + 1 : kCapW;
     for (int t = threadIdx.x; t < bins; t += blockDim.x) {
         if (t < kCapD) {
             const uint32_t v = L.bd[t];
-            if (v) { g_add(j.hd + t, (unsigned long long)v); L.bd[t] = 0; }
+            if (v) { if (t <= j.hmax) g_add(j.hd + t, (unsigned long long)v); L.bd[t] = 0; }
         }
         if (t < kCapV) {
             const uint32_t v = L.bv[t];
-            if (v) { g_add(j.hv + t, (unsigned long long)v); L.bv[t] = 0; }
+            if (v) { if (t <= j.hmax) g_add(j.hv + t, (unsigned long long)v); L.bv[t] = 0; }
         }
         const uint32_t v = L.bw[t];
-        if (v) { g_add(j.hw + t, (unsigned long long)v); L.bw[t] = 0; }
+        if (v) { if (t <= j.hmax) g_add(j.hw + t, (unsigned long long)v); L.bw[t] = 0; }
     }
 }
 
-// One strip of one job.  MODE kModeAuto: the upper triangle U of the symmetric
-// recurrence matrix of one series (horizontal runs are the row segments of the
-// full columns, joined through the band by the stitch).  MODE kModeCross /
-// kModeMatrix: a full n x nb matrix that is not symmetric (every diagonal and
-// every column walked once; no horizontal runs).
-template <int NORM, int M, int MODE>
+// One (strip, column segment) block of one job.  MODE kModeAuto: the upper
+// triangle U of the symmetric recurrence matrix of one series (horizontal runs
+// are the row segments of the full columns, joined through the band by the
+// stitch).  MODE kModeCross / kModeMatrix: a full n x nb matrix that is not
+// symmetric (every diagonal and every column walked once; no horizontal runs).
+//
+// What bounds it, and how it is cut.  A tile costs its predicate (6-11 VALU
+// instructions per column), its run extraction, and bookkeeping.  Smooth
+// series leave most tiles without a colour change.  So
+//  * the wave classifies kGroup tiles at a time from the boxes, and evaluates
+//    only the 8-column chunks that the boxes leave open;
+//  * open runs are kept by their start, in place; a tile of one colour in
+//    which every open run has that colour is passed over, up to a group of
+//    tiles at a time, with no state read or written.
+// BOX: classify the tiles (below); without, every tile is evaluated, and the
+// code for classes takes no registers from it.
+template <int NORM, int M, int MODE, bool BOX>
 __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
     static_assert(kMaxWaves <= 8, "LDS budget assumes at most 8 waves per workgroup");
     constexpr bool FULL = MODE != kModeAuto;
@@ -860,54 +956,67 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
     const int nw = blockDim.x >> 6;
+    const bool bottom = wave == nw - 1;                    // records the strip's bottom edge
     const int n = j.n, wp = j.wp, H = j.H, tau = j.tau;   // n: rows
+    const float *const sb = j.sb;
     const int nb = FULL ? j.nb : n;                        // columns
     const int64_t band = j.theiler;                        // full matrix: cells |i-j| < band are 0
-    // Work item: a (strip, column segment) block; with one segment per strip
-    // (auto mode, many strips) the whole strip.
     const int G = j.segs;
     const bool BLK = FULL || G > 1;              // per-block diagonal summaries
-    const int lstrip = item / G;                 // strip within the row band (auto)
+    const int lstrip = item / G;                 // strip within the row band
     const int strip = j.s_lo + lstrip;
     const int seg = item - lstrip * G;
     const int R0 = strip * H;
-    const int R = R0 + 64 * wave;
+    const int Rl = 64 * wave;                    // first row of this wave within the strip
+    const int R = R0 + Rl;
+    const int rb = R >> 6;
     const int i = R + lane;                      // this lane's row
+    // Column tiles [ca, cb) of this block: the segment's cut to the strip's.
+    // A block that does not start at the strip's first tile begins with the
+    // row and diagonal runs that enter through its left edge, of unknown
+    // history.
     const int c0 = FULL ? 0 : (R0 + wp) >> 6;
-    const int T = j.c_last - c0 + 1;             // tiles of the strip
-    // Tiles [ta, tb) of this block (relative to c0): the segment's absolute
-    // column tiles cut to the strip's.  A block that does not start at the
-    // strip's first tile begins with the row and diagonal runs that enter
-    // through its left edge, of unknown history.
-    const int sa = j.seg_base + seg * j.seg_tiles - c0;
-    const int ta = sa > 0 ? sa : 0;
-    const int tb = sa + j.seg_tiles < T ? sa + j.seg_tiles : T;
-    if (ta >= tb) return;                        // the triangle leaves this block empty
-    const bool seg_start = ta > 0;
-    // Some row of this wave has cells to walk, and the first tile that has.
+    const int sa = j.seg_base + seg * j.seg_tiles;
+    const int ca = sa > c0 ? sa : c0;
+    const int cb = sa + j.seg_tiles < j.c_last + 1 ? sa + j.seg_tiles : j.c_last + 1;
+    if (ca >= cb) return;                        // the triangle leaves this block empty
+    const bool seg_start = ca > c0;
+    // The first tile in which this wave has cells (cb: none).
     const bool wave_has_u = FULL ? R <= n - 1 : R + wp <= n - 1;
-    const int cfirst = FULL ? 0 : (R + wp) >> 6;
+    int cw = FULL ? ca : (R + wp) >> 6;
+    cw = !wave_has_u || cw > cb ? cb : (cw < ca ? ca : cw);
     const int64_t soff = FULL ? 0 : strip_offset(strip, n, wp, H) - j.soff_lo;
     // Summary slots: columns -- per (strip, column), in triangular strip order
     // from the row band's first strip in auto mode; diagonals -- auto with one
     // segment: per (strip, diagonal of U) in the same order; otherwise per
-    // work item (a (strip, segment) block) j.dw slots for the diagonals
-    // k = x0-(R0+H-1) .. x1-1-R0 that have a cell in the block's columns [x0, x1).
-    const int x0 = (c0 + ta) * 64;
-    const int x1 = (c0 + tb) * 64 < nb ? (c0 + tb) * 64 : nb;
+    // work item j.dw slots for the diagonals k = x0-(R0+H-1) .. x1-1-R0 that
+    // have a cell in the block's columns [x0, x1).
+    const int x0 = ca * 64;
+    const int x1 = cb * 64 < nb ? cb * 64 : nb;
     const int64_t vbase = FULL ? (int64_t)lstrip * nb : soff - R0 - wp;
     const int64_t dbase = BLK ? (int64_t)item * j.dw + (R0 + H - 1) - x0 : soff - wp;
     const int kmin = BLK ? (FULL || x0 - (R0 + H - 1) > wp ? x0 - (R0 + H - 1) : wp) : wp;
     const int kmax = BLK ? x1 - 1 - R0 : n - 1 - R0;
-    auto dok = [&](int k) -> bool { return k >= kmin && k <= kmax; };
-
-    // Column boxes of this job, when the probe chose to use them.
-    // (The header is read as a scalar load, so `box` is known to be uniform
-    // and the records are read with scalar loads too.)
-    ConstF box = nullptr;
-    if constexpr (MODE != kModeMatrix && M > 0) {
-        const ConstF bx = to_const(j.box);
-        if (bx != nullptr && __float_as_int(bx[0]) != 0) box = bx + kBoxHeader;
+    // (Interior tiles have slots for all their diagonals, but for lane 0's lower
+    // part in a block's first tile, which is empty.)
+    auto dok = [&](int k, bool interior, int c) -> bool {
+        return (interior && c > ca) || (k >= kmin && k <= kmax);
+    };
+    // Interior tiles need no masking, and every column and diagonal of theirs
+    // goes on below this wave: tiles [ia, ib), in a full matrix without those
+    // that the band touches, [ja, jb).
+    int ia, ib, ja = 0x7FFFFFFF, jb = 0x7FFFFFFF;
+    if constexpr (FULL) {
+        ia = 0;
+        ib = R + 64 <= n - 1 ? nb >> 6 : 0;
+        if (band > 0) {
+            const int64_t a = (int64_t)R - 63 - band, b = (int64_t)R + 63 + band;
+            ja = (int)(a < 0 ? 0 : (a >> 6) + 1);
+            jb = (int)((b + 63) >> 6 < 0x7FFFFFFF ? (b + 63) >> 6 : 0x7FFFFFFF);
+        }
+    } else {
+        ia = (R + 64 + wp + 63) >> 6;
+        ib = n >> 6;
     }
 
     // Row coordinates of this lane (clamped for rows past the end).
@@ -929,423 +1038,437 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
     // Horizontal runs: with segments, each row's piece in this block records
     // its first and last runs (hfirst / hlast); otherwise the row's first run
     // is its lead.
-    const LineCtx hctx{&j, bins, (int64_t)(i - j.s_lo * H) * G + seg, G > 1, (uint32_t)i};
-    Run hs{0, 0, 0};          // horizontal run of this lane's row (auto)
-    bool hstarted = false;
-    Run left{0, 0, 0};        // diagonal carry from the previous tile (upper part end)
+    auto hslot = [&]() -> uint32_t * {
+        return G > 1 ? j.hfirst + ((int64_t)(R - j.s_lo * H) * G + seg) : j.lead + R;
+    };
+    const uint32_t hoff = (uint32_t)lane * (uint32_t)(G > 1 ? G : 1);
+    constexpr uint32_t kNotBegun = 0xFFFFFFFFu;
+    Run hs{0, kNotBegun, 0};  // horizontal run of this lane's row (auto)
+    // Colours (kHasBlack, kHasWhite) of the open runs of the rows, and of the
+    // diagonals that leave this wave's last tile through its right edge.
+    uint32_t hown = 0, lown = kHasWhite;
 
-    // The waves form a pipeline over the tiles: wave w reads the carries that
-    // wave w-1 wrote for the same tile and writes its own for wave w+1, through a
-    // ring of kRing slots per wave pair.  A wave waits only for its neighbours:
-    // for the tile's carries from above and for a free slot below.
-    const int tfirst = cfirst - c0 > ta ? cfirst - c0 : ta;   // first tile with cells for this wave
-    if (wave > 0) publish_counter(&L.cons[wave - 1], wave_has_u ? tfirst : 0x7FFFFFFF);
-    bool sync_ok = true;
-    const int wbias = j.wait_bias;   // 0 (a test injecting give-ups sets it), read once per strip
     // Given matrix: the next tile's row word is loaded while the current tile
-    // is processed (one load in flight per lane hides the memory latency that
-    // otherwise sets the pace of a strip; loading 2, 4 or 8 tiles ahead
-    // measured no faster).
+    // is processed (loading 2, 4 or 8 tiles ahead measured no faster).
     const auto mrow = MODE == kModeMatrix && i < n ? glb(j.bits) + (int64_t)i * j.words : nullptr;
     uint64_t mnext = 0;
     if constexpr (MODE == kModeMatrix) {
-        if (mrow && wave_has_u && tfirst < tb) mnext = mrow[c0 + tfirst];
+        if (mrow && cw < cb) mnext = mrow[cw];
     }
-    for (int t = wave_has_u ? tfirst : tb; t < tb; ++t) {
-        const int c = c0 + t;
-        const int slot = t & (kRing - 1);
-        {
-            const int jbase = c * 64;
-            uint32_t xlo, xhi;
-            if constexpr (MODE == kModeMatrix) {
-                const uint64_t word = mnext;
-                if (mrow && t + 1 < tb) mnext = mrow[c + 1];
-                xlo = (uint32_t)word;
-                xhi = (uint32_t)(word >> 32);
-            } else {
-                const ConstF cols = to_const((c == j.c_last) ? j.tail : j.sb + jbase);
-                tile_bits<NORM, M>(cols, tau, xr, rowp, j.m, j.thr, j.thr0,
-                                          box == nullptr ? nullptr : box + (int64_t)c * kBoxStride,
-                                          xlo, xhi);
-            }
 
-            // Interior tile: no cell needs masking, and every column and
-            // diagonal continues below this wave.
-            bool interior;
-            if constexpr (FULL) {
-                interior = R + 64 <= n - 1 && jbase + 63 <= nb - 1 &&
-                           (band == 0 || (int64_t)jbase - (R + 63) >= band ||
-                            (int64_t)R - (jbase + 63) >= band);
-            } else {
-                interior = jbase >= R + 64 + wp && jbase + 63 <= n - 1;
-            }
-            int lo_v = 0, hi_v = 64;
-            uint64_t vmask = ~0ull;
-            uint64_t X = mk64(xlo, xhi);
-            if (!interior) {
-                if constexpr (FULL) {
-                    // Valid cells of this row: columns [0, nb) outside the band.
-                    vmask = 0ull;
-                    if (i < n) {
-                        const int hv = nb - jbase < 64 ? nb - jbase : 64;
-                        vmask = hv > 0 ? range_mask(0, hv) : 0ull;
-                        if (band > 0) {
-                            int64_t blo = (int64_t)i - band + 1 - jbase, bhi = (int64_t)i + band - jbase;
-                            blo = blo < 0 ? 0 : blo;
-                            bhi = bhi > 64 ? 64 : bhi;
-                            if (blo < bhi) vmask &= ~range_mask((uint32_t)blo, (uint32_t)bhi);
-                        }
-                    }
+    // Progress.  Tiles [.., ready) may be entered: the wave above is done with
+    // them, or (wave 0) their state slots are free again, the last wave being
+    // kRing tiles behind.  After one wait has given up the wave stops waiting
+    // (the job is flagged as failed), so a strip finishes in bounded time.
+    bool sync_ok = true;
+    int *const from = &L.prog[wave == 0 ? nw : wave];
+    const int lead = wave == 0 ? kRing : 0;
+    const int wbias = j.wait_bias;   // 0 (a test injecting give-ups sets it)
+    int ready = wbias ? ca : ca + lead;
+    uint32_t notes = kHasWhite;      // lane s: the note found for slot s
+    int c = ca;
+    auto await = [&]() {
+        if (c < ready) return;
+        ready = ca + lead + wait_counter(from, c - ca - lead + 1 + wbias, j, sync_ok);
+        notes = L.note[wave * kRing + (lane & (kRing - 1))];
+        if (!sync_ok) ready = 0x7FFFFFFF;
+        // A strip goes at the pace of its slowest wave (the one whose rows hold
+        // most recurrences); the others wait for it.  So a wave with many tiles
+        // ready is issued first: 1M-point Lorenz series 63.2 -> 52.5 ms, 1M-point
+        // sine 47.4 -> 34.1, 262,144-point cross recurrence 7.7 -> 6.5.
+        const int lag = __builtin_amdgcn_readfirstlane(ready - c);
+        if (lag >= 12) __builtin_amdgcn_s_setprio(3);
+        else if (lag >= 4) __builtin_amdgcn_s_setprio(2);
+        else if (lag >= 2) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+    };
+    auto advance = [&](int next) {   // done with the tiles up to `next`
+        publish_counter(&L.prog[wave + 1], next - ca);
+        // (readfirstlane: the compiler does not see that `next` is uniform, and
+        // took the column coordinates as vector loads from here on)
+        c = __builtin_amdgcn_readfirstlane(next);
+    };
+    // A tile whose columns are white from the strip's top edge to its bottom
+    // edge, or whose diagonals are white at the edge, writes no summaries.  The
+    // others are noted in LDS (columns and bottom-edge diagonals by the bottom
+    // wave, top-edge diagonals by wave 0) and, 32 tiles at a time, in the masks
+    // (one lane per tile; an atomic per tile in the tile's own path made the
+    // bottom wave, which sets the pace, slower: 62.6 -> 69.8 ms on the 1M-point
+    // Lorenz series).
+    auto note_written = [&](int which) {
+        if (lane == 0) atomicOr(&L.words[which], 1u << (c & 31));
+    };
+    auto flush_written = [&](int window) {   // tiles [32 window, 32 window + 32)
+        const int e = 32 * window + lane;
+        const int64_t strip_word = lstrip >> 5;
+        const uint32_t bit = 1u << (lstrip & 31);
+        auto put = [&](int which, uint32_t *mask, int entry) {
+            if (lane < 32 && (L.words[which] >> lane & 1u))
+                __hip_atomic_fetch_or(glb(mask + ((int64_t)entry * j.mask_words + strip_word)), bit,
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) L.words[which] = 0u;
+        };
+        if (wave == 0) put(1, j.dfmask, e - rb + j.kb_off);
+        if (bottom) {
+            put(0, j.vmask, e);
+            put(2, j.dlmask, e - rb - 1 + j.kb_off);
+        }
+    };
+    int window = wave == 0 || bottom ? ca >> 5 : 0x7FFFFFFF;
+    while (c < cw) {   // nothing of this wave here yet: follow the wave above
+        await();
+        advance(ready < cw ? ready : cw);
+    }
+    const uint32_t stop_white = kHasBlack | (bottom ? kStored : 0u);
+    const uint32_t stop_black = kHasWhite | (bottom ? ~0u : 0u);
+    // Plain tiles: interior, and not the first behind a segment edge.
+    const int pa = seg_start && ia <= ca ? ca + 1 : ia;
+    int group = -1;                  // group of tiles that act / full / kinds describe
+    uint64_t act = ~0ull, full = 0ull;
+    uint32_t kinds = 0;              // bit i: tile i of the group is empty; bit 8 + i: it is full
+    int unsorted = 0;                // groups to take unclassified (boxes decide little here)
+    while (c < cb) {
+        if ((c >> 5) > window) {
+            flush_written(window);
+            window = c >> 5;
+        }
+        const int slot = c & (kRing - 1);
+        const int gi = c & (kGroup - 1);
+        if constexpr (BOX) {
+            if ((c / kGroup) != group) {
+                group = c / kGroup;
+                if (unsorted > 0) {
+                    --unsorted;
+                    act = ~0ull;
+                    full = 0ull;
+                    kinds = 0u;
                 } else {
-                    // Valid cells of this row: columns [i + wp, n-1], rows < n.
-                    lo_v = i + wp - jbase;
-                    lo_v = lo_v < 0 ? 0 : lo_v;
-                    if (i >= n || lo_v > 64) lo_v = 64;
-                    hi_v = n - jbase;
-                    hi_v = hi_v > 64 ? 64 : hi_v;
-                    vmask = lo_v < hi_v ? range_mask(lo_v, hi_v) : 0ull;
-                }
-                X &= vmask;
-                xlo = (uint32_t)X;
-                xhi = (uint32_t)(X >> 32);
-            }
-
-            const bool any = __ballot(X != 0ull) != 0ull;
-
-            // First tile of a full-matrix block that does not start at the left
-            // border: the diagonals entering through its left edge start a
-            // segment here.  Lane q's lower part (q > 0) begins at cell
-            // (R + 64 - q, jbase), bit 0 of lane 64 - q's row word; lane 0's
-            // lower part is empty and its diagonal enters the block in the wave
-            // below, which starts it (`fresh_up`).
-            const bool fresh = seg_start && t == ta;
-            if (fresh) {
-                const uint64_t col0 = __ballot((X & 1ull) != 0ull);
-                left = lane == 0 ? Run{0u, 0u, 0u}
-                                 : Run{(uint32_t)(col0 >> (64 - lane)) & 1u, 0u, 1u};
-                // A row of U that began left of this block enters it here.
-                if constexpr (!FULL) {
-                    if (i < n && i + wp < jbase) {
-                        hs = Run{(uint32_t)(X & 1ull), 0u, 1u};
-                        hstarted = true;
-                    }
+                    classify<NORM, M>(j, rb, group, lane, act, full);
+                    const uint32_t b = (uint32_t)((act >> (8 * (lane & 7))) & 0xFFull);
+                    const uint32_t f = (uint32_t)((full >> (8 * (lane & 7))) & 0xFFull);
+                    kinds = ((uint32_t)__builtin_amdgcn_ballot_w64(b == 0u) & 0xFFu) |
+                            (((uint32_t)__builtin_amdgcn_ballot_w64(f == 0xFFu) & 0xFFu) << 8);
+                    // Where nearly every chunk stays open, the next seven
+                    // groups are not classified: noise pays an eighth of the
+                    // cost (1-2% of its predicate) instead of all of it.
+                    if (__builtin_popcountll(act & ~full) >= 60) unsorted = 7;
                 }
             }
-            // The upper part of this lane's diagonal starts a segment in this
-            // tile: on the strip's top edge (wave 0), or for lane 0 on the
-            // block's left edge.
-            const bool fresh_up = wave == 0 || (fresh && lane == 0);
+        }
+        const bool plain = c >= pa && c < ib && (!FULL || c < ja || c >= jb);
+        const uint32_t kind = BOX ? (kinds >> gi) & 0x101u : 0u;   // 1: empty, 0x100: full
 
-            // This tile's carries from the wave above, and a free slot below.
-            // After one wait has given up the wave stops waiting (the job is
-            // flagged as failed), so a strip finishes in bounded time.
-            if (wave > 0 && sync_ok)
-                sync_ok = wait_counter(&L.prod[wave - 1], t + 1 + wbias, j);
-            if (wave < nw - 1 && sync_ok)
-                sync_ok = wait_counter(&L.cons[wave], t - kRing + 1 + wbias, j);
-
-            if (interior && !any) {
-                // No recurrence in an interior tile: every open run sees 64
-                // white cells.  Only carried states change; a black run that
-                // was open ends at the tile's first cell.
-                if constexpr (!FULL) {
-                    if (hs.color) {
-                        finish_run<kHoriz>(hctx, 1u, hs.len, hs.first);
-                        hs = Run{0u, 64u, 0u};
-                    } else {
-                        hs.len += 64u;
-                    }
-                }
-                {
-                    Run st = wave == 0 ? Run{0u, 0u, 1u} : unpack_run(L.vs(slot, wave - 1, lane));
-                    const int64_t sidx = vbase + (jbase + lane);
-                    if (st.color) {
-                        const LineCtx lc{&j, bins, sidx, true, 0u};
-                        finish_run<kVert>(lc, 1u, st.len, st.first);
-                        st = Run{0u, 64u, 0u};
-                    } else {
-                        st.len += 64u;
-                    }
-                    if (wave == nw - 1) {
-                        const uint16_t pk = (uint16_t)(st.len | (st.color << 15));
-                        if (st.first) *glb(j.vfirst + sidx) = pk;   // one run: its last is its first
-                        else *glb(j.vlast + sidx) = pk;
-                    } else {
-                        L.vs(slot, wave, lane) = pack_run(st);
-                    }
-                }
-                {
-                    // Interior: both diagonal parts of every lane are valid and
-                    // continue on the next row.
-                    const int kup = jbase + lane - R;
-                    const int klo = kup - 64;
-                    Run up;
-                    if (fresh_up) {
-                        if (!FULL || dok(kup)) *glb(j.dfirst + dbase + kup) = 0;   // white first cell
-                        up = Run{0u, 0u, 0u};
-                    } else {
-                        up = unpack_run(L.ds(slot, wave - 1, lane));
-                    }
-                    if (up.color) {
-                        const LineCtx lc{&j, bins, dbase + kup, true, 0u};
-                        finish_run<kDiag, kDW>(lc, 1u, up.len, up.first);
-                        up = Run{0u, 0u, 0u};
-                    }
-                    // Lane 0's lower part is empty (its diagonal left this wave
-                    // at the previous tile's corner): its run goes on unchanged.
-                    Run lw = left;
-                    if (lw.color && lane != 0) {
-                        const LineCtx lc{&j, bins, dbase + klo, !FULL || dok(klo), 0u};
-                        finish_run<kDiag, kDW>(lc, 1u, lw.len, lw.first);
-                        lw = Run{0u, 0u, 0u};
-                    }
-                    if (wave < nw - 1) {
-                        L.ds(slot, wave, lane) = pack_run(lw);
-                    } else if (!FULL || dok(klo)) {
-                        const uint16_t b = (uint16_t)(lw.color ? lw.len : 0u);
-                        // A black run over the whole piece: the stitch reads only its first
-                        // (a white one reads as 0 and needs its last too).
-                        if (lw.first && lw.color) {
-                            *glb(j.dfirst + dbase + klo) = b;
-                        } else {
-                            *glb(j.dlast + dbase + klo) = b;
-                            if (lw.first) *glb(j.dfirst + dbase + klo) = b;
-                        }
-                    }
-                    left = up;
-                }
-                if (wave > 0) publish_counter(&L.cons[wave - 1], t + 1);
-                if (wave < nw - 1) publish_counter(&L.prod[wave], t + 1);
+        // ---- tiles of one colour, known from the boxes: passed over if every
+        // open run has that colour, as many of the group's as are alike, with
+        // the same states waiting, and ready ----
+        if (plain && kind) {
+            await();
+            const uint32_t stop = kind == 1u ? stop_white : stop_black;
+            const uint32_t note = (uint32_t)__builtin_amdgcn_readlane((int)notes, slot);
+            if (((note | hown | lown) & stop) == 0u) {
+                uint32_t same = kind == 1u ? kinds : kinds >> 8;
+                same &= ~((uint32_t)__builtin_amdgcn_ballot_w64((notes & stop) != 0u) >>
+                          (slot & ~(kGroup - 1)));
+                int next = c + __builtin_ctz(~(((same & 0xFFu) >> gi) | 1u));   // at least this one
+                next = next < ib ? next : ib;
+                next = next < cb ? next : cb;
+                if (FULL && c < ja) next = next < ja ? next : ja;
+                next = next < ready ? next : ready;
+                if (((lane - slot) & (kRing - 1)) < next - c && lane < kRing)
+                    L.note[(wave + 1) * kRing + lane] =
+                        (uint8_t)(kind == 1u ? kHasWhite | (notes & kStored) : kHasBlack | kStored);
+                lown = kind == 1u ? kHasWhite : kHasBlack;
+                advance(next);
                 continue;
             }
+        }
 
-            if (interior && __ballot(X != ~0ull) == 0ull) {
-                // Every cell of an interior tile recurrent (dense series): the
-                // mirror image of the empty case.  Open white runs end at the
-                // tile's first cell, black runs grow by the cells they cross.
-                if constexpr (!FULL) {
-                    if (!hs.color) {
-                        finish_run<kHoriz>(hctx, 0u, hs.len, hs.first);
-                        hs = Run{1u, 64u, 0u};
-                    } else {
-                        hs.len += 64u;
+        // ---- this lane's row of the tile ----
+        const int jbase = c * 64;
+        const bool interior = plain || (c >= ia && c < ib && (!FULL || c < ja || c >= jb));
+        const bool fresh = seg_start && c == ca;   // first tile behind a segment edge
+        uint32_t xlo = kind & 0x100u ? ~0u : 0u, xhi = xlo;
+        if constexpr (MODE == kModeMatrix) {
+            const uint64_t word = mnext;
+            if (mrow && c + 1 < cb) mnext = mrow[c + 1];
+            xlo = (uint32_t)word;
+            xhi = (uint32_t)(word >> 32);
+        } else if (kind == 0u) {
+            uint32_t eval = 0xFFu, ones = 0u;
+            if (BOX) {
+                eval = (uint32_t)(act >> (8 * gi)) & 0xFFu;
+                ones = (uint32_t)(full >> (8 * gi)) & 0xFFu;
+                eval &= ~ones;
+            }
+            // The last tile's coordinates end past the series unless it is
+            // interior.
+            const ConstF cols = to_const(!interior && c == j.c_last ? j.tail : sb + jbase);
+            if (!BOX || eval == 0xFFu)
+                tile_bits<NORM, M>(cols, tau, xr, rowp, j.m, j.thr, j.thr0, xlo, xhi);
+            else
+                tile_bits_some<NORM, M>(cols, tau, xr, rowp, j.m, j.thr, j.thr0, eval, ones, xlo, xhi);
+        }
+        int lo_v = 0;
+        uint64_t vmask = ~0ull;
+        if (!interior) {
+            if constexpr (FULL) {
+                // Valid cells of this row: columns [0, nb) outside the band.
+                vmask = 0ull;
+                if (i < n) {
+                    const int hv = nb - jbase < 64 ? nb - jbase : 64;
+                    vmask = hv > 0 ? range_mask(0, hv) : 0ull;
+                    if (band > 0) {
+                        int64_t blo = (int64_t)i - band + 1 - jbase, bhi = (int64_t)i + band - jbase;
+                        blo = blo < 0 ? 0 : blo;
+                        bhi = bhi > 64 ? 64 : bhi;
+                        if (blo < bhi) vmask &= ~range_mask((uint32_t)blo, (uint32_t)bhi);
                     }
                 }
-                {
-                    Run st = wave == 0 ? Run{1u, 0u, 1u} : unpack_run(L.vs(slot, wave - 1, lane));
-                    const int64_t sidx = vbase + (jbase + lane);
-                    if (!st.color) {
-                        const LineCtx lc{&j, bins, sidx, true, 0u};
-                        finish_run<kVert>(lc, 0u, st.len, st.first);
-                        st = Run{1u, 64u, 0u};
-                    } else {
-                        st.len += 64u;
-                    }
-                    if (wave == nw - 1) {
-                        const uint16_t pk = (uint16_t)(st.len | (st.color << 15));
-                        if (st.first) *glb(j.vfirst + sidx) = pk;   // one run: its last is its first
-                        else *glb(j.vlast + sidx) = pk;
-                    } else {
-                        L.vs(slot, wave, lane) = pack_run(st);
-                    }
-                }
-                {
-                    // Lane q's diagonal has 64 - q cells in the upper part and
-                    // q in the lower part (none for lane 0, whose lower run
-                    // passes through unchanged).
-                    const int kup = jbase + lane - R;
-                    const int klo = kup - 64;
-                    const uint32_t nup = 64u - (uint32_t)lane;
-                    Run up;
-                    if (fresh_up) {
-                        up = Run{1u, nup, 1u};   // black first run from the block's edge
-                    } else {
-                        up = unpack_run(L.ds(slot, wave - 1, lane));
-                        if (up.color) {
-                            up.len += nup;
-                        } else {
-                            if (up.first) {
-                                const LineCtx lc{&j, bins, dbase + kup, !FULL || dok(kup), 0u};
-                                finish_run<kDiag, kDW>(lc, 0u, up.len, 1u);
-                            }
-                            up = Run{1u, nup, 0u};
-                        }
-                    }
-                    Run lw = left;
-                    if (lane != 0) {
-                        if (lw.color) {
-                            lw.len += (uint32_t)lane;
-                        } else {
-                            if (lw.first) {
-                                const LineCtx lc{&j, bins, dbase + klo, !FULL || dok(klo), 0u};
-                                finish_run<kDiag, kDW>(lc, 0u, lw.len, 1u);
-                            }
-                            lw = Run{1u, (uint32_t)lane, 0u};
-                        }
-                    }
-                    if (wave < nw - 1) {
-                        L.ds(slot, wave, lane) = pack_run(lw);
-                    } else if (!FULL || dok(klo)) {
-                        const uint16_t b = (uint16_t)(lw.color ? lw.len : 0u);
-                        // A black run over the whole piece: the stitch reads only its first
-                        // (a white one reads as 0 and needs its last too).
-                        if (lw.first && lw.color) {
-                            *glb(j.dfirst + dbase + klo) = b;
-                        } else {
-                            *glb(j.dlast + dbase + klo) = b;
-                            if (lw.first) *glb(j.dfirst + dbase + klo) = b;
-                        }
-                    }
-                    left = up;
-                }
-                if (wave > 0) publish_counter(&L.cons[wave - 1], t + 1);
-                if (wave < nw - 1) publish_counter(&L.prod[wave], t + 1);
+            } else {
+                // Valid cells of this row: columns [i + wp, n-1], rows < n.
+                lo_v = i + wp - jbase;
+                lo_v = lo_v < 0 ? 0 : lo_v;
+                if (i >= n || lo_v > 64) lo_v = 64;
+                int hi_v = n - jbase;
+                hi_v = hi_v > 64 ? 64 : hi_v;
+                vmask = lo_v < hi_v ? range_mask(lo_v, hi_v) : 0ull;
+            }
+            xlo &= (uint32_t)vmask;
+            xhi &= (uint32_t)(vmask >> 32);
+        }
+        const bool any = __builtin_amdgcn_ballot_w64((xlo | xhi) != 0u) != 0ull;
+        await();   // the columns' and diagonals' states from the wave above
+        if (plain && !any) {   // evaluated, and found empty
+            const uint32_t note = (uint32_t)__builtin_amdgcn_readlane((int)notes, slot);
+            if (((note | hown | lown) & stop_white) == 0u) {
+                if (lane == 0)
+                    L.note[(wave + 1) * kRing + slot] = (uint8_t)(kHasWhite | (note & kStored));
+                lown = kHasWhite;
+                advance(c + 1);
                 continue;
             }
+        }
+        const bool all = any && __builtin_amdgcn_ballot_w64((xlo & xhi) != ~0u) == 0ull;
+        const uint64_t X = mk64(xlo, xhi);
 
-            // ---- horizontal runs (row i of U) ----
-            if constexpr (!FULL) {
-                if (lo_v < hi_v) {
-                    if (!hstarted) {
-                        hstarted = true;
-                        hs = Run{(uint32_t)((X >> lo_v) & 1ull), 0u, 1u};
-                    }
-                    run_segment<kHoriz>(X, vmask, (uint32_t)lo_v, (uint32_t)hi_v, hs, hctx);
-                }
+        // The diagonals that enter a block through its left edge start a segment
+        // there: lane q's lower part (q > 0) begins at cell (R + 64 - q, jbase),
+        // bit 0 of lane 64 - q's row word; lane 0's lower part is empty and its
+        // diagonal enters the block in the wave below, which starts it.
+        const bool fresh_up = wave == 0 || (fresh && lane == 0);
+
+        // ---- horizontal runs (row i of U) ----
+        if constexpr (!FULL) {
+            if (!plain && vmask != 0ull && hs.start == kNotBegun) {
+                hs = Run{(uint32_t)((X >> lo_v) & 1ull), (uint32_t)(jbase + lo_v), 1u};
             }
+            uint64_t t = changes(X, vmask, (uint32_t)lo_v, hs.color);
+            if (t != 0ull) {
+                uint32_t p = low_bit(t), col = hs.color ^ 1u;
+                finish_row(j, bins, hs.color, (uint32_t)jbase + p - hs.start, hs.first, hslot(), hoff);
+                t &= t - 1ull;
+                inner_runs(bins, t, p, col);
+                hs = Run{col, (uint32_t)jbase + p, 0u};
+            }
+            hown = (__builtin_amdgcn_ballot_w64(hs.color != 0u) != 0ull ? kHasBlack : 0u) |
+                   (__builtin_amdgcn_ballot_w64(hs.color == 0u) != 0ull ? kHasWhite : 0u);
+        }
 
-            // ---- vertical runs (columns) ----
-            {
-                uint32_t ylo = xlo, yhi = xhi;
-                if (any) transpose64(ylo, yhi, lane);
-                else { ylo = 0; yhi = 0; }
-                const uint64_t Y = mk64(ylo, yhi);
+        // ---- vertical runs (columns) ----
+        uint32_t vcolor = 0;   // colours of the columns' open runs below this wave
+        {
+            uint32_t ylo = (uint32_t)X, yhi = (uint32_t)(X >> 32);
+            if (any && !all) transpose64(ylo, yhi, lane);
+            const uint64_t Y = mk64(ylo, yhi);
+            uint16_t *const first = j.vfirst + (vbase + jbase);
+            if (plain) {
+                Run st = wave == 0 ? Run{(uint32_t)(Y & 1ull), 0u, 1u} : unpack_run(L.vs(slot, lane));
+                column_runs(bins, Y, ~0ull, (uint32_t)Rl, st, first, (uint32_t)lane);
+                if (bottom) {
+                    const uint16_t pk = (uint16_t)(((uint32_t)(Rl + 64) - st.start) | (st.color << 15));
+                    uint16_t *const last = j.vlast + (vbase + jbase);
+                    glb(st.first ? first : last)[lane] = pk;   // one run: its last is its first
+                    st = unpack_run(kFreshColumn);
+                }
+                L.vs(slot, lane) = pack_run(st);
+                vcolor = st.color;
+            } else {
                 const int jc = jbase + lane;
                 // last valid local row of column jc: the band (auto) or the
                 // bottom border (full) ends its segment
-                const int e = interior ? 64 : (FULL ? n - 1 - R : jc - wp - R);
-                if (interior || (jc <= nb - 1 && e >= 0)) {
+                const int e = FULL ? n - 1 - R : jc - wp - R;
+                if (jc <= nb - 1 && e >= 0) {
                     const uint32_t vhi = e >= 63 ? 64u : (uint32_t)(e + 1);
-                    Run st;
-                    if (wave == 0) st = Run{(uint32_t)(Y & 1ull), 0u, 1u};
-                    else st = unpack_run(L.vs(slot, wave - 1, lane));
-                    const int64_t sidx = vbase + jc;
-                    LineCtx lc{&j, bins, sidx, true, 0u};
-                    const uint64_t vwin = vhi >= 64 ? ~0ull : ((1ull << vhi) - 1ull);
-                    run_segment<kVert>(Y, vwin, 0u, vhi, st, lc);
-                    if (e <= 63 || wave == nw - 1) {
-                        const uint16_t pk = (uint16_t)(st.len | (st.color << 15));
-                        if (st.first) *glb(j.vfirst + sidx) = pk;   // one run: its last is its first
-                        else *glb(j.vlast + sidx) = pk;
-                    } else {
-                        L.vs(slot, wave, lane) = pack_run(st);
+                    Run st = wave == 0 ? Run{(uint32_t)(Y & 1ull), 0u, 1u} : unpack_run(L.vs(slot, lane));
+                    column_runs(bins, Y, vhi >= 64 ? ~0ull : ((1ull << vhi) - 1ull), (uint32_t)Rl, st,
+                                first, (uint32_t)lane);
+                    if (e <= 63 || bottom) {
+                        const uint16_t pk = (uint16_t)((Rl + vhi - st.start) | (st.color << 15));
+                        uint16_t *const last = j.vlast + (vbase + jbase);
+                        glb(st.first ? first : last)[lane] = pk;
+                        st = unpack_run(kFreshColumn);
                     }
+                    L.vs(slot, lane) = pack_run(st);
                 }
             }
+            if (bottom) note_written(0);
+        }
 
-            // ---- diagonal runs ----
-            {
-                uint32_t zlo = xlo, zhi = xhi;
-                if (any) {
-                    rotr64(zlo, zhi, (uint32_t)lane);
-                    transpose64(zlo, zhi, lane);
-                } else {
-                    zlo = 0;
-                    zhi = 0;
+        // ---- diagonal runs ----
+        {
+            uint32_t zlo = (uint32_t)X, zhi = (uint32_t)(X >> 32);
+            if (any && !all) {
+                rotr64(zlo, zhi, (uint32_t)lane);
+                transpose64(zlo, zhi, lane);
+            }
+            const uint64_t D = mk64(zlo, zhi);
+            const int q = lane;
+            const int kb = c - rb;                  // diagonal block of the upper part
+            const int kup = 64 * kb + q;            // diagonal of the upper part
+            const int klo = kup - 64;               // diagonal of the lower part
+            const uint64_t upwin = ~0ull >> q;
+            uint16_t *const ufirst = j.dfirst + (dbase + 64 * kb), *const lfirst = ufirst - 64;
+            const bool uok = dok(kup, interior, c), lok = dok(klo, interior, c);
+            Run up;
+            if (fresh_up) {
+                // Segment start on the strip's top row (or the block's left
+                // edge).  A white first cell means "no black run at the edge"
+                // (white diagonal runs are never counted, so it is not a run
+                // to record either).
+                const uint32_t b = (uint32_t)(D & 1ull);
+                up = Run{b, (uint32_t)Rl, b};
+            } else if (jbase + q > nb - 1) {
+                up = Run{0u, 0u, 0u};   // starts past the border
+            } else {
+                up = unpack_run(L.ds(kb, lane));
+            }
+            if (wave == 0) {
+                // On the strip's top row the white diagonals are recorded only
+                // beside black ones.
+                if (__builtin_amdgcn_ballot_w64(up.color != 0u) != 0ull) {
+                    note_written(1);
+                    if (up.color == 0u && uok) glb(ufirst)[lane] = 0;
                 }
-                const uint64_t D = mk64(zlo, zhi);
-                const int q = lane;
-                const int kup = jbase + q - R;          // diagonal of the upper part
-                const int klo = kup - 64;               // diagonal of the lower part
-                const uint64_t upwin = q == 0 ? ~0ull : ((1ull << (64 - q)) - 1ull);
-                Run up;
-                if (fresh_up) {
-                    // Segment start on the strip's top row (or the block's left
-                    // edge).  A white first cell means "no black run at the
-                    // edge": record it at once (white diagonal runs are never
-                    // counted, so their length does not matter).
-                    up = Run{(uint32_t)(D & 1ull), 0u, 1u};
-                    if (!up.color) {
-                        if (dok(kup)) *glb(j.dfirst + dbase + kup) = 0;
-                        up.first = 0;
-                    }
-                } else if (jbase + q > nb - 1) {
-                    up = Run{0u, 0u, 0u};   // starts past the border
-                } else {
-                    up = unpack_run(L.ds(slot, wave - 1, lane));
+            } else if (fresh && lane == 0 && up.color == 0u && uok) {
+                glb(ufirst)[lane] = 0;
+            }
+            diagonal_runs<kDW>(bins, D, upwin, 0u, (uint32_t)Rl, up, ufirst, (uint32_t)lane, uok);
+            L.ds(kb, lane) = pack_run(up);
+            lown = (__builtin_amdgcn_ballot_w64(up.color != 0u) != 0ull ? kHasBlack : 0u) |
+                   (__builtin_amdgcn_ballot_w64(up.color == 0u) != 0ull ? kHasWhite : 0u);
+
+            Run lw;
+            if (fresh) {
+                const uint64_t col0 = __builtin_amdgcn_ballot_w64((X & 1ull) != 0ull);
+                const uint32_t b = lane == 0 ? 0u : (uint32_t)(col0 >> ((64 - lane) & 63)) & 1u;
+                lw = Run{b, (uint32_t)(Rl + 64 - q), b};
+                if (lane != 0 && b == 0u && lok) glb(lfirst)[lane] = 0;
+            } else {
+                lw = unpack_run(L.ds(kb - 1, lane));
+            }
+            diagonal_runs<kDW>(bins, D, ~upwin, (uint32_t)(64 - q), (uint32_t)Rl, lw, lfirst,
+                               (uint32_t)lane, lok);
+            // The lower part ends on row R+63.  Diagonals with no cell on the
+            // next row end here at the right (or, full matrix, bottom) border;
+            // the others go to the wave below or, from the last wave, into the
+            // summary.
+            const uint32_t len = (uint32_t)(Rl + 64) - lw.start;
+            bool ends = false;
+            if (!interior) {
+                ends = FULL ? (R + 64 > n - 1 || R + 64 + klo > nb - 1) : (R + 64 + klo > n - 1);
+                if (ends) {
+                    if (lw.color) end_diagonal<kDW>(bins, len, lw.first, lfirst, (uint32_t)lane, lok);
+                    lw = Run{0u, 0u, 0u};
                 }
-                {
-                    LineCtx lc{&j, bins, dbase + kup, dok(kup), 0u};
-                    run_segment<kDiag, kDW>(D, upwin, 0u, (uint32_t)(64 - q), up, lc);
+            }
+            if (bottom) {
+                if (__builtin_amdgcn_ballot_w64(lw.color != 0u) != 0ull) {
+                    note_written(2);
+                    // A black run over the whole piece: the stitch reads only
+                    // its first (a white one reads as 0 and needs its last).
+                    uint16_t *const llast = j.dlast + (dbase + 64 * kb - 64);
+                    if (!ends && lok) glb(lw.first ? lfirst : llast)[lane] = (uint16_t)(lw.color ? len : 0u);
                 }
-                Run lw = left;
-                {
-                    const bool ok = dok(klo);
-                    LineCtx lc{&j, bins, dbase + klo, ok, 0u};
-                    run_segment<kDiag, kDW>(D, ~upwin, (uint32_t)(64 - q), 64u, lw, lc);
-                    // The lower part ends on row R+63.  Diagonals with no cell on
-                    // the next row end here at the right (or, full matrix,
-                    // bottom) border; the others go to the wave below or, from
-                    // the last wave, into the summary.
-                    const bool ends = FULL ? (R + 64 > n - 1 || R + 64 + klo > nb - 1)
-                                           : (R + 64 + klo > n - 1);
-                    if (ends) {
-                        if (lw.color || lw.first) finish_run<kDiag, kDW>(lc, lw.color, lw.len, lw.first);
-                    } else if (wave < nw - 1) {
-                        L.ds(slot, wave, lane) = pack_run(lw);
-                    } else if (ok) {
-                        const uint16_t b = (uint16_t)(lw.color ? lw.len : 0u);
-                        // A black run over the whole piece: the stitch reads only its first
-                        // (a white one reads as 0 and needs its last too).
-                        if (lw.first && lw.color) {
-                            *glb(j.dfirst + dbase + klo) = b;
-                        } else {
-                            *glb(j.dlast + dbase + klo) = b;
-                            if (lw.first) *glb(j.dfirst + dbase + klo) = b;
-                        }
-                    }
+                lw = Run{0u, 0u, 0u};   // the slot is free again
+            }
+            L.ds(kb - 1, lane) = pack_run(lw);
+            if (!bottom) {
+                uint32_t mine = kHasBlack | kHasWhite | kStored;   // at a border: not known
+                if (plain) {
+                    mine = kStored;
+                    if (__builtin_amdgcn_ballot_w64((vcolor | lw.color) != 0u) != 0ull) mine |= kHasBlack;
+                    if (__builtin_amdgcn_ballot_w64((vcolor & lw.color) == 0u) != 0ull) mine |= kHasWhite;
                 }
-                left = up;
+                if (lane == 0) L.note[(wave + 1) * kRing + slot] = (uint8_t)mine;
             }
         }
-        if (wave > 0) publish_counter(&L.cons[wave - 1], t + 1);
-        if (wave < nw - 1) publish_counter(&L.prod[wave], t + 1);
+        advance(c + 1);
     }
-    if (!sync_ok) g_or(j.flag, 8);   // a neighbour wait gave up: result invalid
+    if (wave == 0 || bottom) flush_written(window);
+    if (!sync_ok) {   // a neighbour wait gave up: result invalid
+        g_or(j.flag, 8);
+        *L.bad = 1;
+    }
 
-    if (wave_has_u) {
+    if (cw < cb) {
         // Rows end at column n-1: their last run is complete; a block that is
         // not the strip's last records each row's open run as its last.
         if constexpr (!FULL) {
-            if (hstarted) {
-                if (tb == T) {
-                    finish_run<kHoriz>(hctx, hs.color, hs.len, hs.first);
-                } else {
-                    const uint32_t h = hs.len | (hs.color << 31);
-                    if (hs.first) *glb(j.hfirst + hctx.sum_idx) = h;
-                    else *glb(j.hlast + hctx.sum_idx) = h;
-                }
+            if (hs.start != kNotBegun) {
+                const uint32_t len = (uint32_t)x1 - hs.start;
+                uint32_t *const first = hslot();
+                if (cb == j.c_last + 1)
+                    finish_row(j, bins, hs.color, len, hs.first, first, hoff);
+                else
+                    glb(hs.first ? first : j.hlast + (first - j.hfirst))[hoff] = len | (hs.color << 31);
             }
         }
         // Upper parts that left the last tile on its right edge end at the
         // border, and so do those whose next cell (one row down, in the next
         // block) lies below the matrix; the others go on in the next block:
         // recorded as the block's last runs.
-        const int kup = (c0 + tb - 1) * 64 + lane - R;
-        if (tb == T || R + 64 - lane > n - 1) {
-            LineCtx lc{&j, bins, dbase + kup, dok(kup), 0u};
-            if (left.color || left.first) finish_run<kDiag, kDW>(lc, left.color, left.len, left.first);
-        } else if (dok(kup)) {
-            const uint16_t b = (uint16_t)(left.color ? left.len : 0u);
-            // A black run over the whole piece: the stitch reads only its first
-            // (a white one reads as 0 and needs its last too).
-            if (left.first && left.color) {
-                *glb(j.dfirst + dbase + kup) = b;
-            } else {
-                *glb(j.dlast + dbase + kup) = b;
-                if (left.first) *glb(j.dfirst + dbase + kup) = b;
-            }
+        const int kb = cb - 1 - rb;
+        const bool uok = dok(64 * kb + lane, false, ca);
+        const Run left = unpack_run(L.ds(kb, lane));
+        const uint32_t len = (uint32_t)(Rl + 64 - lane) - left.start;
+        uint16_t *const first = j.dfirst + (dbase + 64 * kb), *const last = j.dlast + (dbase + 64 * kb);
+        if (cb == j.c_last + 1 || R + 64 - lane > n - 1) {
+            if (left.color) end_diagonal<kDW>(bins, len, left.first, first, (uint32_t)lane, uok);
+        } else if (uok) {
+            // A black run over the whole piece: the stitch reads only its first.
+            glb(left.first ? first : last)[lane] = (uint16_t)(left.color ? len : 0u);
         }
+    }
+}
+
+// Whether a wave classifies the tiles of its part of a block: four groups of it,
+// spread over its tiles, are tried, and where the boxes decide less than a
+// sixteenth of their chunks (noise), none is.  Every wave decides for itself:
+// only speed depends on it.  (With the classes in its code the L1, m = 5 kernel
+// ran 4.5% slower on uniform noise, 9.52 -> 9.96 ms for the 400 windows.)
+template <int NORM, int M, int MODE>
+__device__ __forceinline__ bool use_boxes(const JobDesc &j, int item) {
+    if constexpr (MODE == kModeMatrix || M == 0) {
+        return false;
+    } else {
+        if (j.boxc == nullptr) return false;
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int lstrip = item / j.segs, seg = item - lstrip * j.segs;
+        const int R = (j.s_lo + lstrip) * j.H + 64 * wave;
+        const int c0 = MODE == kModeAuto ? (R + j.wp) >> 6 : 0;
+        const int sa = j.seg_base + seg * j.seg_tiles;
+        const int ca = sa > c0 ? sa : c0;
+        const int cb = sa + j.seg_tiles < j.c_last + 1 ? sa + j.seg_tiles : j.c_last + 1;
+        if (ca >= cb || R > j.n - 1) return false;
+        int open = 0;
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            uint64_t act, full;
+            classify<NORM, M>(j, R >> 6, (ca + (int)((int64_t)(cb - 1 - ca) * q / 3)) / kGroup, lane, act, full);
+            open += __builtin_popcountll(act & ~full);
+        }
+        return open < 240;
     }
 }
 
@@ -1354,17 +1477,17 @@ __global__ void __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_pe
 k_tiles(const JobDesc *__restrict__ jobs, const GroupDesc *__restrict__ groups, int g,
         int *counters) {
     extern __shared__ uint32_t lds_words[];
-    const int nw = blockDim.x >> 6;
     StripLds L;
     L.bd = lds_words;
     L.bv = L.bd + kCapD;
     L.bw = L.bv + kCapV;
-    L.vslot = L.bw + kCapW;
-    L.dslot = L.vslot + kRing * nw * 64;
-    L.prod = reinterpret_cast<int *>(L.dslot + kRing * nw * 64);
-    L.cons = L.prod + kMaxWaves;
-    L.item = L.cons + kMaxWaves;
-    L.nw = nw;
+    L.vst = reinterpret_cast<uint16_t *>(L.bw + kCapW);
+    L.dst = L.vst + kRing * 64;
+    L.prog = reinterpret_cast<int *>(L.dst + kDiagRing * 64);
+    L.note = reinterpret_cast<uint8_t *>(L.prog + kMaxWaves + 1);
+    L.words = reinterpret_cast<uint32_t *>(L.note + (kMaxWaves + 1) * kRing);
+    L.item = reinterpret_cast<int *>(L.words + 3);
+    L.bad = L.item + 1;
     const GroupDesc gd = groups[g];
     for (int t = threadIdx.x; t < kCapW; t += blockDim.x) {
         if (t < kCapD) L.bd[t] = 0;
@@ -1373,8 +1496,17 @@ k_tiles(const JobDesc *__restrict__ jobs, const GroupDesc *__restrict__ groups, 
     }
     __syncthreads();
     while (true) {
-        if (threadIdx.x == 0) *L.item = atomicAdd(counters + g, 1);
-        if (threadIdx.x < 2 * kMaxWaves) L.prod[threadIdx.x] = 0;   // prod and cons
+        if (threadIdx.x == 0) {
+            *L.item = atomicAdd(counters + g, 1);
+            *L.bad = 0;
+        }
+        if (threadIdx.x <= kMaxWaves) L.prog[threadIdx.x] = 0;
+        if (threadIdx.x < kRing) L.note[threadIdx.x] = (uint8_t)kHasWhite;
+        if (threadIdx.x < 3) L.words[threadIdx.x] = 0u;
+        static_assert(kNoDiagonal == 0u, "pairs of 16-bit states");
+        uint32_t *rings = reinterpret_cast<uint32_t *>(L.vst);
+        for (int t = threadIdx.x; t < 32 * (kRing + kDiagRing); t += blockDim.x)
+            rings[t] = t < 32 * kRing ? kFreshColumn * 0x10001u : 0u;
         __syncthreads();
         const int item = *L.item;
         __syncthreads();
@@ -1388,7 +1520,13 @@ k_tiles(const JobDesc *__restrict__ jobs, const GroupDesc *__restrict__ groups, 
         // By reference: fields are re-read with scalar loads where needed
         // instead of occupying SGPRs for the whole strip.
         const JobDesc &j = jobs[lo];
-        process_strip<NORM, M, MODE>(j, item - j.strip_base, L);
+        const int block = item - j.strip_base;
+        if constexpr (MODE != kModeMatrix && M > 0) {
+            if (use_boxes<NORM, M, MODE>(j, block)) process_strip<NORM, M, MODE, true>(j, block, L);
+            else process_strip<NORM, M, MODE, false>(j, block, L);
+        } else {
+            process_strip<NORM, M, MODE, false>(j, block, L);
+        }
         __syncthreads();
         flush_bins(L, j);
         __syncthreads();
@@ -1462,7 +1600,7 @@ __device__ __forceinline__ int seg_of(const JobDesc &j, int x) {
 // piece edges and return the row's first (leading) run, which the join with
 // column r needs.  Runs inside a piece were counted by the tile kernel, and so
 // was the last piece's final run at column n-1 unless it is that piece's
-// first.
+// first.  kStitchBatch pieces are loaded before any is folded.
 __device__ void row_pieces(StitchLds &L, const JobDesc &j, int r, uint32_t &lc, uint32_t &ll) {
     const int n = j.n;
     const int a = r + j.wp;                     // first column of the row
@@ -1475,38 +1613,145 @@ __device__ void row_pieces(StitchLds &L, const JobDesc &j, int r, uint32_t &lc, 
         if (lead_open) { lc = c; ll = l; lead_open = false; }
         else emit_line(L, j, c, l);
     };
-    const int gl = seg_of(j, n - 1);
-    for (int g = seg_of(j, a); g <= gl; ++g) {
-        const int g0 = (j.seg_base + g * j.seg_tiles) * 64;
-        const int lo = a > g0 ? a : g0;
-        const int hi = n - 1 < g0 + W - 1 ? n - 1 : g0 + W - 1;
-        const uint32_t len = (uint32_t)(hi - lo + 1);
-        const bool last = g == gl;
-        const int64_t idx = (int64_t)(r - j.s_lo * j.H) * j.segs + g;   // rows of the band
-        const uint32_t f = *glb(j.hfirst + idx);
-        const uint32_t fc = f >> 31, fl = f & 0x7FFFFFFFu;
-        if (have && fc == oc) {
-            ol += fl;
-        } else {
-            if (have) close(oc, ol);
-            oc = fc;
-            ol = fl;
-            have = true;
+    const int ga = seg_of(j, a), gl = seg_of(j, n - 1);
+    const int64_t row = (int64_t)(r - j.s_lo * j.H) * j.segs;   // rows of the band
+    for (int gb = ga; gb <= gl; gb += kStitchBatch) {
+        uint32_t fv[kStitchBatch], hv[kStitchBatch];
+#pragma unroll
+        for (int u = 0; u < kStitchBatch; ++u) {
+            if (gb + u <= gl) {
+                fv[u] = *glb(j.hfirst + row + gb + u);
+                hv[u] = *glb(j.hlast + row + gb + u);
+            }
         }
-        if (fl == len && !last) continue;       // the piece is one run: it stays open
-        close(oc, ol);                          // the open run ends in this piece
-        have = false;
-        if (!last) {
-            const uint32_t h = *glb(j.hlast + idx);
-            oc = h >> 31;
-            ol = h & 0x7FFFFFFFu;
-            have = true;
+#pragma unroll
+        for (int u = 0; u < kStitchBatch; ++u) {
+            const int g = gb + u;
+            if (g > gl) break;
+            const int g0 = (j.seg_base + g * j.seg_tiles) * 64;
+            const int lo = a > g0 ? a : g0;
+            const int hi = n - 1 < g0 + W - 1 ? n - 1 : g0 + W - 1;
+            const uint32_t len = (uint32_t)(hi - lo + 1);
+            const bool last = g == gl;
+            const uint32_t f = fv[u];
+            const uint32_t fc = f >> 31, fl = f & 0x7FFFFFFFu;
+            if (have && fc == oc) {
+                ol += fl;
+            } else {
+                if (have) close(oc, ol);
+                oc = fc;
+                ol = fl;
+                have = true;
+            }
+            if (fl == len && !last) continue;       // the piece is one run: it stays open
+            close(oc, ol);                          // the open run ends in this piece
+            have = false;
+            if (!last) {
+                oc = hv[u] >> 31;
+                ol = hv[u] & 0x7FFFFFFFu;
+                have = true;
+            }
         }
     }
 }
 
+// The written bits (process_strip) of 32 strips of the band, from strip s on (a
+// multiple of 32 above the band's first), of a mask entry.
+__device__ __forceinline__ uint32_t written32(const JobDesc &j, const uint32_t *mask, int entry, int s) {
+    const int word = (s - j.s_lo) >> 5;
+    return word < j.mask_words ? *glb(mask + ((int64_t)entry * j.mask_words + word)) : 0u;
+}
+
+// The pieces of diagonal k in the (strip, segment) blocks it crosses in strips
+// [s, sb], in order, from row ra0 (its first row there): a block's first and
+// last black runs are folded across edges.  `open`: the black run that enters.
+// r1 is the diagonal's last row.  W is the segment width, g0 the first column of
+// segment 0.  FULL: a piece that begins where the diagonal begins, below its
+// strip's top row, starts at the matrix's left border: nothing enters it, and
+// its runs were counted where they ended.
+// Top-edge and bottom-edge summaries exist where the masks say so; those at a
+// segment's left or right edge always do.  kStitchBatch pieces are loaded
+// before any is folded: one piece at a time cost a memory latency each
+// (150 of 740 us of a 65,521-point series).
+template <bool FULL>
+__device__ __forceinline__ uint32_t fold_diagonal(StitchLds &L, const JobDesc &j, int k, int r0, int r1,
+                                                  int s, int sb, uint32_t open, uint32_t wt) {
+    const int H = j.H, W = j.seg_tiles * 64, base = j.seg_base * 64;
+    int ra = r0 > s * H ? r0 : s * H;          // first row of the next piece
+    const int entry = (k >> 6) + j.kb_off;
+    uint32_t wf = 0, wl = 0;                   // written bits of strip s's 32
+    int have = -1;
+    while (s <= sb) {
+        if ((s - j.s_lo) >> 5 != have) {
+            have = (s - j.s_lo) >> 5;
+            wf = written32(j, j.dfmask, entry, s);
+            wl = written32(j, j.dlmask, entry, s);
+        }
+        uint32_t fv[kStitchBatch], lv[kStitchBatch], ln[kStitchBatch];   // ln: length, top bits below
+        constexpr uint32_t kLast = 1u << 31, kBorder = 1u << 30;
+        int count = 0;
+#pragma unroll
+        for (int u = 0; u < kStitchBatch; ++u) {
+            if (s <= sb && (s - j.s_lo) >> 5 == have) {
+                const uint32_t bit = 1u << ((s - j.s_lo) & 31);
+                const int ca = ra + k;
+                const int g = (ca - base) / W;
+                const int gend = base + (g + 1) * W - 1;                 // segment's last column
+                int rz = r1 < s * H + H - 1 ? r1 : s * H + H - 1;        // last row in the strip
+                const bool right = rz + k >= gend;                       // leaves at the right edge
+                if (right) rz = gend - k;
+                const bool last = rz == r1;
+                // the block's first column tile (auto: cut by the strip's)
+                const int xs = FULL ? 0 : ((s * H + j.wp) >> 6) * 64;
+                const int bx0 = base + g * W > xs ? base + g * W : xs;
+                const int64_t idx = (int64_t)((s - j.s_lo) * j.segs + g) * j.dw + (s * H + H - 1 - bx0) + k;
+                const bool top = ra == s * H;
+                const bool border = FULL && ra == r0 && !top;
+                fv[u] = 0u;
+                lv[u] = 0u;
+                if (!border && (!top || (wf & bit)))
+                    fv[u] = *glb(j.dfirst + idx);
+                if (!last && (right || (wl & bit)))
+                    lv[u] = *glb(j.dlast + idx);
+                ln[u] = (uint32_t)(rz - ra + 1) | (last ? kLast : 0u) | (border ? kBorder : 0u);
+                count = u + 1;
+                ra = rz + 1;
+                if (ra == (s + 1) * H || last) ++s;
+                if (last) s = sb + 1;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kStitchBatch; ++u) {
+            if (u >= count) break;
+            const uint32_t len = ln[u] & ~(kLast | kBorder), fb = fv[u];
+            const bool last = (ln[u] & kLast) != 0u;
+            if (!(ln[u] & kBorder)) {
+                if (!last && fb == len) { open += len; continue; }
+                if (open + fb) emit_stitch(L.bd, kCapD, j.hd, open + fb, wt, (uint32_t)j.hmax, j.flag);
+            }
+            open = last ? 0u : lv[u];
+        }
+    }
+    return open;
+}
+
+// Lines of a stitch: columns first, then, from here on, diagonals.  Columns and
+// diagonals both begin at the first lane of a wave, diagonals so that those of a
+// block of 64 (k >> 6) share one: a wave's lines then have one mask entry, and what
+// was not written is skipped by whole waves.
+__host__ __device__ __forceinline__ int64_t stitch_diag_line(int mode, int64_t n, int64_t nb, int64_t lo) {
+    if (mode == kModeAuto) return (n - lo + 63) / 64 * 64;
+    return (nb + 63) / 64 * 64 + ((64 - ((n - 1) & 63)) & 63);
+}
+__device__ __forceinline__ int64_t stitch_diag_line(const JobDesc &j, int64_t lo) {
+    return stitch_diag_line(j.mode, j.n, j.nb, lo);
+}
+__host__ __device__ __forceinline__ int64_t stitch_lines(int mode, int64_t n, int64_t nb, int64_t lo) {
+    return stitch_diag_line(mode, n, nb, lo) + (mode == kModeAuto ? n - lo : n + nb - 1);
+}
+
 // Stitch of a full (not symmetric) matrix: lines [0, nb) are the columns, lines
-// [nb, nb + n + nb - 1) the diagonals k = -(n-1) .. nb-1.  A diagonal that
+// from stitch_diag_line on the diagonals k = -(n-1) .. nb-1.  A diagonal that
 // starts inside a strip (at the left border) has no top-edge summary there.
 __device__ __forceinline__ void stitch_full(StitchLds &L, const JobDesc &j, int64_t line) {
     const int n = j.n, nb = j.nb, H = j.H, S = j.nstrips;
@@ -1517,6 +1762,7 @@ __device__ __forceinline__ void stitch_full(StitchLds &L, const JobDesc &j, int6
     const bool first_band = s_lo == 0, last_band = s_hi >= S;
     if (line < nb) {
         const int col = (int)line;
+        uint32_t w = 0, wn = written32(j, j.vmask, col >> 6, s_lo);
         uint32_t oc = 0, ol = 0;
         if (!first_band) {
             const uint32_t c = *glb(j.cstate + col);
@@ -1525,12 +1771,23 @@ __device__ __forceinline__ void stitch_full(StitchLds &L, const JobDesc &j, int6
         }
         for (int s0 = s_lo; s0 < s_hi; s0 += kStitchBatch) {
             uint32_t fv[kStitchBatch], lv[kStitchBatch];
+            if (((s0 - s_lo) & 31) == 0) {   // the next word is loaded one ahead
+                w = (uint32_t)__builtin_amdgcn_readfirstlane((int)wn);   // (one tile per wave)
+                wn = written32(j, j.vmask, col >> 6, s0 + 32);
+            }
 #pragma unroll
             for (int u = 0; u < kStitchBatch; ++u) {
-                const int64_t idx = (int64_t)(s0 + u - s_lo) * nb + col;
-                if (s0 + u < s_hi) {
-                    fv[u] = *glb(j.vfirst + idx);
-                    lv[u] = *glb(j.vlast + idx);
+                const int s = s0 + u;
+                const int64_t idx = (int64_t)(s - s_lo) * nb + col;
+                if (s < s_hi) {
+                    // The last strip's are always written (its columns end at
+                    // the border); another that is not is white from edge to edge.
+                    fv[u] = (uint32_t)H;
+                    lv[u] = 0u;
+                    if (s == S - 1 || (w >> ((s - s_lo) & 31) & 1u)) {
+                        fv[u] = *glb(j.vfirst + idx);
+                        lv[u] = *glb(j.vlast + idx);
+                    }
                 }
             }
 #pragma unroll
@@ -1553,39 +1810,18 @@ __device__ __forceinline__ void stitch_full(StitchLds &L, const JobDesc &j, int6
         }
         if (last_band) emit_line(L, j, oc, ol);
         else *glb(j.cstate + col) = ol | (oc << 31);
-    } else if (line < (int64_t)nb + n + nb - 1) {
+    } else if (line >= stitch_diag_line(j, 0) && line < stitch_diag_line(j, 0) + n + nb - 1) {
         // Diagonal k: its pieces in the (strip, segment) blocks it crosses, in
         // order; a block's first and last black runs are folded across edges.
-        const int dk = (int)(line - nb);                            // carry slot
+        const int dk = (int)(line - stitch_diag_line(j, 0));        // carry slot
         const int k = dk - (n - 1);
         const int r0 = k < 0 ? -k : 0;                              // first row
         const int r1 = n - 1 < nb - 1 - k ? n - 1 : nb - 1 - k;     // last row
         const int sa = r0 / H > s_lo ? r0 / H : s_lo;               // its strips in this band
         const int sb = r1 / H < s_hi - 1 ? r1 / H : s_hi - 1;
         if (sa > sb) return;
-        const int W = j.seg_tiles * 64;                             // segment width
         uint32_t open = r0 / H < s_lo ? (uint32_t)*glb(j.dstate + dk) : 0u;
-        for (int s = sa; s <= sb; ++s) {
-            const int ra = r0 > s * H ? r0 : s * H;
-            const int rb = r1 < s * H + H - 1 ? r1 : s * H + H - 1;
-            const int ca = ra + k, cb = rb + k;                     // its columns in strip s
-            for (int g = ca / W; g <= cb / W; ++g) {
-                const int lo = ca > g * W ? ca : g * W;
-                const int hi = cb < g * W + W - 1 ? cb : g * W + W - 1;
-                const uint32_t len = (uint32_t)(hi - lo + 1);
-                const bool last = rb == r1 && hi == cb;
-                const int64_t idx = (int64_t)((s - s_lo) * j.segs + g) * j.dw + (s * H + H - 1 - g * W) + k;
-                // A piece that begins where the diagonal begins, below the
-                // strip's top row, starts at the matrix's left border: nothing
-                // enters it, and its runs were counted where they ended.
-                if (!(lo == ca && ra > s * H)) {
-                    const uint32_t fb = *glb(j.dfirst + idx);
-                    if (!last && fb == len) { open += len; continue; }
-                    if (open + fb) emit_stitch(L.bd, kCapD, j.hd, open + fb, 1u, (uint32_t)j.hmax, j.flag);
-                }
-                open = last ? 0u : (uint32_t)*glb(j.dlast + idx);
-            }
-        }
+        open = fold_diagonal<true>(L, j, k, r0, r1, sa, sb, open, 1u);
         if (r1 / H > sb) *glb(j.dstate + dk) = open;
     }
 }
@@ -1606,6 +1842,8 @@ __device__ __forceinline__ void stitch_auto(StitchLds &L, const JobDesc &j, int6
         // ---- column col of the full matrix ----
         const int col = (int)((int64_t)s_lo * H + line);
         const int s_last = col >= wp ? (col - wp) / H : -1;   // strips holding column col of U
+        uint32_t w = 0, wn = written32(j, j.vmask, col >> 6, s_lo);
+        const int tile = __builtin_amdgcn_readfirstlane(col);   // the wave's first column
         const bool has_row = col + wp <= n - 1;               // row col of U has cells
         const int js = has_row ? col / H : (s_last > 0 ? s_last : 0);
         const bool join = js >= s_lo && (js < s_hi || last_band);
@@ -1620,13 +1858,26 @@ __device__ __forceinline__ void stitch_auto(StitchLds &L, const JobDesc &j, int6
         // folded, so a thread has that many loads in flight.
         for (int s0 = s_lo; s0 <= sb; s0 += kStitchBatch) {
             uint32_t fv[kStitchBatch], lv[kStitchBatch];
+            if (((s0 - s_lo) & 31) == 0) {   // the next word is loaded one ahead
+                w = (uint32_t)__builtin_amdgcn_readfirstlane((int)wn);   // (one tile per wave)
+                wn = written32(j, j.vmask, col >> 6, s0 + 32);
+            }
 #pragma unroll
             for (int u = 0; u < kStitchBatch; ++u) {
                 const int s = s0 + u;
                 if (s <= sb) {
                     const int64_t idx = strip_offset(s, n, wp, H) - j.soff_lo + (col - s * H - wp);
-                    fv[u] = *glb(j.vfirst + idx);
-                    lv[u] = *glb(j.vlast + idx);
+                    // A piece that ends inside the strip is always written; one
+                    // that is not is white from edge to edge.
+                    fv[u] = (uint32_t)H;
+                    lv[u] = 0u;
+                    const bool bit = w >> ((s - s_lo) & 31) & 1u;
+                    if (bit || tile - wp < s * H + H - 1) {
+                        const uint32_t f = *glb(j.vfirst + idx), l = *glb(j.vlast + idx);
+                        const bool there = bit || col - wp < s * H + H - 1;
+                        fv[u] = there ? f : fv[u];
+                        lv[u] = there ? l : lv[u];
+                    }
                 }
             }
 #pragma unroll
@@ -1676,49 +1927,41 @@ __device__ __forceinline__ void stitch_auto(StitchLds &L, const JobDesc &j, int6
             else { emit_line(L, j, oc, ol); oc = hc; ol = hl; }
         }
         emit_line(L, j, oc, ol);
-    } else if (line < 2 * lines) {
+    } else if (line >= stitch_diag_line(j, (int64_t)s_lo * H) &&
+               line < stitch_diag_line(j, (int64_t)s_lo * H) + lines) {
         // ---- diagonal k of U (and its mirror) ----
-        const int k = (int)(line - lines);
+        const int k = (int)(line - stitch_diag_line(j, (int64_t)s_lo * H));
         if (k >= wp && j.segs > 1) {
-            // its pieces in the (strip, segment) blocks it crosses, in order
             const int r1 = n - 1 - k;
             const int s_end = r1 / H;                           // >= s_lo
             const int sb = s_end < s_hi - 1 ? s_end : s_hi - 1;
             uint32_t open = carried ? (uint32_t)*glb(j.dstate + k) : 0u;
-            for (int s = s_lo; s <= sb; ++s) {
-                const int ra = s * H;
-                const int rb = r1 < s * H + H - 1 ? r1 : s * H + H - 1;
-                const int ca = ra + k, cb = rb + k;
-                const int xs = ((s * H + wp) >> 6) * 64;   // the strip's first column tile
-                for (int g = seg_of(j, ca); g <= seg_of(j, cb); ++g) {
-                    const int g0 = (j.seg_base + g * j.seg_tiles) * 64;
-                    const int lo = ca > g0 ? ca : g0;
-                    const int hi = cb < g0 + j.seg_tiles * 64 - 1 ? cb : g0 + j.seg_tiles * 64 - 1;
-                    const uint32_t len = (uint32_t)(hi - lo + 1);
-                    const bool last = rb == r1 && hi == cb;
-                    const int bx0 = g0 > xs ? g0 : xs;      // the block's first column
-                    const int64_t idx = (int64_t)((s - s_lo) * j.segs + g) * j.dw +
-                                        (s * H + H - 1 - bx0) + k;
-                    const uint32_t fb = *glb(j.dfirst + idx);
-                    if (!last && fb == len) { open += len; continue; }
-                    if (open + fb) emit_stitch(L.bd, kCapD, j.hd, open + fb, 2u, (uint32_t)n, j.flag);
-                    open = last ? 0u : (uint32_t)*glb(j.dlast + idx);
-                }
-            }
+            open = fold_diagonal<false>(L, j, k, 0, r1, s_lo, sb, open, 2u);
             if (s_end > sb) *glb(j.dstate + k) = open;
         } else if (k >= wp) {
             const int s_last = (n - 1 - k) / H;                 // >= s_lo
             const int sb = s_last < s_hi - 1 ? s_last : s_hi - 1;
             uint32_t open = carried ? (uint32_t)*glb(j.dstate + k) : 0u;
+            const int entry = (k >> 6) + j.kb_off;
+            uint32_t wf = 0, wl = 0;
+            uint32_t wfn = written32(j, j.dfmask, entry, s_lo), wln = written32(j, j.dlmask, entry, s_lo);
             for (int s0 = s_lo; s0 <= sb; s0 += kStitchBatch) {
                 uint32_t fv[kStitchBatch], lv[kStitchBatch];
+                if (((s0 - s_lo) & 31) == 0) {
+                    wf = (uint32_t)__builtin_amdgcn_readfirstlane((int)wfn);
+                    wl = (uint32_t)__builtin_amdgcn_readfirstlane((int)wln);
+                    wfn = written32(j, j.dfmask, entry, s0 + 32);
+                    wln = written32(j, j.dlmask, entry, s0 + 32);
+                }
 #pragma unroll
                 for (int u = 0; u < kStitchBatch; ++u) {
                     const int s = s0 + u;
                     if (s <= sb) {
                         const int64_t idx = strip_offset(s, n, wp, H) - j.soff_lo + (k - wp);
-                        fv[u] = *glb(j.dfirst + idx);
-                        lv[u] = *glb(j.dlast + idx);
+                        fv[u] = 0u;
+                        lv[u] = 0u;
+                        if (wf >> ((s - s_lo) & 31) & 1u) fv[u] = *glb(j.dfirst + idx);
+                        if (wl >> ((s - s_lo) & 31) & 1u) lv[u] = *glb(j.dlast + idx);   // (used if s < s_last)
                     }
                 }
 #pragma unroll
@@ -1734,7 +1977,7 @@ __device__ __forceinline__ void stitch_auto(StitchLds &L, const JobDesc &j, int6
             if (s_last > sb) *glb(j.dstate + k) = open;
         } else if (k == 0 && j.theiler == 0 && s_lo == 0) {
             // main diagonal: every cell (i,i) is recurrent (distance 0 <= eps)
-            emit(L.bd, kCapD, j.hd, (uint32_t)n, 1u, (uint32_t)n, j.flag);
+            emit_stitch(L.bd, kCapD, j.hd, (uint32_t)n, 1u, (uint32_t)n, j.flag);
         }
     }
 }
@@ -1926,13 +2169,19 @@ __global__ void __launch_bounds__(kStatThreads) k_stats_entropy(const JobDesc *_
     __shared__ double red[kStatThreads / 64][3];
     int64_t lo, hi;
     chunk_of(j, blockIdx.x, lo, hi);
+    const unsigned long long *hs[3] = {j.hd, j.hv, j.hw};
     double e[3] = {};
-    for (int64_t base = lo; base < hi; base += kStatLengths) {
-        StatCounts s;
-        load_counts(j, base, hi, s);
-#pragma unroll
-        for (int h = 0; h < 3; ++h)
-            e[h] = e[h] + entropy_part(s.c[h], base, j.mins[h], j.stats->cnt_min[h]);
+    for (int h = 0; h < 3; ++h) {
+        const unsigned long long total = j.stats->cnt_min[h];
+        if (!total) continue;
+        const double C = (double)total;
+        const int64_t from = lo > j.mins[h] ? lo : (int64_t)j.mins[h];
+        for (int64_t l = from + threadIdx.x; l < hi; l += kStatThreads) {
+            const unsigned long long c = *glb(hs[h] + l);
+            if (l == 0 || c == 0) continue;
+            const double p = (double)c / C;
+            e[h] -= p * log(p);
+        }
     }
     block_sums(e, red);
     if (threadIdx.x >= 64) return;
@@ -1943,7 +2192,11 @@ __global__ void __launch_bounds__(kStatThreads) k_stats_entropy(const JobDesc *_
         for (int h = 0; h < 3; ++h)
             __hip_atomic_store(j.ent_part + h * kStatMaxBlocks + blockIdx.x, e[h], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-        done = __hip_atomic_fetch_add(j.stat_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        // The partial sums are agent-scope stores: once they have left (the wait),
+        // the count may follow.  (A release at agent scope writes the whole L2
+        // back, once per block: 74 instead of 36 us for the 400-window batch.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        done = __hip_atomic_fetch_add(j.stat_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
     if (done + 1u != (uint32_t)j.stat_blocks) return;
@@ -2054,9 +2307,10 @@ __global__ void __launch_bounds__(256) k_plot(const PlotDesc d) {
         uint32_t xlo, xhi;
         // The predicate path of the tile kernel: a tile that its column box
         // rules out for every row is empty without evaluating a pair.
-        tile_bits<NORM, M>(cols, d.tau, xr, rowp, d.m, d.thr, d.thr0,
-                                  M > 0 ? to_const(d.box) + (int64_t)c * kBoxStride : nullptr, xlo,
-                                  xhi);
+        bool empty = false;
+        if constexpr (M > 0) empty = box_decides<M>(to_const(d.box) + (int64_t)c * kBoxStride, xr);
+        if (empty) xlo = xhi = 0u;
+        else tile_bits<NORM, M>(cols, d.tau, xr, rowp, d.m, d.thr, d.thr0, xlo, xhi);
         uint64_t vm = 0ull;
         if (i < n) {
             const int hv = nb - jbase < 64 ? nb - jbase : 64;
@@ -2147,9 +2401,12 @@ struct Layout {
     int64_t ventries;      // vertical summary entries per array (first, last), one band
     int64_t dentries;      // diagonal summary entries per array, one band
     int64_t tail_len;
-    int64_t box_floats;    // column boxes (header + records), 0 if none
+    int ncr, ncc;          // boxes of the rows' and the columns' vectors (0: none)
+    int64_t box_floats;    // floats of their planes
+    int mask_words;        // words per mask entry
+    int64_t vmask_entries, dmask_entries;
     size_t off_tail, off_lead, off_vf, off_vl, off_df, off_dl, off_ent, off_nf, off_hf, off_hl, off_box,
-        off_cs, off_ds, bytes;
+        off_mask, off_cs, off_ds, bytes;
 };
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -2254,7 +2511,8 @@ Layout layout_of(const Job &jb) {
     if (L.ventries < 1) L.ventries = 1;
     if (L.dentries < 1) L.dentries = 1;
     L.tail_len = jb.mode == kModeMatrix ? 0 : 64 + (int64_t)(jb.kp.m - 1) * jb.kp.tau;
-    const int64_t lead = jb.mode == kModeAuto ? n : 1;
+    // Row leads: with whole strips only (with segments the row pieces hold them).
+    const int64_t lead = jb.mode == kModeAuto && L.segs == 1 ? n : 1;
     size_t off = 0;
     L.off_tail = off; off += a256(sizeof(float) * (size_t)L.tail_len);
     L.off_lead = off; off += a256(sizeof(uint32_t) * (size_t)lead);
@@ -2272,9 +2530,21 @@ Layout layout_of(const Job &jb) {
     // Boxes for the modes with a predicate and the embedding dimensions whose
     // row coordinates live in registers.
     const int64_t ncols = jb.mode == kModeAuto ? n : jb.n_cols;
-    L.box_floats = (jb.mode != kModeMatrix && jb.kp.m <= kMaxM)
-                       ? kBoxHeader + ((ncols - 1) / 64 + 1) * (int64_t)kBoxStride : 0;
+    const int64_t ctiles = (ncols - 1) / 64 + 1;
+    if (jb.mode != kModeMatrix && jb.kp.m <= kMaxM && ctiles >= kBoxMinTiles) {
+        L.ncc = (int)((ctiles + kGroup - 1) / kGroup * kGroup * (64 / kBoxVecs));
+        L.ncr = jb.mode == kModeAuto ? L.ncc : (int)(((n - 1) / 64 + 1) * (64 / kBoxVecs));
+        L.box_floats = 2 * std::min(jb.kp.m, kBoxK) *
+                       ((int64_t)L.ncc + (jb.mode == kModeAuto ? 0 : L.ncr));
+    }
     L.off_box = off; off += a256(sizeof(float) * (size_t)L.box_floats);
+    // Masks of what summaries were written: a bit per strip of the band, for
+    // every column tile and (twice) every block of 64 diagonals.
+    L.mask_words = (L.band + 31) / 32;
+    L.vmask_entries = ctiles;
+    L.dmask_entries = ctiles + 1 + (jb.mode == kModeAuto ? 0 : (n - 1) / 64 + 1);
+    L.off_mask = off;
+    off += a256(sizeof(uint32_t) * (size_t)((L.vmask_entries + 2 * L.dmask_entries) * L.mask_words));
     // Per-line carries between bands: the open run of each column (of U in
     // auto mode) and of each diagonal (n - 1 + nb of them in a full matrix).
     const bool banded = L.nbands > 1;
@@ -2353,7 +2623,17 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
     d.stats = jb.stats ? reinterpret_cast<JobStats *>(jb.stats)
                        : reinterpret_cast<JobStats *>(reinterpret_cast<char *>(jb.flag) + 8);
     d.ent_part = reinterpret_cast<double *>(scr + lay.off_ent);
-    d.box = lay.box_floats > 0 ? reinterpret_cast<float *>(scr + lay.off_box) : nullptr;
+    d.boxc = lay.box_floats > 0 ? reinterpret_cast<float *>(scr + lay.off_box) : nullptr;
+    d.boxr = jb.mode == kModeAuto || !d.boxc
+                 ? d.boxc : d.boxc + (int64_t)2 * std::min(kp.m, kBoxK) * lay.ncc;
+    d.ncc = lay.ncc;
+    d.ncr = lay.ncr;
+    d.mask_words = lay.mask_words;
+    d.vmask = reinterpret_cast<uint32_t *>(scr + lay.off_mask);
+    d.dfmask = d.vmask + lay.vmask_entries * lay.mask_words;
+    d.dlmask = d.dfmask + lay.dmask_entries * lay.mask_words;
+    d.mask_total = (lay.vmask_entries + 2 * lay.dmask_entries) * lay.mask_words;
+    d.kb_off = 1 + (full ? (int32_t)((jb.n_vec - 1) / 64 + 1) : 0);
     // Fault injection for tests of the give-up path: with
     // RQA_DEBUG_WAIT_GIVEUP=1 in the environment every neighbour wait of the
     // tile kernel aims at a count no wave reaches and gives up after 64
@@ -2372,16 +2652,9 @@ void launch_stats(const JobDesc *jobs, int blocks, int njobs, hipStream_t st) {
         hipLaunchKernelGGL(k_stats_entropy, dim3(blocks, njobs), dim3(kStatThreads), 0, st, jobs);
 }
 
-// Blocks of k_box_bounds for one job: one thread per box entry, at most 128
-// blocks (the kernel strides over the rest).
-int box_blocks_of(const Layout &lay) {
-    const int64_t entries = lay.box_floats > 0 ? (lay.box_floats - kBoxHeader) / kBoxStride * kBoxK : 0;
-    return (int)std::min<int64_t>(128, std::max<int64_t>(1, (entries + 255) / 256));
-}
-
 int stitch_blocks_of(const Job &jb) {
     const bool full = jb.mode != kModeAuto;
-    const int64_t lines = full ? jb.n_cols + jb.n_vec + jb.n_cols - 1 : 2 * jb.n_vec;
+    const int64_t lines = stitch_lines(jb.mode, jb.n_vec, full ? jb.n_cols : jb.n_vec, 0);
     return (int)((lines + kStitchThreads - 1) / kStitchThreads);
 }
 
@@ -2497,7 +2770,6 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
     std::vector<int> gkeys;
     int stitch_blocks = 0;
     int stat_grid = 1;
-    int box_grid = 1;
     int ngroups = 0;
     int strip_acc = 0;
     for (int r = 0; r < njobs; ++r) {
@@ -2518,7 +2790,6 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         hgroups[ngroups - 1].job1 = r + 1;
         JobDesc d = make_desc(jb, lay, strip_acc, stitch_blocks);
         stat_grid = std::max(stat_grid, (int)d.stat_blocks);
-        box_grid = std::max(box_grid, box_blocks_of(lay));
         strip_acc += lay.items;
         stitch_blocks += stitch_blocks_of(jb);
         hdesc[r] = d;
@@ -2538,8 +2809,6 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
                            ddesc, dgroups, dcounters);
     else
         hipLaunchKernelGGL(k_prepare, dim3(kPrepareBlocks, njobs), dim3(256), 0, st, ddesc, dcounters);
-    hipLaunchKernelGGL(k_box_bounds, dim3(box_grid, njobs), dim3(256), 0, st, ddesc);
-    hipLaunchKernelGGL(k_box_probe, dim3(njobs), dim3(kProbeThreads), 0, st, ddesc);
 
     if (phases) hipEventRecord(phases->ev[1], st);
     if (njobs == 1 && hdesc[0].nbands > 1) {
@@ -2549,7 +2818,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         const Job &jb = jobs_in[0];
         TileKernel kern = tile_kernel(jb.mode, jb.kp.norm, jb.kp.m);
         int occ = 0;
-        const size_t lds = strip_lds_bytes(jb.waves);
+        const size_t lds = kStripLdsBytes;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * jb.waves, lds) != hipSuccess ||
             occ < 1)
             occ = 1;
@@ -2558,9 +2827,8 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
             const int lo = b * d.band_strips;
             const int hi = std::min(lo + d.band_strips, d.nstrips);
             const int items = (hi - lo) * d.segs;
-            const int64_t lines = d.mode == kModeAuto ? 2 * ((int64_t)d.n - (int64_t)lo * d.H)
-                                                      : (int64_t)d.nb + d.n + d.nb - 1;
-            hipLaunchKernelGGL(k_band, dim3(1), dim3(64), 0, st, ddesc, dgroups, dcounters, b);
+            const int64_t lines = stitch_lines(d.mode, d.n, d.nb, (int64_t)lo * d.H);
+            hipLaunchKernelGGL(k_band, dim3(64), dim3(256), 0, st, ddesc, dgroups, dcounters, b);
             if (items > 0)
                 hipLaunchKernelGGL(kern, dim3(std::min(full_grid, items)), dim3(64 * jb.waves), lds, st,
                                    ddesc, dgroups, 0, dcounters);
@@ -2586,7 +2854,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         const int w = jobs_in[order[gd.job0]].waves;
         TileKernel kern = tile_kernel(jobs_in[order[gd.job0]].mode, kp.norm, kp.m);
         int occ = 0;
-        const size_t lds = strip_lds_bytes(w);
+        const size_t lds = kStripLdsBytes;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * w, lds) != hipSuccess ||
             occ < 1)
             occ = 1;
@@ -2622,6 +2890,19 @@ size_t engine_static_bytes(const Job &jb) {
     return engine_launch_scratch_bytes(1) + a256(kInfoBytes) + layout_of(jb).bytes;
 }
 
+// What the static scratch limit counts: all of it but the boxes and the masks,
+// whose room is set aside apart from the limit, and eight floats per column
+// tile in their place, so the series that fit are the ones that always did.
+size_t engine_static_charge(const Job &jb) {
+    const Layout lay = layout_of(jb);
+    const size_t own = a256(sizeof(float) * (size_t)lay.box_floats) +
+                       a256(sizeof(uint32_t) *
+                            (size_t)((lay.vmask_entries + 2 * lay.dmask_entries) * lay.mask_words));
+    const size_t tiles = (size_t)((jb.n_vec - 1) / 64 + 1);
+    return engine_static_bytes(jb) - own +
+           (jb.kp.m <= kMaxM ? a256(sizeof(float) * (64 + 8 * tiles)) : 0);
+}
+
 int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     if (jb.waves < 1 || jb.waves > kMaxWaves || jb.mode != kModeAuto) return RQA_EINVAL;
     int dev = 0, ncu = 0;
@@ -2641,12 +2922,10 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     const GroupDesc g{0, 1, lay.items, 0};
     hipLaunchKernelGGL(k_prepare_one, dim3(kPrepareBlocks), dim3(256), 0, st, d, g, ddesc, dgroups,
                        dcounters);
-    hipLaunchKernelGGL(k_box_bounds, dim3(box_blocks_of(lay), 1), dim3(256), 0, st, ddesc);
-    hipLaunchKernelGGL(k_box_probe, dim3(1), dim3(kProbeThreads), 0, st, ddesc);
     if (lay.items > 0) {
         TileKernel kern = tile_kernel(kModeAuto, jb.kp.norm, jb.kp.m);
         int occ = 0;
-        const size_t lds = strip_lds_bytes(jb.waves);
+        const size_t lds = kStripLdsBytes;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * jb.waves, lds) != hipSuccess ||
             occ < 1)
             occ = 1;
