@@ -76,39 +76,35 @@ using namespace rqa;
 
 // ---------------------------------------------------------------------------
 // Workgroup-shape autotuner.  For a launch signature (norm, m, size class,
-// number of jobs) it times each candidate shape on real runs (the tile phase,
-// measured with hipEvents when the run's result is fetched) and then keeps the
+// number of jobs) it times each candidate shape on real runs (tiles, stitch and
+// statistics, measured with hipEvents when the run's result is fetched) and then keeps the
 // fastest.  Results never depend on the shape, so trial runs are ordinary runs.
 // The table is process-wide; with RQA_AUTOTUNE_CACHE=<file> decisions persist
 // across processes as "key waves" lines.
 // ---------------------------------------------------------------------------
 namespace {
 
-constexpr int kCandidates[] = {2, 4, 8};
 constexpr int kNumCandidates = 3;
-// A trial this much slower than the best so far ends the trials in its
-// direction (fewer or more waves than the default shape): at N = 1M the
-// 4-wave shape is 12% slower than 8 waves and 2 waves 65% slower.
-constexpr double kGiveUp = 1.10;
 
 struct TuneEntry {
-    int cand[kNumCandidates] = {};   // trial order: the default shape first, then fewer
-    int ncand = 0;                   // waves, then more
-    int dflt = 0;
+    int cand[kNumCandidates] = {};   // trials: the default shape, its neighbour, the default again
+    int ncand = 0;
     int next = 0;          // next candidate to try
     int best = 0;          // best waves so far
     double best_ms = 1e300;
     bool done = false;
 };
 
-void tune_init(TuneEntry &e, int dflt) {
-    e.dflt = dflt;
-    e.ncand = 0;
-    e.cand[e.ncand++] = dflt;
-    for (int k = kNumCandidates - 1; k >= 0; --k)
-        if (kCandidates[k] < dflt) e.cand[e.ncand++] = kCandidates[k];
-    for (int k = 0; k < kNumCandidates; ++k)
-        if (kCandidates[k] > dflt) e.cand[e.ncand++] = kCandidates[k];
+// Three trials: the default shape, its neighbour (8 and 4 waves; below 4,096
+// delay vectors 4 and 2), and the default again, because a signature's first run
+// is a cold one: with one run per shape the 65,521-point Lorenz series settled on
+// 4 waves (640 us) instead of 8 (500 us).  Two waves are never the fastest from
+// 4,096 vectors on.
+void tune_init(TuneEntry &e, int dflt, int64_t nmax) {
+    const int other = dflt > 4 ? 4 : (nmax < 4096 ? 2 : 8);
+    e.ncand = 3;
+    e.cand[0] = e.cand[2] = dflt;
+    e.cand[1] = other;
 }
 
 std::mutex g_tune_mu;
@@ -276,7 +272,11 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
     const size_t info_block_off = total;
     total += align256(kInfoBytes * static_cast<size_t>(count));
     const size_t hist_block_off = total;
-    for (int32_t w = 0; w < count; ++w) jobs[w].waves = waves;
+    for (int32_t w = 0; w < count; ++w) {
+        jobs[w].waves = waves;
+        jobs[w].fine = count == 1;
+    }
+    if (count > 1) engine_batch_segs(jobs);
     // A job run alone (a series, a cross pair or a given matrix) is cut into
     // row bands when its line summaries would exceed the workspace limit.
     if (count == 1) {
@@ -292,7 +292,6 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
         sig = fnv(sig, &jobs[0].band_strips, sizeof jobs[0].band_strips);
     }
     Job first = jobs[0];
-    if (count > 1 && first.segs == 0) first.segs = 1;   // as the engine launches it
     const JobPlan plan = engine_job_plan(first);
     for (int32_t w = 0; w < count; ++w) {
         nvec[w] = jobs[w].n_vec;
@@ -409,7 +408,7 @@ int enqueue(rqa_handle *h, const float *d_series, int64_t n_points, const int64_
         std::lock_guard<std::mutex> lk(g_tune_mu);
         tune_load_locked();
         TuneEntry &e = g_tune[key];
-        if (!e.done && e.ncand == 0) tune_init(e, engine_default_waves(nmax));
+        if (!e.done && e.ncand == 0) tune_init(e, engine_default_waves(nmax), nmax);
         if (e.done) {
             waves = e.best;
         } else {
@@ -449,12 +448,14 @@ int enqueue_full(rqa_handle *h, Job jb, void *stream) {
     return launch(h, jobs, waves, false, std::string(), sig, stream, false);
 }
 
-// Record the tile-phase time of a finished autotuning trial.
+// Record the time of a finished autotuning trial: tiles, stitch and statistics
+// (fewer waves per workgroup mean more strips to stitch: 65,521 Lorenz points take
+// 0.39 + 0.10 ms with 8 waves, 0.45 + 0.16 with 4).
 void finish_trial(rqa_handle *h) {
     if (!h->trial) return;
     h->trial = false;
     float ms = 0.f;
-    if (hipEventElapsedTime(&ms, h->prof.ev[1], h->prof.ev[2]) != hipSuccess) {
+    if (hipEventElapsedTime(&ms, h->prof.ev[1], h->prof.ev[3]) != hipSuccess) {
         (void)hipGetLastError();
         return;
     }
@@ -465,14 +466,6 @@ void finish_trial(rqa_handle *h) {
     if (ms < e.best_ms) {
         e.best_ms = ms;
         e.best = w;
-    } else if (ms > kGiveUp * e.best_ms && w != e.dflt) {
-        // drop the untried shapes beyond this one, on its side of the default
-        int keep = e.next + 1;
-        for (int k = e.next + 1; k < e.ncand; ++k) {
-            const bool beyond = w < e.dflt ? e.cand[k] < w : e.cand[k] > w;
-            if (!beyond) e.cand[keep++] = e.cand[k];
-        }
-        e.ncand = keep;
     }
     if (++e.next >= e.ncand) {
         e.done = true;
@@ -782,6 +775,7 @@ int rqa_workspace_plan(const rqa_params *p, int64_t n_points, int32_t waves, int
     jb.n_cols = nv;
     jb.kp = make_kparams(*p);
     jb.waves = waves > 0 ? waves : engine_default_waves(nv);
+    jb.fine = true;
     jb.band_strips = engine_band_strips(jb, static_cast<size_t>(limit_bytes));
     const JobPlan plan = engine_job_plan(jb);
     if (bands) *bands = plan.bands;

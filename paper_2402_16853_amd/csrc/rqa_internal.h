@@ -72,6 +72,8 @@ struct Job {
     int segs = 0;                   // auto mode: column segments per strip (0: the engine
                                     // decides, 1 for a job launched with others); scratch
                                     // is sized for the largest choice
+    bool fine = false;              // a job launched alone: its chain of tiles may be cut into
+                                    // segments narrower than 64 tiles (a handle's own run)
     int band_strips = 0;            // auto mode, a job launched alone: strips per row
                                     // band (0: one band).  The strip-edge summaries then
                                     // hold one band's strips and per-line carries pass
@@ -110,6 +112,10 @@ struct JobPlan {
     size_t scratch_bytes;
 };
 JobPlan engine_job_plan(const Job &job);
+
+// Column segments of the jobs of a batch whose workspace is laid out for it
+// (their `waves` are set).
+void engine_batch_segs(std::vector<Job> &jobs);
 
 // Default waves per workgroup for a job of n delay vectors.
 int engine_default_waves(int64_t n);

@@ -88,7 +88,8 @@ namespace {
 constexpr int kMaxWaves = 8;
 constexpr int kCapD = 1024;    // LDS bins for diagonal lengths < kCapD
 constexpr int kCapV = 1024;    // LDS bins for vertical lengths < kCapV
-constexpr int kCapW = 6016;    // LDS bins for white-vertical lengths < kCapW
+constexpr int kCapW = 6016;    // LDS bins for white-vertical lengths < kCapW; a launch whose
+                               // jobs have no longer line takes fewer (GroupDesc::capw)
 constexpr int kMaxM = 6;       // embedding dimensions held in registers
 constexpr int kRing = 32;      // column-state slots: tiles wave 0 may run ahead of the last wave
 constexpr int kDiagRing = 64;  // diagonal-state slots (of 64 diagonals each); at most
@@ -187,7 +188,8 @@ struct JobDesc {
 struct GroupDesc {
     int32_t job0, job1;        // jobs [job0, job1) of the descriptor table
     int32_t items;             // total strips of the group
-    int32_t pad;
+    int32_t capw;              // LDS bins for white lengths: enough for the longest line, at
+                               // most kCapW (short jobs: more workgroups per CU, less to clear)
 };
 
 __host__ __device__ inline int64_t strip_offset(int32_t s, int32_t n, int32_t wp, int32_t H) {
@@ -306,6 +308,7 @@ __device__ __forceinline__ void g_or(int *p, int v) {
 // vertical (kCapW) lengths.
 struct Bins {
     uint32_t *d, *v, *w;
+    int capw;
 };
 
 // A length beyond the LDS bins goes to the global histogram; one beyond the
@@ -367,7 +370,7 @@ __device__ __forceinline__ void finish_row(const JobDesc &j, const Bins &bins, u
                                            uint32_t len, uint32_t first, uint32_t *slot, uint32_t off) {
     if (first) {
         glb(slot)[off] = len | (color << 31);
-    } else if (len < (color ? (uint32_t)kCapV : (uint32_t)kCapW)) {
+    } else if (len < (color ? (uint32_t)kCapV : (uint32_t)bins.capw)) {
         atomicAdd((color ? bins.v : bins.w) + len, 1u);
     } else {
         emit_global(color ? j.hv : j.hw, len, 1u, (uint32_t)j.hmax, j.flag);
@@ -871,6 +874,7 @@ __global__ void k_band(JobDesc *jobs, GroupDesc *groups, int *counters, int b) {
 // most 80 VGPRs), i.e. three 8-wave workgroups per CU.
 struct StripLds {
     uint32_t *bd, *bv, *bw;
+    int capw;           // entries of bw
     uint16_t *vst;      // [kRing][64]
     uint16_t *dst;      // [kDiagRing][64]
     int *prog;          // [kMaxWaves + 1]
@@ -887,9 +891,10 @@ struct StripLds {
 // kFreshColumn any more.
 constexpr uint32_t kHasBlack = 1u, kHasWhite = 2u, kStored = 4u;
 
-constexpr size_t kStripLdsBytes =
-    sizeof(uint32_t) * ((size_t)kCapD + kCapV + kCapW) + sizeof(uint16_t) * 64 * (kRing + kDiagRing) +
+constexpr size_t strip_lds_bytes(int capw) {
+    return sizeof(uint32_t) * ((size_t)kCapD + kCapV + capw) + sizeof(uint16_t) * 64 * (kRing + kDiagRing) +
     sizeof(int) * (kMaxWaves + 1) + (size_t)(kMaxWaves + 1) * kRing + 3 * sizeof(uint32_t) + 16;
+}
 
 // Wait (wave-uniform) until the counter reaches `target`; returns its value.  Each
 // wait is bounded: past j.spin_limit polls it gives up (ok = false), so a wave
@@ -917,8 +922,8 @@ __device__ __forceinline__ void publish_counter(int *ctr, int value) {
 __device__ void flush_bins(const StripLds &L, const JobDesc &j) {
     // No line is longer than hmax.  (Where a wait gave up, the job is flagged as
     // failed, and bins may hold any length: all are cleared.)
-    const int bins = j.hmax + 1 < kCapW && !*L.bad ? j.hmax + 1 : kCapW;
-    for (int t = threadIdx.x; t < bins; t += blockDim.x) {
+    const int bins = j.hmax + 1 < L.capw && !*L.bad ? j.hmax + 1 : L.capw;
+    for (int t = threadIdx.x; t < bins || (*L.bad && t < kCapV); t += blockDim.x) {
         if (t < kCapD) {
             const uint32_t v = L.bd[t];
             if (v) { if (t <= j.hmax) g_add(j.hd + t, (unsigned long long)v); L.bd[t] = 0; }
@@ -927,7 +932,7 @@ __device__ void flush_bins(const StripLds &L, const JobDesc &j) {
             const uint32_t v = L.bv[t];
             if (v) { if (t <= j.hmax) g_add(j.hv + t, (unsigned long long)v); L.bv[t] = 0; }
         }
-        const uint32_t v = L.bw[t];
+        const uint32_t v = t < L.capw ? L.bw[t] : 0u;
         if (v) { if (t <= j.hmax) g_add(j.hw + t, (unsigned long long)v); L.bw[t] = 0; }
     }
 }
@@ -1034,7 +1039,7 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
         for (int k = 0; k < (M > 0 ? M : 1); ++k) asm volatile("" : "+v"(xr[k]));
     }
 
-    Bins bins{L.bd, L.bv, L.bw};
+    Bins bins{L.bd, L.bv, L.bw, L.capw};
     // Horizontal runs: with segments, each row's piece in this block records
     // its first and last runs (hfirst / hlast); otherwise the row's first run
     // is its lead.
@@ -1481,19 +1486,16 @@ k_tiles(const JobDesc *__restrict__ jobs, const GroupDesc *__restrict__ groups, 
     L.bd = lds_words;
     L.bv = L.bd + kCapD;
     L.bw = L.bv + kCapV;
-    L.vst = reinterpret_cast<uint16_t *>(L.bw + kCapW);
+    const GroupDesc gd = groups[g];
+    L.capw = gd.capw;
+    L.vst = reinterpret_cast<uint16_t *>(L.bw + gd.capw);
     L.dst = L.vst + kRing * 64;
     L.prog = reinterpret_cast<int *>(L.dst + kDiagRing * 64);
     L.note = reinterpret_cast<uint8_t *>(L.prog + kMaxWaves + 1);
     L.words = reinterpret_cast<uint32_t *>(L.note + (kMaxWaves + 1) * kRing);
     L.item = reinterpret_cast<int *>(L.words + 3);
     L.bad = L.item + 1;
-    const GroupDesc gd = groups[g];
-    for (int t = threadIdx.x; t < kCapW; t += blockDim.x) {
-        if (t < kCapD) L.bd[t] = 0;
-        if (t < kCapV) L.bv[t] = 0;
-        L.bw[t] = 0;
-    }
+    for (int t = threadIdx.x; t < kCapD + kCapV + gd.capw; t += blockDim.x) L.bd[t] = 0;
     __syncthreads();
     while (true) {
         if (threadIdx.x == 0) {
@@ -2431,27 +2433,37 @@ int effective_wp(int32_t theiler, int64_t n) {
 }
 
 int default_waves_impl(int64_t n) {
-    // Eight waves per workgroup (two workgroups per compute unit) measured
-    // fastest for long series; short series use four so that more strips exist.
-    if (n >= 4096 * 8) return 8;
+    // Eight waves per workgroup measured fastest from about 16,000 vectors on
+    // (20,000 Lorenz points, tiles + stitch: 156 us, 177 with four); shorter
+    // series use four so that more strips exist.
+    if (n >= 16384) return 8;
     return 4;
 }
 
 // Column segments of an auto-mode job when it runs alone (`nstrips`: the
-// strips of one launch, i.e. of one row band): enough for about kSegItems
-// work items, each at least 64 tiles wide; 1 for jobs whose first strip is
-// shorter than 128 tiles (their chains are short) or that have more than
-// kTargetItems / 2 strips already (the 1,048,576-point workload has 2,048,
-// the paper's 1,000,001-point sine 1,954: cutting it in two measured 5%
-// slower, the extra summaries costing more than the shorter chains gain).
-// kSegItems rather than kTargetItems items: shorter chains measured faster
-// on dense jobs (a 199,873-vector served job at RR 5%: 13.9 ms with 2,048
-// items, 12.1 with 4,096, 11.5 with 8,192; a 300,000-point Lorenz series
-// 9.2 / 8.3 / 7.8 ms).
-int auto_segs_max(int64_t n, int wp, int H, int nstrips) {
+// strips of one launch, i.e. of one row band).
+//  * Enough for about kSegItems work items, each at least 64 tiles wide, for
+//    jobs whose first strip has 128 tiles or more (a 199,873-vector served job at
+//    RR 5%: 13.9 ms with 2,048 items, 12.1 with 4,096, 11.5 with 8,192; a
+//    300,000-point Lorenz series 9.2 / 8.3 / 7.8 ms).
+//  * With `fine` (a handle's own run) at least kFineSegs, however narrow: a short
+//    job is its longest chain of tiles (7 us each at RR 12%, for want of other
+//    waves to hide their latency), and cutting it into 16 to 20 costs less in
+//    the stitch than it saves.  Tile kernel + stitch, whole strips -> cut: 500
+//    points 73 -> 41 us, 2,000 (RR 12%) 270 -> 72, 9,973 (AR(1)) 500 -> 149, 20,000
+//    (Lorenz) 254 -> 156; at 65,521 points both rules give about the same.
+//    (A served job keeps the first rule, and its footprint.)
+//  * 1 for jobs of more than kTargetItems / 2 strips (the 1,048,576-point workload
+//    has 2,048): whole strips leave no CU idle there.
+constexpr int kFineSegs = 20;
+int auto_segs_max(int64_t n, int wp, int H, int nstrips, bool fine) {
     const int T0 = (int)((n - 1) / 64 - wp / 64 + 1);
-    if (nstrips < 1 || T0 < 128 || 2 * nstrips > kTargetItems) return 1;
-    return (int)std::max<int64_t>(1, std::min<int64_t>((kSegItems + nstrips - 1) / nstrips, T0 / 64));
+    if (nstrips < 1 || 2 * nstrips > kTargetItems) return 1;
+    int segs = 1;
+    if (T0 >= 128)
+        segs = (int)std::max<int64_t>(1, std::min<int64_t>((kSegItems + nstrips - 1) / nstrips, T0 / 64));
+    if (fine) segs = std::max(segs, std::min(T0, kFineSegs));
+    return segs;
 }
 
 Layout layout_of(const Job &jb) {
@@ -2470,7 +2482,7 @@ Layout layout_of(const Job &jb) {
         L.ventries = strip_offset(L.band, (int32_t)n, wp, L.H);
         // Segments: as set on the job, else the most it could be given.
         const int T0 = (int)((n - 1) / 64 - wp / 64 + 1);
-        int segs = jb.segs > 0 ? jb.segs : auto_segs_max(n, wp, L.H, L.band);
+        int segs = jb.segs > 0 ? std::min(jb.segs, std::max(T0, 1)) : auto_segs_max(n, wp, L.H, L.band, jb.fine);
         L.seg_base = wp / 64;
         L.seg_tiles = (T0 + segs - 1) / segs;
         L.segs = segs > 1 ? (T0 + L.seg_tiles - 1) / L.seg_tiles : 1;
@@ -2487,15 +2499,14 @@ Layout layout_of(const Job &jb) {
         // A strip of a full matrix walks every column tile; its chain of
         // tiles is cut into column segments walked by different workgroups,
         // enough of them for about kFullItems work items, each at least
-        // max(8, H/64) tiles wide (so a diagonal crosses at most one segment
-        // edge inside a strip).
+        // max(8, H/64) tiles wide, or a kFineSegs-th of a short chain.
         const int64_t nb = jb.n_cols;
         L.nstrips = (int)((n + L.H - 1) / L.H);
         // Row bands as in auto mode: summaries for one band's strips.
         L.band = jb.band_strips > 0 && jb.band_strips < L.nstrips ? jb.band_strips : L.nstrips;
         L.nbands = (L.nstrips + L.band - 1) / L.band;
         const int T = (int)((nb - 1) / 64 + 1);
-        const int min_tiles = std::max(8, L.H / 64);
+        const int min_tiles = std::max(1, std::min(std::max(8, L.H / 64), T / kFineSegs));
         int segs = (int)std::min<int64_t>((kFullItems + L.band - 1) / L.band,
                                           std::max(1, T / min_tiles));
         segs = std::max(segs, 1);
@@ -2652,6 +2663,11 @@ void launch_stats(const JobDesc *jobs, int blocks, int njobs, hipStream_t st) {
         hipLaunchKernelGGL(k_stats_entropy, dim3(blocks, njobs), dim3(kStatThreads), 0, st, jobs);
 }
 
+// LDS bins for the white lengths of a job.
+int white_bins_of(const Job &jb) {
+    return (int)std::min<int64_t>(kCapW, (jb.hist_len() + 63) / 64 * 64);
+}
+
 int stitch_blocks_of(const Job &jb) {
     const bool full = jb.mode != kModeAuto;
     const int64_t lines = stitch_lines(jb.mode, jb.n_vec, full ? jb.n_cols : jb.n_vec, 0);
@@ -2693,6 +2709,18 @@ JobPlan engine_job_plan(const Job &job) {
 }
 
 int engine_default_waves(int64_t n) { return default_waves_impl(n); }
+
+// Few windows, or short ones, leave CUs idle as whole strips: the chains of
+// tiles are then cut so that the launch has about kBatchItems work items (at
+// least two tiles each).
+void engine_batch_segs(std::vector<Job> &jobs) {
+    constexpr int64_t kBatchItems = 4096;
+    int64_t strips = 0;
+    for (const Job &jb : jobs) strips += (jb.n_vec + 64 * jb.waves - 1) / (64 * jb.waves);
+    const int64_t segs = kBatchItems / std::max<int64_t>(strips, 1);
+    for (Job &jb : jobs)
+        jb.segs = (int)std::max<int64_t>(1, std::min<int64_t>({segs, jb.n_vec / 128, kFineSegs}));
+}
 
 size_t engine_launch_scratch_bytes(size_t njobs) {
     return a256(sizeof(JobDesc) * njobs) + a256(sizeof(GroupDesc) * 64) + 256;
@@ -2776,18 +2804,19 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         // A job launched with others keeps whole strips: the launch has work
         // items enough, and its scratch is sized for any choice.
         Job jb = jobs_in[order[r]];
-        if (jb.segs == 0 && njobs > 1) jb.segs = 1;
+        if (jb.segs == 0 && njobs > 1) jb.segs = 1;   // (or what engine_batch_segs chose)
         const Layout lay = layout_of(jb);
         const int key = group_key(jb);
         if (ngroups == 0 || gkeys.back() != key) {
             if (ngroups == 64) return RQA_EINVAL;
             if (ngroups > 0) hgroups[ngroups - 1].items = strip_acc;
             gkeys.push_back(key);
-            hgroups[ngroups] = GroupDesc{r, r + 1, 0, 0};
+            hgroups[ngroups] = GroupDesc{r, r + 1, 0, 0};   // items, capw: below
             ++ngroups;
             strip_acc = 0;
         }
         hgroups[ngroups - 1].job1 = r + 1;
+        hgroups[ngroups - 1].capw = std::max(hgroups[ngroups - 1].capw, white_bins_of(jb));
         JobDesc d = make_desc(jb, lay, strip_acc, stitch_blocks);
         stat_grid = std::max(stat_grid, (int)d.stat_blocks);
         strip_acc += lay.items;
@@ -2818,7 +2847,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         const Job &jb = jobs_in[0];
         TileKernel kern = tile_kernel(jb.mode, jb.kp.norm, jb.kp.m);
         int occ = 0;
-        const size_t lds = kStripLdsBytes;
+        const size_t lds = strip_lds_bytes(hgroups[0].capw);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * jb.waves, lds) != hipSuccess ||
             occ < 1)
             occ = 1;
@@ -2854,7 +2883,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         const int w = jobs_in[order[gd.job0]].waves;
         TileKernel kern = tile_kernel(jobs_in[order[gd.job0]].mode, kp.norm, kp.m);
         int occ = 0;
-        const size_t lds = kStripLdsBytes;
+        const size_t lds = strip_lds_bytes(gd.capw);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * w, lds) != hipSuccess ||
             occ < 1)
             occ = 1;
@@ -2919,13 +2948,13 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     jb.scratch = base + engine_launch_scratch_bytes(1) + a256(kInfoBytes);
     const Layout lay = layout_of(jb);
     const JobDesc d = make_desc(jb, lay, 0, 0);
-    const GroupDesc g{0, 1, lay.items, 0};
+    const GroupDesc g{0, 1, lay.items, white_bins_of(jb)};
     hipLaunchKernelGGL(k_prepare_one, dim3(kPrepareBlocks), dim3(256), 0, st, d, g, ddesc, dgroups,
                        dcounters);
     if (lay.items > 0) {
         TileKernel kern = tile_kernel(kModeAuto, jb.kp.norm, jb.kp.m);
         int occ = 0;
-        const size_t lds = kStripLdsBytes;
+        const size_t lds = strip_lds_bytes(g.capw);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * jb.waves, lds) != hipSuccess ||
             occ < 1)
             occ = 1;
