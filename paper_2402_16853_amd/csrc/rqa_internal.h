@@ -163,10 +163,10 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t stream);
 
 // Recurrence plot: the masked matrix of series a (b == nullptr) or the cross
 // matrix of a and b, bit-packed into `bits` (rows of `words` u64), on `stream`.
-// `scratch` holds engine_plot_scratch_floats(kp, nb) device floats (the last
-// column tile's coordinates and the column boxes of the exact tile pruning),
-// nb being the number of column vectors.
-int64_t engine_plot_scratch_floats(const KParams &kp, int64_t nb);
+// `scratch` holds engine_plot_scratch_floats(kp, n, nb, cross) device floats (the
+// last column tile's coordinates and the boxes of the exact pruning), n and nb
+// being the numbers of row and column vectors.
+int64_t engine_plot_scratch_floats(const KParams &kp, int64_t n, int64_t nb, bool cross);
 int engine_plot(const KParams &kp, const float *a, int64_t na_points, const float *b,
                 int64_t nb_points, uint64_t *bits, int64_t words, float *scratch,
                 hipStream_t stream);

@@ -115,7 +115,6 @@ constexpr int kCounters = 64;        // work counters of a launch
 constexpr int kBoxK = 3;
 constexpr int kBoxVecs = 8;
 constexpr int kBoxMinTiles = 128;
-constexpr int kBoxStride = 8;        // recurrence plot: floats per column tile's record
 
 // Device-side description of one job (one series or window).
 struct JobDesc {
@@ -526,24 +525,6 @@ __device__ __forceinline__ uint32_t nonrec_sign_dyn(ConstF col, const float *__r
     return __float_as_uint(thr - a);
 }
 
-// Box test.  `rec` holds, for the first kBoxK coordinates k of a tile's
-// columns, lo_k = the smallest float l with fl(cmin_k - l) <= b and hi_k = the
-// largest float h with fl(h - cmax_k) <= b, where cmin_k / cmax_k are the
-// smallest / largest k-th coordinate of those columns and b is the
-// per-coordinate bound of KParams::d0_bound.  Subtraction is monotone in each
-// operand, so a row coordinate x_k < lo_k (or > hi_k) makes |d_k| > b against
-// every column of the tile, and the accumulated distance, never below its
-// largest term, then exceeds the threshold: the pair is not recurrent.  True
-// when every row of the wave is decided so by some coordinate.
-template <int M>
-__device__ __forceinline__ bool box_decides(ConstF rec, const float *xr) {
-    constexpr int K = M < kBoxK ? M : kBoxK;
-    bool out = false;
-#pragma unroll
-    for (int k = 0; k < K; ++k) out = out | (xr[k] < rec[2 * k]) | (xr[k] > rec[2 * k + 1]);
-    return __builtin_amdgcn_ballot_w64(!out) == 0ull;
-}
-
 // Recurrence of eight columns for this lane's row: bit b of the result is set when
 // column b of the chunk at `cb` is NOT recurrent (on top of acc << 8).
 // m >= 5 takes the first coordinate's differences first: when no lane of the
@@ -668,19 +649,24 @@ __device__ __forceinline__ void tile_bits_some(ConstF cols, int tau, const float
 // Cost: about 90 VALU instructions per 8 tiles.  On the 1M-point Lorenz series
 // 2.0 of 8 chunks per tile are left to evaluate (4.6 with one box per 64
 // columns), on the 1M-point sine 0.6.
+struct Boxes {
+    const float *r, *c;   // planes of the rows' and the columns' boxes
+    int64_t nr, nc;       // entries per plane
+    float thr;
+};
 template <int NORM, int M>
-__device__ __forceinline__ void classify(const JobDesc &j, int rb, int cg, int lane, uint64_t &act,
+__device__ __forceinline__ void classify(const Boxes &bx, int rb, int cg, int lane, uint64_t &act,
                                          uint64_t &full) {
     constexpr int K = M < kBoxK ? M : kBoxK;
     float yn[K], yx[K];
-    const auto pc = glb(j.boxc) + (int64_t)cg * (kGroup * 8) + lane;
+    const auto pc = glb(bx.c) + (int64_t)cg * (kGroup * 8) + lane;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        yn[k] = pc[(int64_t)(2 * k) * j.ncc];
-        yx[k] = pc[(int64_t)(2 * k + 1) * j.ncc];
+        yn[k] = pc[(2 * k) * bx.nc];
+        yx[k] = pc[(2 * k + 1) * bx.nc];
     }
-    const ConstF pr = to_const(j.boxr) + (int64_t)rb * 8;
-    const int64_t ncr = j.ncr;
+    const ConstF pr = to_const(bx.r) + (int64_t)rb * 8;
+    const int64_t ncr = bx.nr;
     float best = INFINITY, worst = 0.0f;
 #pragma unroll 1
     for (int r0 = 0; r0 < 8; r0 += 4) {
@@ -699,60 +685,26 @@ __device__ __forceinline__ void classify(const JobDesc &j, int rb, int cg, int l
         best = fminf(fminf(best, fminf(a[0], a[1])), fminf(a[2], a[3]));
         if (M <= kBoxK) worst = fmaxf(fmaxf(worst, fmaxf(a[0], a[1])), fmaxf(a[2], a[3]));
     }
-    const float thr = j.thr;
+    const float thr = bx.thr;
     act = __builtin_amdgcn_ballot_w64(best <= thr);
     full = 0ull;
     if (M <= kBoxK && __builtin_amdgcn_ballot_w64(worst <= thr) != 0ull) {
         float a = 0.0f;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            float bn = INFINITY, bx = -INFINITY;   // the whole block's range
+            float xn = INFINITY, xx = -INFINITY;   // the whole block's range
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                bn = fminf(bn, pr[(2 * k) * ncr + r]);
-                bx = fmaxf(bx, pr[(2 * k + 1) * ncr + r]);
+                xn = fminf(xn, pr[(2 * k) * ncr + r]);
+                xx = fmaxf(xx, pr[(2 * k + 1) * ncr + r]);
             }
-            const float g = fmaxf(fabsf(yn[k] - bx), fabsf(yx[k] - bn));
+            const float g = fmaxf(fabsf(yn[k] - xx), fabsf(yx[k] - xn));
             if (NORM == RQA_NORM_LINF) a = fmaxf(a, g);
             else if (NORM == RQA_NORM_L1) a = a + g;
             else a = a + g * g;
         }
         full = __builtin_amdgcn_ballot_w64(worst <= thr && a <= thr);
     }
-}
-
-// ---------------------------------------------------------------------------
-// Column boxes.  Ordered keys of the non-NaN floats (unsigned order = float
-// order, -0 just below +0), used to bisect over float values.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t fkey(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float fval(uint32_t k) {
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
-}
-
-// Largest float h with fl(h - cmax) <= b (h = +inf when b = +inf).
-__device__ float box_hi(float cmax, float b) {
-    if (b == INFINITY) return INFINITY;
-    uint32_t t = fkey(-INFINITY), f = fkey(INFINITY);   // P(t) true, P(f) false
-    while (f - t > 1u) {
-        const uint32_t mid = t + (f - t) / 2u;
-        if (fval(mid) - cmax <= b) t = mid; else f = mid;
-    }
-    return fval(t);
-}
-
-// Smallest float l with fl(cmin - l) <= b (l = -inf when b = +inf).
-__device__ float box_lo(float cmin, float b) {
-    if (b == INFINITY) return -INFINITY;
-    uint32_t f = fkey(-INFINITY), t = fkey(INFINITY);   // Q(f) false, Q(t) true
-    while (t - f > 1u) {
-        const uint32_t mid = f + (t - f) / 2u;
-        if (cmin - fval(mid) <= b) t = mid; else f = mid;
-    }
-    return fval(t);
 }
 
 // ---------------------------------------------------------------------------
@@ -935,6 +887,10 @@ __device__ void flush_bins(const StripLds &L, const JobDesc &j) {
         const uint32_t v = t < L.capw ? L.bw[t] : 0u;
         if (v) { if (t <= j.hmax) g_add(j.hw + t, (unsigned long long)v); L.bw[t] = 0; }
     }
+}
+
+__device__ __forceinline__ Boxes boxes_of(const JobDesc &j) {
+    return Boxes{j.boxr, j.boxc, j.ncr, j.ncc, j.thr};
 }
 
 // One (strip, column segment) block of one job.  MODE kModeAuto: the upper
@@ -1148,7 +1104,7 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
                     full = 0ull;
                     kinds = 0u;
                 } else {
-                    classify<NORM, M>(j, rb, group, lane, act, full);
+                    classify<NORM, M>(boxes_of(j), rb, group, lane, act, full);
                     const uint32_t b = (uint32_t)((act >> (8 * (lane & 7))) & 0xFFull);
                     const uint32_t f = (uint32_t)((full >> (8 * (lane & 7))) & 0xFFull);
                     kinds = ((uint32_t)__builtin_amdgcn_ballot_w64(b == 0u) & 0xFFu) |
@@ -1470,7 +1426,7 @@ __device__ __forceinline__ bool use_boxes(const JobDesc &j, int item) {
 #pragma unroll 1
         for (int q = 0; q < 4; ++q) {
             uint64_t act, full;
-            classify<NORM, M>(j, R >> 6, (ca + (int)((int64_t)(cb - 1 - ca) * q / 3)) / kGroup, lane, act, full);
+            classify<NORM, M>(boxes_of(j), R >> 6, (ca + (int)((int64_t)(cb - 1 - ca) * q / 3)) / kGroup, lane, act, full);
             open += __builtin_popcountll(act & ~full);
         }
         return open < 240;
@@ -2234,43 +2190,23 @@ struct PlotDesc {
     float thr, thr0;
     int32_t row_tiles, col_tiles, chunks, cross;
     int32_t xchunks;           // column chunks per XCD: ceil(chunks / 8)
-    float *box;                // per column tile kBoxStride floats: (lo_k, hi_k), k < kBoxK
+    float *boxr, *boxc;        // boxes of the rows' and the columns' vectors (one series: the same)
+    int32_t ncr, ncc;          // entries per plane
     int32_t tail_len;
 };
 
 constexpr int kPlotChunk = 16;   // column tiles per wave
 
-// Column boxes of the plot's column tiles (the records k_box_bounds writes for
-// a job, for the plot's columns; always used: the test costs one scalar load
-// and a few compares per tile).
-__global__ void k_plot_boxes(const PlotDesc d) {
-    const int K = d.m < kBoxK ? d.m : kBoxK;
-    const int64_t total = (int64_t)d.col_tiles * K;
-    const float bnd = d.thr0;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(t % K);
-        const int64_t c = t / K;
-        const int64_t j0 = c * 64;
-        const int64_t j1 = j0 + 64 < d.nb ? j0 + 64 : d.nb;
-        float cmin = INFINITY, cmax = -INFINITY;
-        const float *col = d.b + (int64_t)k * d.tau;
-        for (int64_t q = j0; q < j1; ++q) {
-            const float v = col[q];
-            cmin = fminf(cmin, v);
-            cmax = fmaxf(cmax, v);
-        }
-        float *rec = d.box + c * kBoxStride;
-        rec[2 * k] = box_lo(cmin, bnd);
-        rec[2 * k + 1] = box_hi(cmax, bnd);
-    }
-}
-
-__global__ void k_plot_tail(const PlotDesc d) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// Boxes of the plot's vectors, and the coordinates of the last column tile.
+__global__ void k_plot_prepare(const PlotDesc d) {
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t base = (int64_t)(d.col_tiles - 1) * 64;
-    if (t < d.tail_len)
+    for (int64_t t = tid; t < d.tail_len; t += stride)
         const_cast<float *>(d.tail)[t] = base + t < d.nb_points ? d.b[base + t] : 0.0f;
+    if (d.boxc == nullptr) return;
+    make_boxes(d.boxc, d.ncc, d.b, d.nb, d.m, d.tau, tid, stride);
+    if (d.boxr != d.boxc) make_boxes(d.boxr, d.ncr, d.a, d.n, d.m, d.tau, tid, stride);
 }
 
 template <int NORM, int M>
@@ -2297,47 +2233,67 @@ __global__ void __launch_bounds__(256) k_plot(const PlotDesc d) {
     const int cend = cbeg + kPlotChunk < d.col_tiles ? cbeg + kPlotChunk : d.col_tiles;
     if (!d.cross && cbeg < r) cbeg = r;
     const int64_t band = d.theiler;
-    // A whole chunk: this lane's row words are written together at its end.
-    const bool whole = cbeg == cq && cend - cq == kPlotChunk;
-    uint64_t rowbuf[kPlotChunk];
-#pragma unroll
-    for (int u = 0; u < kPlotChunk; ++u) {
-        const int c = cq + u;
-        if (c < cbeg || c >= cend) continue;
-        const int jbase = c * 64;
-        const ConstF cols = to_const(c == d.col_tiles - 1 ? d.tail : d.b + jbase);
-        uint32_t xlo, xhi;
-        // The predicate path of the tile kernel: a tile that its column box
-        // rules out for every row is empty without evaluating a pair.
-        bool empty = false;
-        if constexpr (M > 0) empty = box_decides<M>(to_const(d.box) + (int64_t)c * kBoxStride, xr);
-        if (empty) xlo = xhi = 0u;
-        else tile_bits<NORM, M>(cols, d.tau, xr, rowp, d.m, d.thr, d.thr0, xlo, xhi);
-        uint64_t vm = 0ull;
-        if (i < n) {
-            const int hv = nb - jbase < 64 ? nb - jbase : 64;
-            vm = range_mask(0, (uint32_t)hv);
-            if (band > 0) {
-                int64_t blo = (int64_t)i - band + 1 - jbase, bhi = (int64_t)i + band - jbase;
-                blo = blo < 0 ? 0 : blo;
-                bhi = bhi > 64 ? 64 : bhi;
-                if (blo < bhi) vm &= ~range_mask((uint32_t)blo, (uint32_t)bhi);
+    // Row words go through LDS and out a group of tiles at a time, eight lanes to
+    // a row's 64 bytes.  (In registers, a chunk's 16 words took 32 of 122 VGPRs
+    // and an unrolled loop of 16 tiles: four waves per SIMD.)
+    __shared__ uint64_t words[4][64 * (kGroup + 1)];
+    uint64_t *const mine = words[threadIdx.x >> 6];
+#pragma unroll 1
+    for (int g = 0; g < kPlotChunk / kGroup; ++g) {
+        const int cg = cq + g * kGroup;
+        if (cg >= cend || cg + kGroup <= cbeg) continue;
+        // The tile kernel's classes: only the 8-column pieces that the boxes leave
+        // open are evaluated.
+        uint64_t act = ~0ull, full = 0ull;
+        if constexpr (M > 0)
+            classify<NORM, M>(Boxes{d.boxr, d.boxc, d.ncr, d.ncc, d.thr}, r, cg / kGroup, lane, act, full);
+        const int u1 = cend - cg < kGroup ? cend - cg : kGroup;
+#pragma unroll 1
+        for (int u = cbeg > cg ? cbeg - cg : 0; u < u1; ++u) {
+            const int c = cg + u;
+            const int jbase = c * 64;
+            const ConstF cols = to_const(c == d.col_tiles - 1 ? d.tail : d.b + jbase);
+            uint32_t xlo, xhi;
+            const uint32_t ones = (uint32_t)(full >> (8 * u)) & 0xFFu;
+            const uint32_t eval = (uint32_t)(act >> (8 * u)) & 0xFFu & ~ones;
+            if (eval == 0xFFu)
+                tile_bits<NORM, M>(cols, d.tau, xr, rowp, d.m, d.thr, d.thr0, xlo, xhi);
+            else
+                tile_bits_some<NORM, M>(cols, d.tau, xr, rowp, d.m, d.thr, d.thr0, eval, ones, xlo, xhi);
+            // Cells outside the matrix or inside the Theiler band are 0 (few
+            // tiles have any).
+            uint64_t vm = ~0ull;
+            if (!(R + 64 <= n && jbase + 64 <= nb &&
+                  ((int64_t)jbase - (R + 63) >= band || (int64_t)R - (jbase + 63) >= band))) {
+                vm = 0ull;
+                if (i < n) {
+                    const int hv = nb - jbase < 64 ? nb - jbase : 64;
+                    vm = range_mask(0, (uint32_t)hv);
+                    if (band > 0) {
+                        int64_t blo = (int64_t)i - band + 1 - jbase, bhi = (int64_t)i + band - jbase;
+                        blo = blo < 0 ? 0 : blo;
+                        bhi = bhi > 64 ? 64 : bhi;
+                        if (blo < bhi) vm &= ~range_mask((uint32_t)blo, (uint32_t)bhi);
+                    }
+                }
+            }
+            const uint64_t X = mk64(xlo, xhi) & vm;
+            mine[lane * (kGroup + 1) + u] = X;
+            if (!d.cross && c > r) {
+                uint32_t lo = (uint32_t)X, hi = (uint32_t)(X >> 32);
+                if (__builtin_amdgcn_ballot_w64(X != 0ull) != 0ull) transpose64(lo, hi, lane);
+                const int jr = jbase + lane;   // row of the mirror tile
+                if (jr < n) glb(d.bits)[(int64_t)jr * d.words + r] = mk64(lo, hi);
             }
         }
-        const uint64_t X = mk64(xlo, xhi) & vm;
-        if (whole) rowbuf[u] = X;
-        else if (i < n) d.bits[(int64_t)i * d.words + c] = X;
-        if (!d.cross && c > r) {
-            uint32_t lo = (uint32_t)X, hi = (uint32_t)(X >> 32);
-            transpose64(lo, hi, lane);
-            const int jr = jbase + lane;   // row of the mirror tile
-            if (jr < n) d.bits[(int64_t)jr * d.words + r] = mk64(lo, hi);
-        }
-    }
-    if (whole && i < n) {
-        uint64_t *dst = d.bits + (int64_t)i * d.words + cq;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own LDS
 #pragma unroll
-        for (int u = 0; u < kPlotChunk; ++u) dst[u] = rowbuf[u];
+        for (int it = 0; it < 8; ++it) {
+            const int row = it * 8 + (lane >> 3), c = cg + (lane & 7);
+            if (R + row < n && c >= cbeg && c < cend)
+                glb(d.bits)[(int64_t)(R + row) * d.words + c] = mine[row * (kGroup + 1) + (lane & 7)];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -2967,12 +2923,16 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? RQA_OK : RQA_EDEVICE;
 }
 
-// The last column tile's coordinates, then (32-byte aligned) the column boxes.
+// The last column tile's coordinates, then (256-byte aligned) the boxes.
 static int64_t plot_tail_floats(const KParams &kp) {
-    return (64 + (int64_t)(kp.m - 1) * kp.tau + 7) / 8 * 8;
+    return (64 + (int64_t)(kp.m - 1) * kp.tau + 63) / 64 * 64;
 }
-int64_t engine_plot_scratch_floats(const KParams &kp, int64_t nb) {
-    return plot_tail_floats(kp) + (nb + 63) / 64 * kBoxStride;
+static int64_t plot_box_entries(int64_t vecs) {   // whole groups of tiles
+    return ((vecs + 63) / 64 + kGroup - 1) / kGroup * kGroup * (64 / kBoxVecs);
+}
+int64_t engine_plot_scratch_floats(const KParams &kp, int64_t n, int64_t nb, bool cross) {
+    const int64_t entries = plot_box_entries(nb) + (cross ? plot_box_entries(n) : 0);
+    return plot_tail_floats(kp) + (kp.m <= kMaxM ? 2 * std::min(kp.m, kBoxK) * entries : 0);
 }
 
 int engine_plot(const KParams &kp, const float *a, int64_t na_points, const float *b,
@@ -2984,7 +2944,12 @@ int engine_plot(const KParams &kp, const float *a, int64_t na_points, const floa
     pd.a = a;
     pd.b = cross ? b : a;
     pd.tail = scratch;
-    pd.box = scratch + plot_tail_floats(kp);
+    if (kp.m <= kMaxM) {
+        pd.boxc = scratch + plot_tail_floats(kp);
+        pd.ncc = (int32_t)plot_box_entries(nb);
+        pd.boxr = cross ? pd.boxc + (int64_t)2 * std::min(kp.m, kBoxK) * pd.ncc : pd.boxc;
+        pd.ncr = cross ? (int32_t)plot_box_entries(n) : pd.ncc;
+    }
     pd.bits = bits;
     pd.words = words;
     pd.nb_points = cross ? nb_points : na_points;
@@ -3001,12 +2966,9 @@ int engine_plot(const KParams &kp, const float *a, int64_t na_points, const floa
     pd.xchunks = (pd.chunks + 7) / 8;
     pd.cross = cross ? 1 : 0;
     pd.tail_len = (int32_t)(64 + (int64_t)(kp.m - 1) * kp.tau);
-    hipLaunchKernelGGL(k_plot_tail, dim3((pd.tail_len + 255) / 256), dim3(256), 0, st, pd);
-    if (kp.m > 0) {
-        const int64_t box_threads = (int64_t)pd.col_tiles * std::min(kp.m, kBoxK);
-        const int box_grid = (int)std::min<int64_t>((box_threads + 255) / 256, 4096);
-        hipLaunchKernelGGL(k_plot_boxes, dim3(box_grid), dim3(256), 0, st, pd);
-    }
+    const int64_t entries = std::max<int64_t>((int64_t)std::min(kp.m, kBoxK) * (pd.ncc + pd.ncr), pd.tail_len);
+    hipLaunchKernelGGL(k_plot_prepare, dim3((unsigned)std::min<int64_t>((entries + 255) / 256, 4096)),
+                       dim3(256), 0, st, pd);
     PlotKernel kern = kp.norm == RQA_NORM_L1 ? pick_plot<RQA_NORM_L1>(kp.m)
                       : kp.norm == RQA_NORM_L2 ? pick_plot<RQA_NORM_L2>(kp.m)
                                                : pick_plot<RQA_NORM_LINF>(kp.m);
