@@ -178,8 +178,9 @@ struct rqa_handle {
     size_t info_block_off = 0;      // info records (flag + statistics) of all jobs
     size_t hist_block_off = 0;      // histograms of all jobs, contiguous
     size_t hist_block_bytes = 0;
-    char *info_cache = nullptr;     // pinned host copies
-    size_t info_cache_bytes = 0;
+    char *pub = nullptr;            // pinned: info records of all jobs, then (one short job)
+    size_t pub_bytes = 0;           // its histograms; written by the launch itself
+    bool pub_hist = false;          // the last run's histograms are there
     uint64_t *host_cache = nullptr;
     size_t host_cache_bytes = 0;
     bool info_valid = false;
@@ -325,9 +326,32 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
         }
         h->staging_bytes = stage;
     }
+    // Pinned host memory for the info records and a short job's histograms.  A
+    // run that has not been fetched may still write to it.
+    const bool pub_hist = count == 1 && hlen[0] <= kPublishEntries;
+    const size_t pub_need = kInfoBytes * static_cast<size_t>(count) +
+                            (pub_hist ? sizeof(uint64_t) * 3 * static_cast<size_t>(hlen[0]) : 0);
+    if (h->pub_bytes < pub_need) {
+        if (h->has_run) hipStreamSynchronize(h->stream);
+        drop_graph(h);
+        if (h->pub) hipHostFree(h->pub);
+        h->pub = nullptr;
+        h->pub_bytes = 0;
+        if (hipHostMalloc(reinterpret_cast<void **>(&h->pub), pub_need,
+                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            h->pub = nullptr;
+            return RQA_ENOMEM;
+        }
+        h->pub_bytes = pub_need;
+    }
     char *base = static_cast<char *>(h->ws.base);
     for (int32_t w = 0; w < count; ++w) {
         Job &jb = jobs[w];
+        jb.host_info = h->pub + kInfoBytes * static_cast<size_t>(w);
+        jb.host_hist = pub_hist ? h->pub + kInfoBytes : nullptr;
+        const int pending = 1 << 30;   // until the launch writes the record: no result
+        std::memcpy(jb.host_info, &pending, sizeof pending);
         jb.hist = reinterpret_cast<uint64_t *>(base + off[w]);
         jb.flag = reinterpret_cast<int *>(base + info_block_off + kInfoBytes * w);
         jb.scratch = base + soff[w];
@@ -338,6 +362,7 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
     sig = fnv(sig, &waves, sizeof waves);
     sig = fnv(sig, &h->groups, sizeof h->groups);
     sig = fnv(sig, &base, sizeof base);
+    sig = fnv(sig, &h->pub, sizeof h->pub);
     const bool plain = !h->profiling && !trial;
 
     h->last_from_graph = false;
@@ -371,6 +396,7 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
     h->hist_block_bytes = hist_block_bytes;
     h->info_valid = false;
     h->cache_valid = false;
+    h->pub_hist = pub_hist;
     h->stream = st;
     h->has_run = true;
     h->batched = batched;
@@ -494,19 +520,14 @@ int fetch(rqa_handle *h, int32_t index, rqa_measures *out, uint64_t *diag, uint6
         *have = need;
         return RQA_OK;
     };
-    const size_t info_bytes = kInfoBytes * h->nvec.size();
     if (!h->info_valid) {
-        // One copy of every job's flag and statistics.
-        int rc = grow(reinterpret_cast<void **>(&h->info_cache), &h->info_cache_bytes, info_bytes);
-        if (rc != RQA_OK) return rc;
-        if (hipMemcpyAsync(h->info_cache, static_cast<const char *>(h->ws.base) + h->info_block_off,
-                           info_bytes, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-            hipStreamSynchronize(h->stream) != hipSuccess)
-            return RQA_EDEVICE;
+        // Every job's flag and statistics are in host memory once the launch
+        // has passed.
+        if (hipStreamSynchronize(h->stream) != hipSuccess) return RQA_EDEVICE;
         finish_trial(h);
         h->info_valid = true;
     }
-    const char *info = h->info_cache + kInfoBytes * static_cast<size_t>(index);
+    const char *info = h->pub + kInfoBytes * static_cast<size_t>(index);
     int flag = 0;
     std::memcpy(&flag, info, sizeof(int));
     if (flag & 1) return RQA_ENONFINITE;
@@ -522,7 +543,7 @@ int fetch(rqa_handle *h, int32_t index, rqa_measures *out, uint64_t *diag, uint6
         for (int k = 0; k < 3; ++k)
             used[k] = std::min<int64_t>(hl, static_cast<int64_t>(st.longest[k]) + 1);
         const bool single = h->nvec.size() == 1;
-        if (!h->cache_valid) {
+        if (!h->cache_valid && !h->pub_hist) {
             int rc = grow(reinterpret_cast<void **>(&h->host_cache), &h->host_cache_bytes,
                           h->hist_block_bytes);
             if (rc != RQA_OK) return rc;
@@ -542,7 +563,9 @@ int fetch(rqa_handle *h, int32_t index, rqa_measures *out, uint64_t *diag, uint6
             h->cache_valid = true;
         }
         const uint64_t *hd = reinterpret_cast<const uint64_t *>(
-            reinterpret_cast<const char *>(h->host_cache) + (h->job_off[index] - h->hist_block_off));
+            h->pub_hist ? h->pub + kInfoBytes
+                        : reinterpret_cast<const char *>(h->host_cache) +
+                              (h->job_off[index] - h->hist_block_off));
         uint64_t *dst[3] = {diag, vert, white};
         for (int k = 0; k < 3; ++k) {
             if (!dst[k]) continue;
@@ -813,7 +836,7 @@ void rqa_destroy(rqa_handle *h) {
     drop_graph(h);
     if (h->capture_stream) hipStreamDestroy(h->capture_stream);
     if (h->host_cache) hipHostFree(h->host_cache);
-    if (h->info_cache) hipHostFree(h->info_cache);
+    if (h->pub) hipHostFree(h->pub);
     if (h->plot_done) {
         hipEventSynchronize(h->plot_done);
         hipEventDestroy(h->plot_done);

@@ -40,6 +40,10 @@ struct JobStats {
 // Bytes of the per-job info record: int flag at offset 0, JobStats at 8.
 constexpr size_t kInfoBytes = 256;
 static_assert(8 + sizeof(JobStats) <= kInfoBytes, "info record too small");
+// Histograms of up to this many entries go to host memory with the statistics
+// (they cross PCIe whether they are asked for or not: under 10 us); longer ones
+// are copied when they are.
+constexpr int64_t kPublishEntries = 16384;
 
 KParams make_kparams(const rqa_params &p);
 
@@ -66,6 +70,9 @@ struct Job {
     int *flag = nullptr;            // device info record (kInfoBytes): flag at 0, JobStats at 8
     void *scratch = nullptr;        // device: engine_job_scratch_bytes(*this) bytes
     void *stats = nullptr;          // device JobStats record (nullptr: at flag + 8)
+    void *host_info = nullptr;      // pinned host memory that receives the info record once the
+                                    // job is done (nullptr: none); kInfoBytes
+    void *host_hist = nullptr;      // the same for the three histograms, 3*hist_len() u64
     int64_t hist_stride = 0;        // entries from one histogram to the next (0: hist_len())
     KParams kp{};                   // parameters of this job
     int waves = 0;                  // waves per workgroup (strip height 64*waves), > 0

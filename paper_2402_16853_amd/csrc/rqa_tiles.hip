@@ -159,6 +159,8 @@ struct JobDesc {
     int32_t stat_blocks;       // blocks of the statistics kernels for this job
     uint8_t *nonfinite;        // kPrepareBlocks bytes: k_prepare block b saw a non-finite value
     uint32_t *stat_done;       // statistics blocks of this job that have finished
+    unsigned char *host_info;  // pinned host copy of the info record (nullptr: none)
+    unsigned long long *host_hist;   // pinned host copy of the histograms (nullptr: none)
     JobStats *stats;           // device statistics record
     double *ent_part;          // [3][kStatMaxBlocks] entropy partial sums
     float *boxr, *boxc;        // boxes of the rows' and the columns' vectors (one series:
@@ -2051,11 +2053,28 @@ __device__ __forceinline__ void block_sums(double (&v)[3], double (*red)[3]) {
     }
 }
 
-// Bit 0 of the flag: non-finite input.  Called by one whole wave.
-__device__ __forceinline__ void finish_flag(const JobDesc &j) {
+// Called by one whole wave once the statistics are complete: bit 0 of the flag
+// (non-finite input), and the info record's copy in pinned host memory, where a
+// result fetch finds it after one wait (a copy of its own, and a second wait
+// for the histograms, were ~40 us of a 2,000-point call).
+__device__ __forceinline__ void finish_job(const JobDesc &j, const double (&ent)[3]) {
     static_assert(kPrepareBlocks == 64, "one k_prepare block per lane");
-    if (__ballot(*glb(j.nonfinite + (threadIdx.x & 63)) != 0) != 0ull && (threadIdx.x & 63) == 0)
-        g_or(j.flag, 1);
+    const int lane = threadIdx.x & 63;
+    const int bad = __ballot(*glb(j.nonfinite + lane) != 0) != 0ull ? 1 : 0;
+    if (lane < 3) j.stats->ent[lane] = lane == 0 ? ent[0] : lane == 1 ? ent[1] : ent[2];
+    if (lane == 0 && bad) g_or(j.flag, 1);
+    if (j.host_info == nullptr) return;
+    constexpr int kMoments = offsetof(JobStats, ent) / 8;
+    auto *rec = reinterpret_cast<unsigned long long *>(j.host_info + 8);
+    const auto *st = reinterpret_cast<const unsigned long long *>(j.stats);
+    if (lane < kMoments)
+        *glb(rec + lane) = __hip_atomic_load(glb(st + lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else if (lane < kMoments + 3)
+        *glb(rec + lane) = (unsigned long long)__double_as_longlong(
+            lane == kMoments ? ent[0] : lane == kMoments + 1 ? ent[1] : ent[2]);
+    if (lane == 0)
+        *glb(reinterpret_cast<int *>(j.host_info)) =
+            bad | __hip_atomic_load(glb(j.flag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ void __launch_bounds__(kStatThreads) k_stats_moments(const JobDesc *__restrict__ jobs) {
@@ -2106,19 +2125,28 @@ __global__ void __launch_bounds__(kStatThreads) k_stats_moments(const JobDesc *_
         // JobStats: the five moments are rows of three u64, in the order above.
         static_assert(offsetof(JobStats, longest) == 12 * sizeof(uint64_t), "moment rows");
         unsigned long long *dst = reinterpret_cast<unsigned long long *>(j.stats) + q * 3 + h;
-        if (alone) *dst = r;
+        if (alone) __hip_atomic_store(glb(dst), r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else if (r && q < 4) atomicAdd(dst, r);
         else if (r) atomicMax(dst, r);
     }
     if (!alone) return;
+    if (j.host_hist != nullptr) {
+        const int64_t hl = (int64_t)j.hmax + 1;
+#pragma unroll
+        for (int h = 0; h < 3; ++h)
+#pragma unroll
+            for (int u = 0; u < kStatPer; ++u) {
+                const int64_t l = threadIdx.x + u * kStatThreads;
+                if (l < hl) glb(j.host_hist)[h * hl + l] = s.c[h][u];
+            }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the moments have left (finish_job reads them)
     __syncthreads();
     double e[3];
 #pragma unroll
     for (int h = 0; h < 3; ++h) e[h] = entropy_part(s.c[h], lo, j.mins[h], part[0][h * 5 + 2]);
     block_sums(e, red);
-    if (threadIdx.x == 0)
-        for (int h = 0; h < 3; ++h) j.stats->ent[h] = e[h];
-    if (threadIdx.x < 64) finish_flag(j);
+    if (threadIdx.x < 64) finish_job(j, e);
 }
 
 __global__ void __launch_bounds__(kStatThreads) k_stats_entropy(const JobDesc *__restrict__ jobs) {
@@ -2140,6 +2168,12 @@ __global__ void __launch_bounds__(kStatThreads) k_stats_entropy(const JobDesc *_
             const double p = (double)c / C;
             e[h] -= p * log(p);
         }
+    }
+    if (j.host_hist != nullptr) {
+        const int64_t hl = (int64_t)j.hmax + 1;
+        for (int h = 0; h < 3; ++h)
+            for (int64_t l = lo + threadIdx.x; l < hi; l += kStatThreads)
+                glb(j.host_hist)[h * hl + l] = *glb(hs[h] + l);
     }
     block_sums(e, red);
     if (threadIdx.x >= 64) return;
@@ -2167,9 +2201,8 @@ __global__ void __launch_bounds__(kStatThreads) k_stats_entropy(const JobDesc *_
                    : 0.0;
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) e[h] = e[h] + __shfl_xor(e[h], d, 64);
-        if (threadIdx.x == 0) j.stats->ent[h] = e[h];
     }
-    finish_flag(j);
+    finish_job(j, e);
 }
 
 // ---------------------------------------------------------------------------
@@ -2590,6 +2623,8 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
     d.stats = jb.stats ? reinterpret_cast<JobStats *>(jb.stats)
                        : reinterpret_cast<JobStats *>(reinterpret_cast<char *>(jb.flag) + 8);
     d.ent_part = reinterpret_cast<double *>(scr + lay.off_ent);
+    d.host_info = static_cast<unsigned char *>(jb.host_info);
+    d.host_hist = static_cast<unsigned long long *>(jb.host_hist);
     d.boxc = lay.box_floats > 0 ? reinterpret_cast<float *>(scr + lay.off_box) : nullptr;
     d.boxr = jb.mode == kModeAuto || !d.boxc
                  ? d.boxc : d.boxc + (int64_t)2 * std::min(kp.m, kBoxK) * lay.ncc;
