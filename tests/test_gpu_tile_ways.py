@@ -105,3 +105,28 @@ def test_batches_of_few_windows(cuda, oracle_lib, count):
             ref = oracle_lib.histograms(s[off[w]:off[w] + ln[w]], p.m, p.tau, p.eps, p.norm, p.theiler)
             check(comp.result_batch(w), ref, (count, run, w))
     comp.close()
+
+
+@pytest.mark.parametrize("rows", [0, 1, 2, 4, 5])
+@pytest.mark.parametrize("waves", [1, 8])
+def test_tiles_of_few_rows(cuda, oracle_lib, rows, waves):
+    """Tiles with a handful of non-zero rows (4 is the last that is gathered row by
+    row, 5 the first that is transposed), whole rows and scattered cells among them,
+    at both ends and on both sides of row 32."""
+    import torch
+    from paper_2402_16853_amd import RQA
+    n, nb = 600, 700
+    rng = np.random.default_rng(10 * rows + waves)
+    dense = np.zeros((n, 11 * 64), dtype=np.uint8)
+    for r0 in range(0, n, 64):
+        near = [r for r in (0, 31, 32, 63) if r0 + r < n]
+        pick = near[:rows] + list(rng.choice([r for r in range(1, min(31, n - r0))], max(0, rows - len(near)), False))
+        for r in pick:
+            dense[r0 + r, :nb] = rng.random(nb) < (1.0 if rng.random() < 0.3 else 0.2)
+    print(f"[case] few rows={rows} waves={waves}", flush=True)
+    bits = np.packbits(dense, axis=1, bitorder="little").view(np.int64)
+    comp = RQA.from_params(Params(m=1, tau=1, eps=0.0, norm=3, theiler=0))
+    comp.set_tiling(waves, 0)
+    res = comp.matrix(torch.from_numpy(bits).to(cuda), nb)
+    comp.close()
+    check(res, oracle_lib.matrix_histograms(bits.view(np.uint64), n, nb, 0), (rows, waves))
