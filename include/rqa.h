@@ -162,7 +162,7 @@ int rqa_run_matrix(rqa_handle *h, const uint64_t *d_bits, int64_t n_rows, int64_
  * be fed back to rqa_run_matrix.  Asynchronous on hip_stream; the caller keeps
  * d_series and d_bits alive until the stream has passed the call.  The handle
  * keeps a device scratch buffer for the plot (the last column tile's
- * coordinates and one 32-byte record per 64 columns); a plot with more
+ * coordinates and 64 min(m, 3) bytes of boxes per 64 vectors of each series); a plot with more
  * columns than any before on this handle grows it (hipMalloc, after the
  * previous plot has passed), RQA_ENOMEM if that fails.
  * RQA_ESIZE if words_per_row is too small, RQA_ETOOSHORT as rqa_run. */
@@ -206,10 +206,10 @@ int rqa_measures_from_hist(const uint64_t *diag, const uint64_t *vert,
                            rqa_measures *out);
 
 /* Tile-shape override: waves per workgroup (1..8, rows per strip = 64*waves;
- * 0 = chosen by the built-in autotuner, which times the candidate shapes 2, 4
- * and 8 waves on the first runs of each launch signature, the default shape
- * first; a shape more than 10% slower than the best so far ends the trials
- * beyond it; RQA_AUTOTUNE_CACHE=<file> persists its choices) and workgroups
+ * 0 = chosen by the built-in autotuner, which times the first three runs of
+ * each launch signature: the default shape, its neighbour (8 and 4 waves; below
+ * 4,096 delay vectors 4 and 2) and the default again;
+ * RQA_AUTOTUNE_CACHE=<file> persists its choices) and workgroups
  * per launch (0 = fill the device).  Results never depend on these. */
 int rqa_set_tiling(rqa_handle *h, int32_t waves_per_group, int32_t groups);
 
@@ -266,8 +266,8 @@ int rqa_workspace_plan(const rqa_params *p, int64_t n_points, int32_t waves, int
  * RQA as rqa_run + rqa_result of one device series under the parameters *p,
  * enqueued on hip_stream with no allocation at all (no hipMalloc, hipFree,
  * pinned host buffer or host-to-device copy): the kernels' scratch lies in a
- * static device array of RQA_STATIC_SCRATCH_BYTES that the library holds on
- * each GPU it runs on until the process ends.  That limit admits series of up
+ * static device array of RQA_STATIC_SCRATCH_BYTES and one MiB (boxes and masks)
+ * that the library holds on each GPU it runs on until the process ends.  It admits series of up
  * to about 92,000 delay vectors; a larger one returns RQA_EBUDGET.
  *   d_series: n_points FP32 values in device memory (caller-owned, alive and
  *             unmodified until the stream has passed the call);
