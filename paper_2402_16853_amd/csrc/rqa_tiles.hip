@@ -1669,6 +1669,11 @@ __device__ __forceinline__ uint32_t fold_diagonal(StitchLds &L, const JobDesc &j
     const int entry = (k >> 6) + j.kb_off;
     uint32_t wf = 0, wl = 0;                   // written bits of strip s's 32
     int have = -1;
+    // The segment of the next piece: the one after, where a piece has left at the
+    // right edge.  A division per piece stood before every load's address: stitch
+    // of a 65,521-point Lorenz series 72 -> 66 us, of the 262,144-point cross
+    // recurrence 537 -> 501.
+    int g = (ra + k - base) / W;
     while (s <= sb) {
         if ((s - j.s_lo) >> 5 != have) {
             have = (s - j.s_lo) >> 5;
@@ -1682,8 +1687,6 @@ __device__ __forceinline__ uint32_t fold_diagonal(StitchLds &L, const JobDesc &j
         for (int u = 0; u < kStitchBatch; ++u) {
             if (s <= sb && (s - j.s_lo) >> 5 == have) {
                 const uint32_t bit = 1u << ((s - j.s_lo) & 31);
-                const int ca = ra + k;
-                const int g = (ca - base) / W;
                 const int gend = base + (g + 1) * W - 1;                 // segment's last column
                 int rz = r1 < s * H + H - 1 ? r1 : s * H + H - 1;        // last row in the strip
                 const bool right = rz + k >= gend;                       // leaves at the right edge
@@ -1704,6 +1707,7 @@ __device__ __forceinline__ uint32_t fold_diagonal(StitchLds &L, const JobDesc &j
                 ln[u] = (uint32_t)(rz - ra + 1) | (last ? kLast : 0u) | (border ? kBorder : 0u);
                 count = u + 1;
                 ra = rz + 1;
+                g += right ? 1 : 0;
                 if (ra == (s + 1) * H || last) ++s;
                 if (last) s = sb + 1;
             }
