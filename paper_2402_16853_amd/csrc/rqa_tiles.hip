@@ -2261,7 +2261,7 @@ struct PlotDesc {
     int32_t tail_len;
 };
 
-constexpr int kPlotChunk = 16;   // column tiles per wave
+constexpr int kPlotChunk = 16;   // column tiles per wave: a 128-byte line of row words
 
 // Boxes of the plot's vectors, and the coordinates of the last column tile.
 __global__ void k_plot_prepare(const PlotDesc d) {
@@ -2299,10 +2299,12 @@ __global__ void __launch_bounds__(256) k_plot(const PlotDesc d) {
     const int cend = cbeg + kPlotChunk < d.col_tiles ? cbeg + kPlotChunk : d.col_tiles;
     if (!d.cross && cbeg < r) cbeg = r;
     const int64_t band = d.theiler;
-    // Row words go through LDS and out a group of tiles at a time, eight lanes to
-    // a row's 64 bytes.  (In registers, a chunk's 16 words took 32 of 122 VGPRs
-    // and an unrolled loop of 16 tiles: four waves per SIMD.)
-    __shared__ uint64_t words[4][64 * (kGroup + 1)];
+    // Row words go through LDS and out as a row's whole 128-byte line, 16 lanes to
+    // a row.  The 35 KB also keep a CU at 16 waves: with 64-byte halves and 28 waves
+    // the open lines of the mirror tiles outgrew the XCD's L2 where the boxes leave
+    // little to evaluate (60,001 points: sine 342 against 276 us, Lorenz, m = 4, L1,
+    // 372 against 295; noise, m = 6, gains from more waves: 546 against 624).
+    __shared__ uint64_t words[4][64 * (kPlotChunk + 1)];
     uint64_t *const mine = words[threadIdx.x >> 6];
 #pragma unroll 1
     for (int g = 0; g < kPlotChunk / kGroup; ++g) {
@@ -2344,7 +2346,7 @@ __global__ void __launch_bounds__(256) k_plot(const PlotDesc d) {
                 }
             }
             const uint64_t X = mk64(xlo, xhi) & vm;
-            mine[lane * (kGroup + 1) + u] = X;
+            mine[lane * (kPlotChunk + 1) + (c - cq)] = X;
             if (!d.cross && c > r) {
                 uint32_t lo = (uint32_t)X, hi = (uint32_t)(X >> 32);
                 if (__builtin_amdgcn_ballot_w64(X != 0ull) != 0ull) transpose64(lo, hi, lane);
@@ -2352,14 +2354,13 @@ __global__ void __launch_bounds__(256) k_plot(const PlotDesc d) {
                 if (jr < n) glb(d.bits)[(int64_t)jr * d.words + r] = mk64(lo, hi);
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own LDS
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int row = it * 8 + (lane >> 3), c = cg + (lane & 7);
-            if (R + row < n && c >= cbeg && c < cend)
-                glb(d.bits)[(int64_t)(R + row) * d.words + c] = mine[row * (kGroup + 1) + (lane & 7)];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own LDS
+#pragma unroll 8
+    for (int it = 0; it < kPlotChunk; ++it) {
+        const int row = it * 4 + (lane >> 4), c = cq + (lane & 15);
+        if (R + row < n && c >= cbeg && c < cend)
+            glb(d.bits)[(int64_t)(R + row) * d.words + c] = mine[row * (kPlotChunk + 1) + (lane & 15)];
     }
 }
 
