@@ -107,7 +107,14 @@ int rqa_hist_len(const rqa_handle *h, int64_t n_points, int64_t *len);
  * d_series: n_points contiguous FP32 values in device memory, owned by the
  * caller, who keeps it alive and unmodified until rqa_result returns.
  * Host-detectable errors return immediately; a non-finite series is flagged on
- * the device and reported by rqa_result. */
+ * the device and reported by rqa_result.  An error leaves the run before it to
+ * rqa_result, unless the workspace that held its histograms has gone
+ * (RQA_EDEVICE).
+ * A run writes its statistics, and histograms of up to 16,384 entries, to pinned
+ * host memory of the handle.  One that needs more than any before allocates it
+ * (256 bytes per window, 24 per histogram entry; hipHostMalloc, no wait; smaller
+ * blocks are kept until rqa_destroy); where that fails, or hip_stream is being
+ * captured, rqa_result copies the results from the device instead. */
 int rqa_run(rqa_handle *h, const float *d_series, int64_t n_points, void *hip_stream);
 
 /* Wait for the last rqa_run (or rqa_run_cross / rqa_run_matrix), copy its

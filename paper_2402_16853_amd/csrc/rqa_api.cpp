@@ -178,9 +178,22 @@ struct rqa_handle {
     size_t info_block_off = 0;      // info records (flag + statistics) of all jobs
     size_t hist_block_off = 0;      // histograms of all jobs, contiguous
     size_t hist_block_bytes = 0;
-    char *pub = nullptr;            // pinned: info records of all jobs, then (one short job)
-    size_t pub_bytes = 0;           // its histograms; written by the launch itself
-    bool pub_hist = false;          // the last run's histograms are there
+    bool on_device = false;         // ... of the last run are still in the workspace
+    // Pinned memory that a launch writes its info records to, and behind them (one
+    // short job) its histograms.  A block stays until the handle goes, also when a
+    // larger one has taken its place: an earlier run, or a graph that the caller
+    // captured, may still write to it.  Each is at least twice as large as the one
+    // before, so all of them are less than two of the last.
+    char *pub = nullptr;
+    size_t pub_bytes = 0;
+    char *pub_old[48] = {};
+    int pub_olds = 0;
+    char *rec = nullptr;            // the last run's records there (nullptr: none, they are copied)
+    bool rec_hist = false;          // and its histograms
+    uint32_t run = 0;               // number of the last run, which its records carry
+    uint32_t run_next = 1;
+    char *info_copy = nullptr;      // records copied from the device (rec == nullptr)
+    size_t info_copy_bytes = 0;
     uint64_t *host_cache = nullptr;
     size_t host_cache_bytes = 0;
     bool info_valid = false;
@@ -193,6 +206,7 @@ struct rqa_handle {
     // graph replay of repeated identical launches
     uint64_t last_sig = 0;
     uint64_t graph_sig = 0;
+    uint32_t graph_run = 0;         // number of the run that was captured
     hipGraphExec_t graph = nullptr;
     void *graph_staging = nullptr;
     hipStream_t capture_stream = nullptr;
@@ -220,6 +234,31 @@ int ensure_events(rqa_handle *h) {
             if (hipEventCreate(&e) != hipSuccess) return RQA_EDEVICE;
     }
     return RQA_OK;
+}
+
+// Pinned memory of at least `need` bytes for a launch on `st` to write its results
+// to, or nullptr: none to be had, or `st` is being captured, where no memory may
+// be allocated.  The results are then copied from the device when they are
+// fetched.
+char *result_block(rqa_handle *h, size_t need, hipStream_t st) {
+    if (h->pub_bytes >= need) return h->pub;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (cap != hipStreamCaptureStatusNone || h->pub_olds == 48) return nullptr;
+    const size_t size = std::max(need, 2 * h->pub_bytes);
+    void *p = nullptr;
+    if (hipHostMalloc(&p, size, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    std::memset(p, 0, size);   // no run is number 0: records that none has written
+    if (h->pub) h->pub_old[h->pub_olds++] = h->pub;
+    h->pub = static_cast<char *>(p);
+    h->pub_bytes = size;
+    return h->pub;
 }
 
 // Capture the launch of `jobs` into a graph (own staging buffer, own capture
@@ -256,14 +295,16 @@ int capture_graph(rqa_handle *h, const std::vector<Job> &jobs, char *base, uint6
         return RQA_EDEVICE;
     }
     h->graph_sig = sig;
+    h->graph_run = jobs[0].run;
     return RQA_OK;
 }
 
 // Lay out the workspace for `jobs` and enqueue them: [launch scratch][info
-// records of every job][histograms of every job][job scratch], so that a fetch
-// copies the small records in one go and the histograms, when asked for, in one
-// more.  `sig` identifies the launch apart from the workspace; an identical
-// repeat replays a captured graph.
+// records of every job][histograms of every job][job scratch].  The launch also
+// writes the records, and the histograms of one short job, to pinned memory; a
+// batch's histograms are copied, when asked for, in one go.  `sig` identifies the
+// launch apart from the workspace; an identical repeat replays a captured graph.
+// The handle goes on describing the run before until the launch has succeeded.
 int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const std::string &key,
            uint64_t sig, void *stream, bool batched) {
     const int32_t count = static_cast<int32_t>(jobs.size());
@@ -307,10 +348,14 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
         soff[w] = total;
         total += align256(engine_job_scratch_bytes(jobs[w]));
     }
-    void *old_base = h->ws.base;
+    const void *old_base = h->ws.base;
+    const size_t old_bytes = h->ws.bytes;
     int rc = h->ws.reserve(total);
+    if (h->ws.base != old_base || h->ws.bytes != old_bytes) {   // (also where the reserve has failed)
+        h->on_device = false;
+        drop_graph(h);
+    }
     if (rc != RQA_OK) return rc;
-    if (h->ws.base != old_base) drop_graph(h);
     const size_t stage = align256(engine_launch_scratch_bytes(count));
     if (!h->staging_free &&
         hipEventCreateWithFlags(&h->staging_free, hipEventDisableTiming) != hipSuccess)
@@ -326,43 +371,34 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
         }
         h->staging_bytes = stage;
     }
-    // Pinned host memory for the info records and a short job's histograms.  A
-    // run that has not been fetched may still write to it.
-    const bool pub_hist = count == 1 && hlen[0] <= kPublishEntries;
-    const size_t pub_need = kInfoBytes * static_cast<size_t>(count) +
-                            (pub_hist ? sizeof(uint64_t) * 3 * static_cast<size_t>(hlen[0]) : 0);
-    if (h->pub_bytes < pub_need) {
-        if (h->has_run) hipStreamSynchronize(h->stream);
-        drop_graph(h);
-        if (h->pub) hipHostFree(h->pub);
-        h->pub = nullptr;
-        h->pub_bytes = 0;
-        if (hipHostMalloc(reinterpret_cast<void **>(&h->pub), pub_need,
-                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-            (void)hipGetLastError();
-            h->pub = nullptr;
-            return RQA_ENOMEM;
-        }
-        h->pub_bytes = pub_need;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const size_t rec_bytes = kInfoBytes * static_cast<size_t>(count);
+    bool rec_hist = count == 1 && hlen[0] <= kPublishEntries;
+    char *rec = result_block(
+        h, rec_bytes + (rec_hist ? sizeof(uint64_t) * 3 * static_cast<size_t>(hlen[0]) : 0), st);
+    if (!rec && rec_hist) {
+        rec_hist = false;
+        rec = result_block(h, rec_bytes, st);
     }
+    uint32_t run = h->run_next++;
+    if (run == 0) run = h->run_next++;
     char *base = static_cast<char *>(h->ws.base);
     for (int32_t w = 0; w < count; ++w) {
         Job &jb = jobs[w];
-        jb.host_info = h->pub + kInfoBytes * static_cast<size_t>(w);
-        jb.host_hist = pub_hist ? h->pub + kInfoBytes : nullptr;
-        const int pending = 1 << 30;   // until the launch writes the record: no result
-        std::memcpy(jb.host_info, &pending, sizeof pending);
+        jb.host_info = rec ? rec + kInfoBytes * static_cast<size_t>(w) : nullptr;
+        jb.host_hist = rec_hist ? rec + rec_bytes : nullptr;
+        jb.run = run;
         jb.hist = reinterpret_cast<uint64_t *>(base + off[w]);
         jb.flag = reinterpret_cast<int *>(base + info_block_off + kInfoBytes * w);
         jb.scratch = base + soff[w];
     }
-    hipStream_t st = static_cast<hipStream_t>(stream);
 
     sig = fnv(sig, &h->p, sizeof h->p);
     sig = fnv(sig, &waves, sizeof waves);
     sig = fnv(sig, &h->groups, sizeof h->groups);
     sig = fnv(sig, &base, sizeof base);
-    sig = fnv(sig, &h->pub, sizeof h->pub);
+    sig = fnv(sig, &rec, sizeof rec);
+    sig = fnv(sig, &rec_hist, sizeof rec_hist);
     const bool plain = !h->profiling && !trial;
 
     h->last_from_graph = false;
@@ -370,16 +406,19 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
         if (hipGraphLaunch(h->graph, st) != hipSuccess) return RQA_EDEVICE;
         h->prof_valid = false;
         h->last_from_graph = true;
+        run = h->graph_run;
     } else if (plain && h->last_sig == sig && capture_graph(h, jobs, base, sig) == RQA_OK) {
         if (hipGraphLaunch(h->graph, st) != hipSuccess) return RQA_EDEVICE;
         h->prof_valid = false;
         h->last_from_graph = true;
+        run = h->graph_run;
     } else {
         const bool timed = h->profiling || trial;
         if (timed && (rc = ensure_events(h)) != RQA_OK) return rc;
         rc = engine_launch(jobs, base, h->staging, h->staging_free, h->groups, st,
                            timed ? &h->prof : nullptr);
         h->prof_valid = timed && rc == RQA_OK;
+        if (rc == RQA_EDEVICE) h->on_device = false;   // some of its kernels may have been enqueued
         if (rc != RQA_OK) return rc;
     }
     h->last_sig = sig;
@@ -396,7 +435,10 @@ int launch(rqa_handle *h, std::vector<Job> &jobs, int waves, bool trial, const s
     h->hist_block_bytes = hist_block_bytes;
     h->info_valid = false;
     h->cache_valid = false;
-    h->pub_hist = pub_hist;
+    h->on_device = true;
+    h->rec = rec;
+    h->rec_hist = rec_hist;
+    h->run = run;
     h->stream = st;
     h->has_run = true;
     h->batched = batched;
@@ -522,12 +564,32 @@ int fetch(rqa_handle *h, int32_t index, rqa_measures *out, uint64_t *diag, uint6
     };
     if (!h->info_valid) {
         // Every job's flag and statistics are in host memory once the launch
-        // has passed.
+        // has passed, or are copied there.
+        if (!h->rec) {
+            const size_t need = kInfoBytes * h->nvec.size();
+            if (h->info_copy_bytes < need) {
+                std::free(h->info_copy);
+                h->info_copy = static_cast<char *>(std::malloc(need));
+                h->info_copy_bytes = h->info_copy ? need : 0;
+                if (!h->info_copy) return RQA_ENOMEM;
+            }
+            if (!h->on_device ||
+                hipMemcpyAsync(h->info_copy, static_cast<const char *>(h->ws.base) + h->info_block_off,
+                               need, hipMemcpyDeviceToHost, h->stream) != hipSuccess)
+                return RQA_EDEVICE;
+        }
         if (hipStreamSynchronize(h->stream) != hipSuccess) return RQA_EDEVICE;
         finish_trial(h);
         h->info_valid = true;
     }
-    const char *info = h->pub + kInfoBytes * static_cast<size_t>(index);
+    const char *info = (h->rec ? h->rec : h->info_copy) + kInfoBytes * static_cast<size_t>(index);
+    if (h->rec) {
+        // Another number: this run's kernels did not run, or those of a later
+        // launch that failed have written over its record.
+        uint32_t run = 0;
+        std::memcpy(&run, info + 4, sizeof run);
+        if (run != h->run) return RQA_EDEVICE;
+    }
     int flag = 0;
     std::memcpy(&flag, info, sizeof(int));
     if (flag & 1) return RQA_ENONFINITE;
@@ -543,7 +605,8 @@ int fetch(rqa_handle *h, int32_t index, rqa_measures *out, uint64_t *diag, uint6
         for (int k = 0; k < 3; ++k)
             used[k] = std::min<int64_t>(hl, static_cast<int64_t>(st.longest[k]) + 1);
         const bool single = h->nvec.size() == 1;
-        if (!h->cache_valid && !h->pub_hist) {
+        if (!h->cache_valid && !h->rec_hist) {
+            if (!h->on_device) return RQA_EDEVICE;
             int rc = grow(reinterpret_cast<void **>(&h->host_cache), &h->host_cache_bytes,
                           h->hist_block_bytes);
             if (rc != RQA_OK) return rc;
@@ -563,7 +626,7 @@ int fetch(rqa_handle *h, int32_t index, rqa_measures *out, uint64_t *diag, uint6
             h->cache_valid = true;
         }
         const uint64_t *hd = reinterpret_cast<const uint64_t *>(
-            h->pub_hist ? h->pub + kInfoBytes
+            h->rec_hist ? h->rec + kInfoBytes
                         : reinterpret_cast<const char *>(h->host_cache) +
                               (h->job_off[index] - h->hist_block_off));
         uint64_t *dst[3] = {diag, vert, white};
@@ -837,6 +900,8 @@ void rqa_destroy(rqa_handle *h) {
     if (h->capture_stream) hipStreamDestroy(h->capture_stream);
     if (h->host_cache) hipHostFree(h->host_cache);
     if (h->pub) hipHostFree(h->pub);
+    for (int k = 0; k < h->pub_olds; ++k) hipHostFree(h->pub_old[k]);
+    std::free(h->info_copy);
     if (h->plot_done) {
         hipEventSynchronize(h->plot_done);
         hipEventDestroy(h->plot_done);

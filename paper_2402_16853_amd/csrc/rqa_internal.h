@@ -37,7 +37,8 @@ struct JobStats {
     double ent[3];          // -sum p ln p over lengths >= minimum, p = count / cnt_min
 };
 
-// Bytes of the per-job info record: int flag at offset 0, JobStats at 8.
+// Bytes of the per-job info record: int flag at offset 0, JobStats at 8; in host
+// memory the run's number at 4.
 constexpr size_t kInfoBytes = 256;
 static_assert(8 + sizeof(JobStats) <= kInfoBytes, "info record too small");
 // Histograms of up to this many entries go to host memory with the statistics
@@ -73,6 +74,7 @@ struct Job {
     void *host_info = nullptr;      // pinned host memory that receives the info record once the
                                     // job is done (nullptr: none); kInfoBytes
     void *host_hist = nullptr;      // the same for the three histograms, 3*hist_len() u64
+    uint32_t run = 0;               // number of the run, written with host_info (bytes 4..7)
     int64_t hist_stride = 0;        // entries from one histogram to the next (0: hist_len())
     KParams kp{};                   // parameters of this job
     int waves = 0;                  // waves per workgroup (strip height 64*waves), > 0

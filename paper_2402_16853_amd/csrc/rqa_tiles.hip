@@ -161,6 +161,7 @@ struct JobDesc {
     uint8_t *nonfinite;        // kPrepareBlocks bytes: k_prepare block b saw a non-finite value
     uint32_t *stat_done;       // statistics blocks of this job that have finished
     unsigned char *host_info;  // pinned host copy of the info record (nullptr: none)
+    uint32_t run;              // number of the run (Job::run)
     unsigned long long *host_hist;   // pinned host copy of the histograms (nullptr: none)
     JobStats *stats;           // device statistics record
     double *ent_part;          // [3][kStatMaxBlocks] entropy partial sums
@@ -2106,8 +2107,9 @@ __device__ __forceinline__ void finish_job(const JobDesc &j, const double (&ent)
         *glb(rec + lane) = (unsigned long long)__double_as_longlong(
             lane == kMoments ? ent[0] : lane == kMoments + 1 ? ent[1] : ent[2]);
     if (lane == 0)
-        *glb(reinterpret_cast<int *>(j.host_info)) =
-            bad | __hip_atomic_load(glb(j.flag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *glb(rec - 1) = mk64((uint32_t)(bad | __hip_atomic_load(glb(j.flag), __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT)),
+                             j.run);
 }
 
 __global__ void __launch_bounds__(kStatThreads) k_stats_moments(const JobDesc *__restrict__ jobs) {
@@ -2658,6 +2660,7 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
                        : reinterpret_cast<JobStats *>(reinterpret_cast<char *>(jb.flag) + 8);
     d.ent_part = reinterpret_cast<double *>(scr + lay.off_ent);
     d.host_info = static_cast<unsigned char *>(jb.host_info);
+    d.run = jb.run;
     d.host_hist = static_cast<unsigned long long *>(jb.host_hist);
     d.boxc = lay.box_floats > 0 ? reinterpret_cast<float *>(scr + lay.off_box) : nullptr;
     d.boxr = jb.mode == kModeAuto || !d.boxc

@@ -1,0 +1,69 @@
+"""Results that reach the host with the run itself, and those that are copied (GPU):
+histograms of 16,384 entries are the last that a run writes to pinned memory.  One
+handle goes over that edge, through batches whose records lie where a run's
+histograms were, over replayed graphs and runs that are never fetched, and each
+result is the oracle's, bit for bit; so is that of a run captured by the caller."""
+import numpy as np
+import pytest
+
+from workloads import Params
+
+pytestmark = pytest.mark.gpu
+
+P = Params(m=1, tau=1, eps=0.01, norm=3, theiler=1)
+
+
+def check(res, ref, tag):
+    for name, a, b in zip(("diag", "vert", "white"), (res.diag, res.vert, res.white), ref):
+        assert np.array_equal(a, b), f"{tag}: {name} differs at {np.nonzero(a != b)[0][:8]}"
+
+
+def test_published_and_copied_results_of_one_handle(cuda, oracle_lib):
+    import torch
+    from paper_2402_16853_amd import RQA
+    rng = np.random.default_rng(5)
+    s = rng.random(16_500).astype(np.float32)
+    ds = torch.from_numpy(s).to(cuda)
+    ref = {}
+
+    def oracle(o, n):
+        if (o, n) not in ref:
+            ref[o, n] = oracle_lib.histograms(s[o:o + n], P.m, P.tau, P.eps, P.norm, P.theiler)
+        return ref[o, n]
+
+    comp = RQA.from_params(P)
+    comp.set_tiling(4, 0)
+    off, ln = np.arange(9) * 50, 300 + 7 * np.arange(9)
+    for step, n in enumerate([100, 16_383, 16_384, 16_383, 0, 200, 200, 200, 0, 16_384, -150, 100, 0]):
+        print(f"[case] results step={step} n={n}", flush=True)
+        if n > 0:
+            check(comp(ds[:n]), oracle(0, n), (step, n))
+        elif n < 0:                                  # never fetched
+            comp.run(ds[:-n])
+        else:
+            comp.run_batch(ds, off, ln)
+            for w in (8, 0, 3):
+                check(comp.result_batch(w), oracle(int(off[w]), int(ln[w])), (step, w))
+    comp.close()
+
+
+@pytest.mark.parametrize("warm", [320, 20_000])
+def test_run_captured_by_the_caller(cuda, oracle_lib, warm):
+    """With pinned memory of an earlier run's size, and (the longer one) without."""
+    import torch
+    from paper_2402_16853_amd import RQA
+    rng = np.random.default_rng(warm)
+    a, b = (rng.random(300).astype(np.float32) for _ in range(2))
+    buf = torch.from_numpy(np.concatenate([a, rng.random(warm).astype(np.float32)])).to(cuda)
+    comp = RQA.from_params(P)
+    comp.set_tiling(4, 0)
+    comp(buf[:warm])
+    print(f"[case] captured run after {warm} points", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        comp.run(buf[:300])
+    buf[:300] = torch.from_numpy(b).to(cuda)
+    graph.replay()
+    torch.cuda.synchronize()
+    check(comp.result(), oracle_lib.histograms(b, P.m, P.tau, P.eps, P.norm, P.theiler), warm)
+    comp.close()
