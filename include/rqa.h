@@ -169,9 +169,11 @@ int rqa_run_matrix(rqa_handle *h, const uint64_t *d_bits, int64_t n_rows, int64_
  * be fed back to rqa_run_matrix.  Asynchronous on hip_stream; the caller keeps
  * d_series and d_bits alive until the stream has passed the call.  The handle
  * keeps a device scratch buffer for the plot (the last column tile's
- * coordinates and 64 min(m, 3) bytes of boxes per 64 vectors of each series); a plot with more
- * columns than any before on this handle grows it (hipMalloc, after the
- * previous plot has passed), RQA_ENOMEM if that fails.
+ * coordinates and, for m <= 6, 64 min(m, 3) bytes of boxes per 64 column vectors
+ * and, in a cross plot, per 64 row vectors too); a plot that needs more than any
+ * before on this handle grows it (hipMalloc, after the previous plot has passed),
+ * RQA_ENOMEM if that fails.  Under stream capture it is not grown for boxes: the
+ * plot then does without them.
  * RQA_ESIZE if words_per_row is too small, RQA_ETOOSHORT as rqa_run. */
 int rqa_plot(rqa_handle *h, const float *d_series, int64_t n_points, uint64_t *d_bits,
              int64_t words_per_row, void *hip_stream);

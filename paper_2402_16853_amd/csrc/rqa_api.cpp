@@ -729,7 +729,15 @@ int plot(rqa_handle *h, const float *a, int64_t na_points, const float *b, int64
     const size_t need = sizeof(float) * static_cast<size_t>(engine_plot_scratch_floats(kp, na, nb, b != nullptr));
     if (!h->plot_done && hipEventCreateWithFlags(&h->plot_done, hipEventDisableTiming) != hipSuccess)
         return RQA_EDEVICE;
-    if (h->plot_tail_bytes < need) {
+    bool boxes = true;
+    if (h->plot_tail_bytes < need && h->plot_tail_bytes >= sizeof(float) * engine_plot_tail_floats(kp)) {
+        // A plot that is being captured allocates nothing: without room for its
+        // boxes it evaluates every pair.
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        boxes = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        if (!boxes) (void)hipGetLastError();
+    }
+    if (boxes && h->plot_tail_bytes < need) {
         if (h->plot_tail) {
             hipEventSynchronize(h->plot_done);
             hipFree(h->plot_tail);
@@ -744,7 +752,7 @@ int plot(rqa_handle *h, const float *a, int64_t na_points, const float *b, int64
     } else if (hipStreamWaitEvent(st, h->plot_done, 0) != hipSuccess) {
         return RQA_EDEVICE;
     }
-    const int rc = engine_plot(kp, a, na_points, b, nb_points, d_bits, words, h->plot_tail, st);
+    const int rc = engine_plot(kp, a, na_points, b, nb_points, d_bits, words, h->plot_tail, boxes, st);
     if (rc != RQA_OK) return rc;
     return hipEventRecord(h->plot_done, st) == hipSuccess ? RQA_OK : RQA_EDEVICE;
 }

@@ -174,10 +174,12 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t stream);
 // matrix of a and b, bit-packed into `bits` (rows of `words` u64), on `stream`.
 // `scratch` holds engine_plot_scratch_floats(kp, n, nb, cross) device floats (the
 // last column tile's coordinates and the boxes of the exact pruning), n and nb
-// being the numbers of row and column vectors.
+// being the numbers of row and column vectors; without boxes (every pair is then
+// evaluated) engine_plot_tail_floats(kp) are enough.
+int64_t engine_plot_tail_floats(const KParams &kp);
 int64_t engine_plot_scratch_floats(const KParams &kp, int64_t n, int64_t nb, bool cross);
 int engine_plot(const KParams &kp, const float *a, int64_t na_points, const float *b,
-                int64_t nb_points, uint64_t *bits, int64_t words, float *scratch,
+                int64_t nb_points, uint64_t *bits, int64_t words, float *scratch, bool boxes,
                 hipStream_t stream);
 
 // Host FP64 measures from histograms of length n+1.

@@ -2316,7 +2316,8 @@ __global__ void __launch_bounds__(256) k_plot(const PlotDesc d) {
         // open are evaluated.
         uint64_t act = ~0ull, full = 0ull;
         if constexpr (M > 0)
-            classify<NORM, M>(Boxes{d.boxr, d.boxc, d.ncr, d.ncc, d.thr}, r, cg / kGroup, lane, act, full);
+            if (d.boxc != nullptr)
+                classify<NORM, M>(Boxes{d.boxr, d.boxc, d.ncr, d.ncc, d.thr}, r, cg / kGroup, lane, act, full);
         const int u1 = cend - cg < kGroup ? cend - cg : kGroup;
 #pragma unroll 1
         for (int u = cbeg > cg ? cbeg - cg : 0; u < u1; ++u) {
@@ -2996,7 +2997,7 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
 }
 
 // The last column tile's coordinates, then (256-byte aligned) the boxes.
-static int64_t plot_tail_floats(const KParams &kp) {
+int64_t engine_plot_tail_floats(const KParams &kp) {
     return (64 + (int64_t)(kp.m - 1) * kp.tau + 63) / 64 * 64;
 }
 static int64_t plot_box_entries(int64_t vecs) {   // whole groups of tiles
@@ -3004,11 +3005,12 @@ static int64_t plot_box_entries(int64_t vecs) {   // whole groups of tiles
 }
 int64_t engine_plot_scratch_floats(const KParams &kp, int64_t n, int64_t nb, bool cross) {
     const int64_t entries = plot_box_entries(nb) + (cross ? plot_box_entries(n) : 0);
-    return plot_tail_floats(kp) + (kp.m <= kMaxM ? 2 * std::min(kp.m, kBoxK) * entries : 0);
+    return engine_plot_tail_floats(kp) + (kp.m <= kMaxM ? 2 * std::min(kp.m, kBoxK) * entries : 0);
 }
 
 int engine_plot(const KParams &kp, const float *a, int64_t na_points, const float *b,
-                int64_t nb_points, uint64_t *bits, int64_t words, float *scratch, hipStream_t st) {
+                int64_t nb_points, uint64_t *bits, int64_t words, float *scratch, bool boxes,
+                hipStream_t st) {
     const int64_t d = (int64_t)(kp.m - 1) * kp.tau;
     const bool cross = b != nullptr;
     const int64_t n = na_points - d, nb = cross ? nb_points - d : n;
@@ -3016,8 +3018,8 @@ int engine_plot(const KParams &kp, const float *a, int64_t na_points, const floa
     pd.a = a;
     pd.b = cross ? b : a;
     pd.tail = scratch;
-    if (kp.m <= kMaxM) {
-        pd.boxc = scratch + plot_tail_floats(kp);
+    if (boxes && kp.m <= kMaxM) {
+        pd.boxc = scratch + engine_plot_tail_floats(kp);
         pd.ncc = (int32_t)plot_box_entries(nb);
         pd.boxr = cross ? pd.boxc + (int64_t)2 * std::min(kp.m, kBoxK) * pd.ncc : pd.boxc;
         pd.ncr = cross ? (int32_t)plot_box_entries(n) : pd.ncc;

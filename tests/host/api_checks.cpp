@@ -56,6 +56,7 @@ hipError_t hipDeviceSynchronize(void) {
 }
 hipError_t hipDeviceTotalMem(size_t *b, hipDevice_t) { *b = size_t(288) << 30; return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t n) {
+    CHECK(!any_capture());
     if (fail_malloc) return hipErrorOutOfMemory;
     *p = std::calloc(n, 1);
     return hipSuccess;
@@ -116,9 +117,13 @@ int engine_band_strips(const Job &, size_t) { return 0; }
 JobPlan engine_job_plan(const Job &) { return JobPlan{}; }
 void engine_batch_segs(std::vector<Job> &) {}
 int engine_default_waves(int64_t) { return 4; }
-int64_t engine_plot_scratch_floats(const KParams &, int64_t, int64_t, bool) { return 1; }
+int64_t engine_plot_tail_floats(const KParams &) { return 64; }
+int64_t engine_plot_scratch_floats(const KParams &, int64_t n, int64_t nb, bool cross) {
+    return 64 + nb + (cross ? n : 0);
+}
+static bool plot_boxes;
 int engine_plot(const KParams &, const float *, int64_t, const float *, int64_t, uint64_t *, int64_t,
-                float *, hipStream_t) { return RQA_OK; }
+                float *, bool boxes, hipStream_t) { plot_boxes = boxes; return RQA_OK; }
 int engine_launch(const std::vector<Job> &jobs, void *, void *, hipEvent_t, int, hipStream_t st,
                   const PhaseEvents *, AuxStreams *) {
     if (engine == kRefuses) return RQA_EINVAL;
@@ -297,6 +302,17 @@ int main() {
     fs(two)->capturing = false;
     CHECK(host_mallocs == before);
     expect(h, kShort);
+    rqa_destroy(h);
+
+    // Nor does a captured plot with more boxes than one before it: it has none.
+    h = handle();
+    uint64_t *bits = reinterpret_cast<uint64_t *>(4096);
+    CHECK(rqa_plot(h, kSeries, 640, bits, 10, one) == RQA_OK && plot_boxes);
+    fs(two)->capturing = true;
+    CHECK(rqa_plot_cross(h, kSeries, 5000, kSeries, 640, bits, 10, two) == RQA_OK && !plot_boxes);
+    CHECK(rqa_plot(h, kSeries, 600, bits, 10, two) == RQA_OK && plot_boxes);
+    fs(two)->capturing = false;
+    CHECK(rqa_plot_cross(h, kSeries, 5000, kSeries, 640, bits, 10, two) == RQA_OK && plot_boxes);
     rqa_destroy(h);
 
     CHECK(hipStreamDestroy(one) == hipSuccess && hipStreamDestroy(two) == hipSuccess);

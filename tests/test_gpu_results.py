@@ -67,3 +67,25 @@ def test_run_captured_by_the_caller(cuda, oracle_lib, warm):
     torch.cuda.synchronize()
     check(comp.result(), oracle_lib.histograms(b, P.m, P.tau, P.eps, P.norm, P.theiler), warm)
     comp.close()
+
+
+def test_plot_captured_by_the_caller(cuda, oracle_lib):
+    """A captured cross plot of more rows than any plot before has no room for its
+    rows' boxes, and may not allocate any."""
+    import torch
+    from paper_2402_16853_amd import RQA
+    rng = np.random.default_rng(8)
+    p = Params(m=2, tau=3, eps=0.3, norm=2, theiler=2)
+    a, b = (rng.random(k + 3).astype(np.float32) for k in (900, 333))
+    da, db = torch.from_numpy(a).to(cuda), torch.from_numpy(b).to(cuda)
+    comp = RQA.from_params(p)
+    comp.plot(db)
+    print("[case] captured cross plot", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = comp.plot(da, db)
+    captured.fill_(-1)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert np.array_equal(captured.cpu().numpy().view(np.uint64), oracle_lib.plot(a, p, b))
+    comp.close()
