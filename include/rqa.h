@@ -256,8 +256,10 @@ int rqa_set_workspace_limit(rqa_handle *h, int64_t bytes);
 
 /* How the last run was cut: row bands and strips per band (1 and all strips
  * when unbanded), column segments per strip, rows per strip, and the device
- * workspace of its first job's line summaries in bytes.  Any output pointer
- * may be NULL.  RQA_ESTATE before the first run. */
+ * workspace of its first job's line summaries in bytes (what rqa_set_workspace_limit
+ * bounds; on top come what prunes the work, at most 3 bytes per vector and 0.2% of
+ * the summaries, and a short run's narrow segments, at most 8 MiB or 4%).  Any
+ * output pointer may be NULL.  RQA_ESTATE before the first run. */
 int rqa_last_plan(const rqa_handle *h, int32_t *bands, int32_t *band_strips, int32_t *segs,
                   int32_t *strip_rows, int64_t *workspace_bytes);
 

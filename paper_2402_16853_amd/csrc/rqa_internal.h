@@ -108,14 +108,16 @@ struct Workspace {
 size_t engine_job_scratch_bytes(const Job &job);
 size_t engine_launch_scratch_bytes(size_t njobs);
 
-// Row bands for a job (auto mode) launched alone whose scratch would exceed
-// `limit` bytes: the largest number of strips per band whose scratch fits, at
+// Row bands for a job launched alone that would be charged more than `limit` bytes
+// (JobPlan::scratch_bytes): the largest number of strips per band that fits, at
 // least 1; 0 when the job fits in one band or `limit` is 0.  The job's waves
 // (strip height) must be set.
 int engine_band_strips(const Job &job, size_t limit);
 
 // How a launch of `job` alone is cut: row bands, strips per band, column
-// segments per strip, strip height, and the job's scratch bytes.
+// segments per strip, strip height, and the scratch bytes that limits and budgets
+// count (without the boxes of the exact pruning, the masks of what summaries were
+// written, and what a short run's narrow segments add).
 struct JobPlan {
     int bands, band_strips, segs, strip_rows;
     size_t scratch_bytes;

@@ -2435,6 +2435,7 @@ struct Layout {
     int64_t vmask_entries, dmask_entries;
     size_t off_tail, off_lead, off_vf, off_vl, off_df, off_dl, off_ent, off_nf, off_hf, off_hl, off_box,
         off_mask, off_cs, off_ds, bytes;
+    size_t charge;         // of these, what a limit or a budget counts (below)
 };
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -2532,7 +2533,8 @@ Layout layout_of(const Job &jb) {
         L.band = jb.band_strips > 0 && jb.band_strips < L.nstrips ? jb.band_strips : L.nstrips;
         L.nbands = (L.nstrips + L.band - 1) / L.band;
         const int T = (int)((nb - 1) / 64 + 1);
-        const int min_tiles = std::max(1, std::min(std::max(8, L.H / 64), T / kFineSegs));
+        const int wide = std::max(8, L.H / 64);
+        const int min_tiles = jb.fine ? std::max(1, std::min(wide, T / kFineSegs)) : wide;
         int segs = (int)std::min<int64_t>((kFullItems + L.band - 1) / L.band,
                                           std::max(1, T / min_tiles));
         segs = std::max(segs, 1);
@@ -2590,6 +2592,24 @@ Layout layout_of(const Job &jb) {
     L.off_cs = off; off += a256(sizeof(uint32_t) * ccarries);
     L.off_ds = off; off += a256(sizeof(uint32_t) * dcarries);
     L.bytes = off;
+    // Limits and budgets count the line summaries of strips cut no finer than into
+    // wide segments, the tail, the row leads (whether or not the segments hold them)
+    // and the carries, and 32 bytes per column tile where there can be boxes.  On top
+    // come the boxes and masks themselves (3 bytes per vector at most, and under 0.2%
+    // of the summaries) and what a short run's narrow segments add (8 MiB or 4%): a
+    // limit then cuts a run into the row bands that its wide cut needs, and no more.
+    // (Counted, they cut 2,000 points in 100 KiB into 8 bands: 272 us, one band 215
+    // with whole strips.)
+    if (jb.fine) {
+        Job wide = jb;
+        wide.fine = false;
+        L.charge = layout_of(wide).charge;
+        return L;
+    }
+    L.charge = off - a256(sizeof(float) * (size_t)L.box_floats) -
+               a256(sizeof(uint32_t) * (size_t)((L.vmask_entries + 2 * L.dmask_entries) * L.mask_words)) +
+               (jb.mode == kModeAuto ? a256(sizeof(uint32_t) * (size_t)n) - a256(sizeof(uint32_t) * (size_t)lead) : 0) +
+               (jb.mode != kModeMatrix && jb.kp.m <= kMaxM ? a256(sizeof(float) * (size_t)(64 + 8 * ctiles)) : 0);
     return L;
 }
 
@@ -2712,17 +2732,17 @@ int engine_band_strips(const Job &job, size_t limit) {
     Job jb = job;
     jb.band_strips = 0;
     const Layout all = layout_of(jb);
-    if (all.bytes <= limit || all.nstrips <= 1) return 0;
+    if (all.charge <= limit || all.nstrips <= 1) return 0;
     // The largest band whose scratch fits (the scratch grows with the band,
     // up to the jumps where the column segments per strip change).
     int lo = 1, hi = all.nstrips - 1;
     while (lo < hi) {
         const int mid = lo + (hi - lo + 1) / 2;
         jb.band_strips = mid;
-        if (layout_of(jb).bytes <= limit) lo = mid; else hi = mid - 1;
+        if (layout_of(jb).charge <= limit) lo = mid; else hi = mid - 1;
     }
     jb.band_strips = lo;
-    while (lo > 1 && layout_of(jb).bytes > limit) jb.band_strips = --lo;
+    while (lo > 1 && layout_of(jb).charge > limit) jb.band_strips = --lo;
     return lo;
 }
 
@@ -2733,7 +2753,7 @@ JobPlan engine_job_plan(const Job &job) {
     p.band_strips = lay.band;
     p.segs = lay.segs;
     p.strip_rows = lay.H;
-    p.scratch_bytes = lay.bytes;
+    p.scratch_bytes = lay.charge;
     return p;
 }
 
@@ -2948,17 +2968,9 @@ size_t engine_static_bytes(const Job &jb) {
     return engine_launch_scratch_bytes(1) + a256(kInfoBytes) + layout_of(jb).bytes;
 }
 
-// What the static scratch limit counts: all of it but the boxes and the masks,
-// whose room is set aside apart from the limit, and eight floats per column
-// tile in their place, so the series that fit are the ones that always did.
+// What the static scratch limit counts.
 size_t engine_static_charge(const Job &jb) {
-    const Layout lay = layout_of(jb);
-    const size_t own = a256(sizeof(float) * (size_t)lay.box_floats) +
-                       a256(sizeof(uint32_t) *
-                            (size_t)((lay.vmask_entries + 2 * lay.dmask_entries) * lay.mask_words));
-    const size_t tiles = (size_t)((jb.n_vec - 1) / 64 + 1);
-    return engine_static_bytes(jb) - own +
-           (jb.kp.m <= kMaxM ? a256(sizeof(float) * (64 + 8 * tiles)) : 0);
+    return engine_launch_scratch_bytes(1) + a256(kInfoBytes) + layout_of(jb).charge;
 }
 
 int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
