@@ -313,15 +313,17 @@ const char *rqa_strerror(int code);
  * ------------------------------------------------------------------------- */
 typedef struct rqa_server rqa_server;
 
-/* budget_bytes: device memory the server may hold for job workspaces;
- * streams: concurrent launch slots (1..16).  With two or more streams, the
+/* budget_bytes: device memory the server may hold for job workspaces (and
+ * budget_bytes/128 + 256 KiB more, where they can be had, for what a footprint does
+ * not count); streams: concurrent launch slots (1..16).  With two or more streams, the
  * first half runs large jobs (above 2e9 matrix cells, each launched alone)
  * and the second half batches of small ones, so small jobs never queue behind
  * a large one; with one stream everything shares it. */
 int rqa_server_create(rqa_server **out, size_t budget_bytes, int32_t streams);
 
-/* Device bytes of the server pool a job of n_points occupies while it runs
- * (histograms, flag and engine scratch; the series stays the caller's). */
+/* Device bytes a job of n_points takes of the server's budget while it runs
+ * (histograms, flag and engine scratch without what prunes the work; the series
+ * stays the caller's). */
 int rqa_job_footprint(const rqa_params *p, int64_t n_points, size_t *bytes);
 
 /* Submit a job.  d_series: n_points FP32 values in device memory, produced on

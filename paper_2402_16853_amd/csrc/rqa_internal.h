@@ -81,6 +81,7 @@ struct Job {
     int segs = 0;                   // auto mode: column segments per strip (0: the engine
                                     // decides, 1 for a job launched with others); scratch
                                     // is sized for the largest choice
+    bool boxes = true;              // classify tiles from boxes, where the job is large enough
     bool fine = false;              // a job launched alone: its chain of tiles may be cut into
                                     // segments narrower than 64 tiles (a handle's own run)
     int band_strips = 0;            // auto mode, a job launched alone: strips per row
@@ -107,6 +108,11 @@ struct Workspace {
 // descriptors and the work counter) of a launch over `njobs` jobs.
 size_t engine_job_scratch_bytes(const Job &job);
 size_t engine_launch_scratch_bytes(size_t njobs);
+
+// Scratch bytes of a job as a budget counts them (the server's, the static array's):
+// JobPlan::scratch_bytes of its default shape; engine_job_scratch_bytes may be
+// larger.
+size_t engine_budget_bytes(Job job);
 
 // Row bands for a job launched alone that would be charged more than `limit` bytes
 // (JobPlan::scratch_bytes): the largest number of strips per band that fits, at

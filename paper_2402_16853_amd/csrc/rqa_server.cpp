@@ -1,8 +1,8 @@
 // Served RQA: a request loop that admits independent jobs by device-memory
 // footprint and runs them with continuous batching.
 //
-// * The server owns one device pool of `budget` bytes, carved up by a
-//   first-fit allocator; a job is admitted (FIFO) when its footprint fits, so
+// * The server owns one device pool of `budget` bytes and a little more (below),
+//   carved up by a first-fit allocator; a job is admitted (FIFO) when its footprint fits, so
 //   no hipMalloc happens on the request path.
 // * A worker thread groups the jobs admitted since its last launch into one
 //   batched launch of the engine; jobs that arrive while earlier launches run
@@ -55,7 +55,8 @@ struct ServedJob {
     const float *series = nullptr;
     int64_t n_points = 0;
     int64_t n_vec = 0;
-    size_t footprint = 0;
+    size_t footprint = 0;          // pool bytes
+    bool boxes = true;
     size_t hist_bytes = 0;
     size_t off = 0;
     hipEvent_t ready = nullptr;    // recorded on the caller's stream at submit
@@ -79,6 +80,7 @@ struct rqa_server {
     int device = 0;
     char *pool_base = nullptr;
     size_t budget = 0;
+    size_t pool_size = 0;
     Pool pool;
     std::vector<hipStream_t> streams;
     std::vector<char *> launch_scratch;   // per stream, device
@@ -109,13 +111,24 @@ size_t job_hist_bytes(int64_t n_vec) {
     return align256(sizeof(uint64_t) * 3 * static_cast<size_t>(n_vec + 1));
 }
 
-size_t job_scratch_bytes(const rqa_params &p, int64_t n_points, int64_t n_vec) {
+Job engine_job(const rqa_params &p, int64_t n_points, int64_t n_vec) {
     Job one;
     one.n_points = n_points;
     one.n_vec = n_vec;
     one.kp = make_kparams(p);
     one.waves = engine_default_waves(n_vec);
-    return align256(engine_job_scratch_bytes(one));
+    return one;
+}
+
+// Pool bytes of a job besides its scratch.
+size_t job_fixed_bytes(int64_t n_vec) { return job_hist_bytes(n_vec) + kInfoBytes; }
+
+// The pool is larger than the budget by the boxes and masks of a job that takes all
+// of it (the masks are under 0.7% of a job; a job whose boxes do not fit goes
+// without).
+size_t pool_bytes(size_t budget) {
+    const size_t extra = align256(budget / 128 + (size_t(256) << 10));
+    return budget <= ~extra ? budget + extra : budget;
 }
 
 // Pinned buffer of at least `bytes` from the cache (lock held), or nullptr.
@@ -183,15 +196,12 @@ size_t admit_and_launch(rqa_server *srv, std::unique_lock<std::mutex> &lk) {
     for (ServedJob *j : batch) {
         if (hipStreamWaitEvent(st, j->ready, 0) != hipSuccess) rc = RQA_EDEVICE;
         char *base = srv->pool_base + j->off;
-        Job e;
+        Job e = engine_job(j->p, j->n_points, j->n_vec);
         e.series = j->series;
-        e.n_points = j->n_points;
-        e.n_vec = j->n_vec;
+        e.boxes = j->boxes;
         e.hist = reinterpret_cast<uint64_t *>(base);
         e.flag = reinterpret_cast<int *>(base + j->hist_bytes);
         e.scratch = base + j->hist_bytes + kInfoBytes;
-        e.kp = make_kparams(j->p);
-        e.waves = engine_default_waves(j->n_vec);
         ej.push_back(e);
     }
     if (rc == RQA_OK)
@@ -287,7 +297,7 @@ int rqa_job_footprint(const rqa_params *p, int64_t n_points, size_t *bytes) {
     if (rc != RQA_OK) return rc;
     const int64_t nv = n_points - static_cast<int64_t>(p->m - 1) * p->tau;
     if (nv < 1) return RQA_ETOOSHORT;
-    *bytes = job_hist_bytes(nv) + kInfoBytes + job_scratch_bytes(*p, n_points, nv);
+    *bytes = job_fixed_bytes(nv) + align256(engine_budget_bytes(engine_job(*p, n_points, nv)));
     return RQA_OK;
 }
 
@@ -300,13 +310,18 @@ int rqa_server_create(rqa_server **out, size_t budget_bytes, int32_t streams) {
             hipSuccess)
         return RQA_EDEVICE;
     void *base = nullptr;
-    if (hipMalloc(&base, budget_bytes) != hipSuccess) {
+    srv->pool_size = pool_bytes(budget_bytes);
+    if (hipMalloc(&base, srv->pool_size) != hipSuccess) {
         (void)hipGetLastError();
-        return RQA_ENOMEM;
+        srv->pool_size = budget_bytes;
+        if (hipMalloc(&base, budget_bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return RQA_ENOMEM;
+        }
     }
     srv->pool_base = static_cast<char *>(base);
     srv->budget = budget_bytes;
-    srv->pool.reset(budget_bytes);
+    srv->pool.reset(srv->pool_size);
     const size_t ls = align256(engine_launch_scratch_bytes(kMaxBatch));
     bool ok = true;
     for (int32_t k = 0; k < streams && ok; ++k) {
@@ -345,13 +360,22 @@ int rqa_submit(rqa_server *srv, const rqa_params *p, const float *d_series, int6
     int rc = rqa_job_footprint(p, n_points, &fp);
     if (rc != RQA_OK) return rc;
     if (fp > srv->budget) return RQA_EBUDGET;
+    const int64_t n_vec = n_points - static_cast<int64_t>(p->m - 1) * p->tau;
+    Job one = engine_job(*p, n_points, n_vec);
+    fp = job_fixed_bytes(n_vec) + align256(engine_job_scratch_bytes(one));
+    if (fp > srv->pool_size) {
+        one.boxes = false;
+        fp = job_fixed_bytes(n_vec) + align256(engine_job_scratch_bytes(one));
+        if (fp > srv->pool_size) return RQA_EBUDGET;   // (a pool of no more than the budget)
+    }
     ServedJob *j = new (std::nothrow) ServedJob;
     if (!j) return RQA_ENOMEM;
     j->p = *p;
     j->series = d_series;
     j->n_points = n_points;
-    j->n_vec = n_points - static_cast<int64_t>(p->m - 1) * p->tau;
+    j->n_vec = n_vec;
     j->footprint = fp;
+    j->boxes = one.boxes;
     j->hist_bytes = job_hist_bytes(j->n_vec);
     const size_t need = sizeof(uint64_t) * (3 * static_cast<size_t>(j->n_vec + 1) + kInfoWords);
     {

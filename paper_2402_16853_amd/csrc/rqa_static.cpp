@@ -2,7 +2,8 @@
 // kind.  Every byte of device scratch the kernels need (launch descriptors,
 // work counters, the statistics record, the tail copy, the row-lead records,
 // the strip-edge summaries and their masks, the boxes) lies in one file-scope
-// device array of RQA_STATIC_SCRATCH_BYTES and a MiB, which each GPU the library runs on holds until the
+// device array of RQA_STATIC_SCRATCH_BYTES and a MiB (the masks and boxes, which
+// RQA_EBUDGET does not count), which each GPU the library runs on holds until the
 // process ends; the caller passes the series and the output histograms and
 // flag.  Calls that overlap on one GPU share the array and race.
 #include <hip/hip_runtime.h>
@@ -68,9 +69,12 @@ extern "C" int rqa_run_static(const rqa_params *p, const float *d_series, int64_
     jb.hist = d_hist;
     jb.hist_stride = hist_len;
     jb.flag = reinterpret_cast<int *>(d_flag);
-    if (engine_static_charge(jb) > RQA_STATIC_SCRATCH_BYTES ||
-        engine_static_bytes(jb) > RQA_STATIC_SCRATCH_BYTES + kStaticExtraBytes)
-        return RQA_EBUDGET;
+    if (engine_static_charge(jb) > RQA_STATIC_SCRATCH_BYTES) return RQA_EBUDGET;
+    // A series of millions of vectors under a Theiler window almost as long has no
+    // room for boxes, nor a use for them.
+    constexpr size_t room = RQA_STATIC_SCRATCH_BYTES + kStaticExtraBytes;
+    if (engine_static_bytes(jb) > room) jb.boxes = false;
+    if (engine_static_bytes(jb) > room) return RQA_EBUDGET;
     void *base = nullptr;
     rc = scratch_on_current_device(&base);
     if (rc != RQA_OK) return rc;

@@ -169,7 +169,7 @@ struct JobDesc {
                                // the same), nullptr if none
     int32_t ncr, ncc;          // entries per plane
     uint32_t *vmask;           // which summaries were written (process_strip): per column
-    uint32_t *dfmask;          // tile, and per block of 64 diagonals at a strip's top edge and
+    uint32_t *dfmask;          // tile from seg_base on, and per block of 64 diagonals at a strip's top edge and
     uint32_t *dlmask;          // at its bottom edge, a bit per strip of the row band
     int32_t mask_words;        // words per tile or block
     int32_t kb_off;            // entry of diagonal block 0
@@ -1097,7 +1097,7 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
         };
         if (wave == 0) put(1, j.dfmask, e - rb + j.kb_off);
         if (bottom) {
-            put(0, j.vmask, e);
+            put(0, j.vmask, e - j.seg_base);
             put(2, j.dlmask, e - rb - 1 + j.kb_off);
         }
     };
@@ -1835,7 +1835,8 @@ __device__ __forceinline__ void stitch_auto(StitchLds &L, const JobDesc &j, int6
         // ---- column col of the full matrix ----
         const int col = (int)((int64_t)s_lo * H + line);
         const int s_last = col >= wp ? (col - wp) / H : -1;   // strips holding column col of U
-        uint32_t w = 0, wn = written32(j, j.vmask, col >> 6, s_lo);
+        const int entry = (col >> 6) > j.seg_base ? (col >> 6) - j.seg_base : 0;   // (below: no strips)
+        uint32_t w = 0, wn = written32(j, j.vmask, entry, s_lo);
         const int tile = __builtin_amdgcn_readfirstlane(col);   // the wave's first column
         const bool has_row = col + wp <= n - 1;               // row col of U has cells
         const int js = has_row ? col / H : (s_last > 0 ? s_last : 0);
@@ -1853,7 +1854,7 @@ __device__ __forceinline__ void stitch_auto(StitchLds &L, const JobDesc &j, int6
             uint32_t fv[kStitchBatch], lv[kStitchBatch];
             if (((s0 - s_lo) & 31) == 0) {   // the next word is loaded one ahead
                 w = (uint32_t)__builtin_amdgcn_readfirstlane((int)wn);   // (one tile per wave)
-                wn = written32(j, j.vmask, col >> 6, s0 + 32);
+                wn = written32(j, j.vmask, entry, s0 + 32);
             }
 #pragma unroll
             for (int u = 0; u < kStitchBatch; ++u) {
@@ -2570,7 +2571,7 @@ Layout layout_of(const Job &jb) {
     // row coordinates live in registers.
     const int64_t ncols = jb.mode == kModeAuto ? n : jb.n_cols;
     const int64_t ctiles = (ncols - 1) / 64 + 1;
-    if (jb.mode != kModeMatrix && jb.kp.m <= kMaxM && ctiles >= kBoxMinTiles) {
+    if (jb.boxes && jb.mode != kModeMatrix && jb.kp.m <= kMaxM && ctiles >= kBoxMinTiles) {
         L.ncc = (int)((ctiles + kGroup - 1) / kGroup * kGroup * (64 / kBoxVecs));
         L.ncr = jb.mode == kModeAuto ? L.ncc : (int)(((n - 1) / 64 + 1) * (64 / kBoxVecs));
         L.box_floats = 2 * std::min(jb.kp.m, kBoxK) *
@@ -2580,8 +2581,9 @@ Layout layout_of(const Job &jb) {
     // Masks of what summaries were written: a bit per strip of the band, for
     // every column tile and (twice) every block of 64 diagonals.
     L.mask_words = (L.band + 31) / 32;
-    L.vmask_entries = ctiles;
-    L.dmask_entries = ctiles + 1 + (jb.mode == kModeAuto ? 0 : (n - 1) / 64 + 1);
+    // (Auto mode: from the first with a cell outside the Theiler window.)
+    L.vmask_entries = std::max<int64_t>(1, ctiles - L.seg_base);
+    L.dmask_entries = L.vmask_entries + 1 + (jb.mode == kModeAuto ? 0 : (n - 1) / 64 + 1);
     L.off_mask = off;
     off += a256(sizeof(uint32_t) * (size_t)((L.vmask_entries + 2 * L.dmask_entries) * L.mask_words));
     // Per-line carries between bands: the open run of each column (of U in
@@ -2693,7 +2695,7 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
     d.dfmask = d.vmask + lay.vmask_entries * lay.mask_words;
     d.dlmask = d.dfmask + lay.dmask_entries * lay.mask_words;
     d.mask_total = (lay.vmask_entries + 2 * lay.dmask_entries) * lay.mask_words;
-    d.kb_off = 1 + (full ? (int32_t)((jb.n_vec - 1) / 64 + 1) : 0);
+    d.kb_off = 1 + (full ? (int32_t)((jb.n_vec - 1) / 64 + 1) : -lay.seg_base);
     // Fault injection for tests of the give-up path: with
     // RQA_DEBUG_WAIT_GIVEUP=1 in the environment every neighbour wait of the
     // tile kernel aims at a count no wave reaches and gives up after 64
@@ -2744,6 +2746,13 @@ int engine_band_strips(const Job &job, size_t limit) {
     jb.band_strips = lo;
     while (lo > 1 && layout_of(jb).charge > limit) jb.band_strips = --lo;
     return lo;
+}
+
+// With strips of 8 waves from 32,768 vectors on, and of 4 below: what a budget
+// admits does not follow the default shape.
+size_t engine_budget_bytes(Job jb) {
+    jb.waves = jb.n_vec >= 32768 ? 8 : 4;
+    return layout_of(jb).charge;
 }
 
 JobPlan engine_job_plan(const Job &job) {
@@ -2968,9 +2977,9 @@ size_t engine_static_bytes(const Job &jb) {
     return engine_launch_scratch_bytes(1) + a256(kInfoBytes) + layout_of(jb).bytes;
 }
 
-// What the static scratch limit counts.
+static_assert(sizeof(JobDesc) <= 512, "counted in what rqa_run_static admits");
 size_t engine_static_charge(const Job &jb) {
-    return engine_launch_scratch_bytes(1) + a256(kInfoBytes) + layout_of(jb).charge;
+    return engine_launch_scratch_bytes(1) + a256(kInfoBytes) + engine_budget_bytes(jb);
 }
 
 int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
