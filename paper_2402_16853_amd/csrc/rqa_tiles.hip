@@ -106,7 +106,8 @@ constexpr int kStatThreads = 256;
 constexpr int kStatMaxBlocks = 60;
 constexpr int kStatLengths = 2048;   // lengths per statistics block (8 per thread: the blocks'
                                      // loops are chains of dependent loads)
-constexpr int kPrepareBlocks = 64;   // k_prepare blocks per job
+constexpr int kPrepareBlocks = 64;   // k_prepare blocks per job, at most
+constexpr int kPrepareThreads = 256;
 constexpr int kCounters = 64;        // work counters of a launch
 // Boxes (exact pruning of the predicate, see classify): of every kBoxVecs
 // consecutive delay vectors the smallest and the largest of each of the first
@@ -116,6 +117,8 @@ constexpr int kCounters = 64;        // work counters of a launch
 constexpr int kBoxK = 3;
 constexpr int kBoxVecs = 8;
 constexpr int kBoxMinTiles = 128;
+constexpr int kBoxHeader = 64;       // floats before the first plane: the samples' counts
+constexpr int kSamples = 32;         // pieces sampled per k_prepare block (see sample_piece)
 
 // Device-side description of one job (one series or window).
 struct JobDesc {
@@ -168,6 +171,9 @@ struct JobDesc {
     float *boxr, *boxc;        // boxes of the rows' and the columns' vectors (one series:
                                // the same), nullptr if none
     int32_t ncr, ncc;          // entries per plane
+    uint8_t *decided;          // kPrepareBlocks bytes: of k_prepare block b's kSamples pieces, those
+                               // that boxes decide (blocks from sample_blocks on sample none)
+    int32_t sample_blocks;
     uint32_t *vmask;           // which summaries were written (process_strip): per column
     uint32_t *dfmask;          // tile from seg_base on, and per block of 64 diagonals at a strip's top edge and
     uint32_t *dlmask;          // at its bottom edge, a bit per strip of the row band
@@ -736,7 +742,7 @@ __device__ __forceinline__ void classify(const Boxes &bx, int rb, int cg, int la
 // ---------------------------------------------------------------------------
 // Kernel 1: per-job preparation -- zero the histograms, the statistics and the
 // flag, reset the work counters, look for non-finite input, build the
-// zero-padded tail of the last column tile.  grid = (kPrepareBlocks, jobs).
+// zero-padded tail of the last column tile.  grid = (prepare_blocks, jobs).
 // Non-finite input is noted per block (a plain store: the flag itself is being
 // cleared by block 0 of this kernel) and enters the flag in the statistics.
 // ---------------------------------------------------------------------------
@@ -762,6 +768,53 @@ __device__ __forceinline__ void make_boxes(float *box, int entries, const float 
         glb(box)[(int64_t)(2 * k) * entries + q] = lo;
         glb(box)[(int64_t)(2 * k + 1) * entries + q] = hi;
     }
+}
+
+// Whether boxes decide a sampled piece (64 rows by 8 columns), as classify would
+// say: eight lanes, one per box of 8 rows, from the series itself (the boxes are
+// being made).  A fixed sequence of places, even over the triangle or the matrix.
+// All lanes of the group return the answer.
+__device__ __forceinline__ bool sample_piece(const JobDesc &j, uint32_t piece) {
+    const int rblocks = j.n / 64, cblocks = j.nb / kBoxVecs;   // (whole ones: jobs with boxes have some)
+    if (rblocks == 0 || cblocks == 0) return false;
+    // Halves of a 64-bit mix of the piece's number (splitmix64's finaliser).
+    uint64_t h = (piece + 1ull) * 0x9E3779B97F4A7C15ull;
+    h = (h ^ (h >> 30)) * 0xBF58476D1CE4E5B9ull;
+    h = (h ^ (h >> 27)) * 0x94D049BB133111EBull;
+    h ^= h >> 31;
+    int rb = (int)(((h >> 32) * (uint64_t)rblocks) >> 32);
+    int cq = (int)(((h & 0xFFFFFFFFull) * (uint64_t)cblocks) >> 32);
+    if (j.mode == kModeAuto && cq < 8 * rb) {   // mirrored into the upper triangle
+        const int r = cq / 8;
+        cq = 8 * rb + (cq & 7);
+        rb = r;
+    }
+    const int K = j.m < kBoxK ? j.m : kBoxK;
+    const int64_t row = (int64_t)rb * 64 + (threadIdx.x & 7) * kBoxVecs, col = (int64_t)cq * kBoxVecs;
+    float least = 0.0f, most = 0.0f;
+    for (int k = 0; k < K; ++k) {
+        const auto x = glb(j.s) + row + (int64_t)k * j.tau, y = glb(j.sb) + col + (int64_t)k * j.tau;
+        float xn = INFINITY, xx = -INFINITY, yn = INFINITY, yx = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < kBoxVecs; ++u) {
+            xn = fminf(xn, x[u]);
+            xx = fmaxf(xx, x[u]);
+            yn = fminf(yn, y[u]);
+            yx = fmaxf(yx, y[u]);
+        }
+        const float a = fmaxf(fmaxf(yn - xx, xn - yx), 0.0f), b = fmaxf(fabsf(yn - xx), fabsf(yx - xn));
+        if (j.norm == RQA_NORM_LINF) {
+            least = fmaxf(least, a);
+            most = fmaxf(most, b);
+        } else {
+            least += j.norm == RQA_NORM_L1 ? a : a * a;
+            most += j.norm == RQA_NORM_L1 ? b : b * b;
+        }
+    }
+    const uint64_t group = 0xFFull << (threadIdx.x & 56);
+    const uint64_t open = __builtin_amdgcn_ballot_w64(least <= j.thr) & group;
+    const uint64_t full = __builtin_amdgcn_ballot_w64(j.m <= kBoxK && most <= j.thr) & group;
+    return open == 0ull || full == group;
 }
 
 __device__ __forceinline__ void prepare_job(const JobDesc &j, int *counters) {
@@ -795,9 +848,19 @@ __device__ __forceinline__ void prepare_job(const JobDesc &j, int *counters) {
     if (j.boxc != nullptr) {
         make_boxes(j.boxc, j.ncc, j.sb, j.nb, j.m, j.tau, tid, stride);
         if (j.boxr != j.boxc) make_boxes(j.boxr, j.ncr, j.s, j.n, j.m, j.tau, tid, stride);
+        int count = 0;
+        if ((int)blockIdx.x < j.sample_blocks) {
+            const bool yes = sample_piece(j, blockIdx.x * kSamples + threadIdx.x / 8);
+            count = __syncthreads_count(yes && (threadIdx.x & 7) == 0 ? 1 : 0);
+        }
+        if (threadIdx.x == 0) j.decided[blockIdx.x] = (uint8_t)count;
     }
     const int any = __syncthreads_or(bad ? 1 : 0);
     if (threadIdx.x == 0) j.nonfinite[blockIdx.x] = any ? 1 : 0;
+    if (blockIdx.x == 0 && threadIdx.x >= gridDim.x && threadIdx.x < kPrepareBlocks) {   // no such blocks
+        j.nonfinite[threadIdx.x] = 0;
+        if (j.boxc != nullptr) j.decided[threadIdx.x] = 0;
+    }
 }
 
 __global__ void k_prepare(const JobDesc *__restrict__ jobs, int *counters) {
@@ -1433,34 +1496,22 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
     }
 }
 
-// Whether a wave classifies the tiles of its part of a block: four groups of it,
-// spread over its tiles, are tried, and where the boxes decide less than a
-// sixteenth of their chunks (noise), none is.  Every wave decides for itself:
-// only speed depends on it.  (With the classes in its code the L1, m = 5 kernel
-// ran 4.5% slower on uniform noise, 9.52 -> 9.96 ms for the 400 windows.)
-template <int NORM, int M, int MODE>
-__device__ __forceinline__ bool use_boxes(const JobDesc &j, int item) {
+// Whether the tiles of a job are classified: where the boxes decide a sixteenth of
+// its sampled pieces (noise: none, or nearly).  With the classes in its code the L1,
+// m = 5 kernel ran 4.5% slower on uniform noise (400 windows 9.52 -> 9.96 ms).  For
+// each wave to try four groups of its part cost two to four memory latencies an item:
+// 200 noise windows of 9,000 points 3.67 ms, 3.52 this way; the 400 windows 9.58 -> 9.36.
+template <int M, int MODE>
+__device__ __forceinline__ bool use_boxes(const JobDesc &j) {
     if constexpr (MODE == kModeMatrix || M == 0) {
         return false;
     } else {
         if (j.boxc == nullptr) return false;
-        const int lane = threadIdx.x & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int lstrip = item / j.segs, seg = item - lstrip * j.segs;
-        const int R = (j.s_lo + lstrip) * j.H + 64 * wave;
-        const int c0 = MODE == kModeAuto ? (R + j.wp) >> 6 : 0;
-        const int sa = j.seg_base + seg * j.seg_tiles;
-        const int ca = sa > c0 ? sa : c0;
-        const int cb = sa + j.seg_tiles < j.c_last + 1 ? sa + j.seg_tiles : j.c_last + 1;
-        if (ca >= cb || R > j.n - 1) return false;
-        int open = 0;
-#pragma unroll 1
-        for (int q = 0; q < 4; ++q) {
-            uint64_t act, full;
-            classify<NORM, M>(boxes_of(j), R >> 6, (ca + (int)((int64_t)(cb - 1 - ca) * q / 3)) / kGroup, lane, act, full);
-            open += __builtin_popcountll(act & ~full);
-        }
-        return open < 240;
+        const auto d = (const __attribute__((address_space(4))) uint32_t *)(const uint32_t *)j.decided;
+        uint32_t sum = 0;   // two 16-bit halves
+#pragma unroll
+        for (int q = 0; q < kPrepareBlocks / 4; ++q) sum += (d[q] & 0x00FF00FFu) + ((d[q] >> 8) & 0x00FF00FFu);
+        return (int)((sum & 0xFFFFu) + (sum >> 16)) >= kSamples / 16 * j.sample_blocks;
     }
 }
 
@@ -1511,7 +1562,7 @@ k_tiles(const JobDesc *__restrict__ jobs, const GroupDesc *__restrict__ groups, 
         const JobDesc &j = jobs[lo];
         const int block = item - j.strip_base;
         if constexpr (MODE != kModeMatrix && M > 0) {
-            if (use_boxes<NORM, M, MODE>(j, block)) process_strip<NORM, M, MODE, true>(j, block, L);
+            if (use_boxes<M, MODE>(j)) process_strip<NORM, M, MODE, true>(j, block, L);
             else process_strip<NORM, M, MODE, false>(j, block, L);
         } else {
             process_strip<NORM, M, MODE, false>(j, block, L);
@@ -2577,8 +2628,8 @@ Layout layout_of(const Job &jb) {
     if (jb.boxes && jb.mode != kModeMatrix && jb.kp.m <= kMaxM && ctiles >= kBoxMinTiles) {
         L.ncc = (int)((ctiles + kGroup - 1) / kGroup * kGroup * (64 / kBoxVecs));
         L.ncr = jb.mode == kModeAuto ? L.ncc : (int)(((n - 1) / 64 + 1) * (64 / kBoxVecs));
-        L.box_floats = 2 * std::min(jb.kp.m, kBoxK) *
-                       ((int64_t)L.ncc + (jb.mode == kModeAuto ? 0 : L.ncr));
+        L.box_floats = kBoxHeader + 2 * std::min(jb.kp.m, kBoxK) *
+                                        ((int64_t)L.ncc + (jb.mode == kModeAuto ? 0 : L.ncr));
     }
     L.off_box = off; off += a256(sizeof(float) * (size_t)L.box_floats);
     // Masks of what summaries were written: a bit per strip of the band, for
@@ -2688,7 +2739,11 @@ JobDesc make_desc(const Job &jb, const Layout &lay, int strip_base, int stitch_b
     d.host_info = static_cast<unsigned char *>(jb.host_info);
     d.run = jb.run;
     d.host_hist = static_cast<unsigned long long *>(jb.host_hist);
-    d.boxc = lay.box_floats > 0 ? reinterpret_cast<float *>(scr + lay.off_box) : nullptr;
+    d.boxc = lay.box_floats > 0 ? reinterpret_cast<float *>(scr + lay.off_box) + kBoxHeader : nullptr;
+    d.decided = reinterpret_cast<uint8_t *>(scr + lay.off_box);
+    // 128 pieces of a short job, 2,048 of one of 131,072 vectors (the samples of
+    // 400 windows of 3,000 points, 2,048 each, took 70 us).
+    d.sample_blocks = (int32_t)std::min<int64_t>(kPrepareBlocks, std::max<int64_t>(4, ncols / 2048));
     d.boxr = jb.mode == kModeAuto || !d.boxc
                  ? d.boxc : d.boxc + (int64_t)2 * std::min(kp.m, kBoxK) * lay.ncc;
     d.ncc = lay.ncc;
@@ -2715,6 +2770,13 @@ void launch_stats(const JobDesc *jobs, int blocks, int njobs, hipStream_t st) {
     hipLaunchKernelGGL(k_stats_moments, dim3(blocks, njobs), dim3(kStatThreads), 0, st, jobs);
     if (blocks > 1)
         hipLaunchKernelGGL(k_stats_entropy, dim3(blocks, njobs), dim3(kStatThreads), 0, st, jobs);
+}
+
+// k_prepare blocks of a launch: a thread per length or point of its longest job, up
+// to kPrepareBlocks (64 for each of 400 windows of 3,000 points: 31 us, 15 so).
+int prepare_blocks_of(const Job &jb) {
+    const int64_t most = std::max({jb.hist_len(), jb.n_points, jb.n_points_b});
+    return (int)std::max<int64_t>(4, std::min<int64_t>(kPrepareBlocks, (most + kPrepareThreads - 1) / kPrepareThreads));
 }
 
 // LDS bins for the white lengths of a job.
@@ -2858,7 +2920,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
 
     std::vector<int> gkeys;
     int stitch_blocks = 0;
-    int stat_grid = 1;
+    int stat_grid = 1, prepare_grid = 1;
     int ngroups = 0;
     int strip_acc = 0;
     for (int r = 0; r < njobs; ++r) {
@@ -2880,6 +2942,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
         hgroups[ngroups - 1].capw = std::max(hgroups[ngroups - 1].capw, white_bins_of(jb));
         JobDesc d = make_desc(jb, lay, strip_acc, stitch_blocks);
         stat_grid = std::max(stat_grid, (int)d.stat_blocks);
+        prepare_grid = std::max(prepare_grid, prepare_blocks_of(jb));
         strip_acc += lay.items;
         stitch_blocks += stitch_blocks_of(jb);
         hdesc[r] = d;
@@ -2895,10 +2958,11 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
 
     if (phases) hipEventRecord(phases->ev[0], st);
     if (njobs == 1)
-        hipLaunchKernelGGL(k_prepare_one, dim3(kPrepareBlocks), dim3(256), 0, st, hdesc[0], hgroups[0],
-                           ddesc, dgroups, dcounters);
+        hipLaunchKernelGGL(k_prepare_one, dim3(prepare_grid), dim3(kPrepareThreads), 0, st, hdesc[0],
+                           hgroups[0], ddesc, dgroups, dcounters);
     else
-        hipLaunchKernelGGL(k_prepare, dim3(kPrepareBlocks, njobs), dim3(256), 0, st, ddesc, dcounters);
+        hipLaunchKernelGGL(k_prepare, dim3(prepare_grid, njobs), dim3(kPrepareThreads), 0, st, ddesc,
+                           dcounters);
 
     if (phases) hipEventRecord(phases->ev[1], st);
     if (njobs == 1 && hdesc[0].nbands > 1) {
@@ -3002,8 +3066,8 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     const Layout lay = layout_of(jb);
     const JobDesc d = make_desc(jb, lay, 0, 0);
     const GroupDesc g{0, 1, lay.items, white_bins_of(jb)};
-    hipLaunchKernelGGL(k_prepare_one, dim3(kPrepareBlocks), dim3(256), 0, st, d, g, ddesc, dgroups,
-                       dcounters);
+    hipLaunchKernelGGL(k_prepare_one, dim3(prepare_blocks_of(jb)), dim3(kPrepareThreads), 0, st, d, g,
+                       ddesc, dgroups, dcounters);
     if (lay.items > 0) {
         TileKernel kern = tile_kernel(kModeAuto, jb.kp.norm, jb.kp.m);
         int occ = 0;
