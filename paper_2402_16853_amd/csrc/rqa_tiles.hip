@@ -111,12 +111,10 @@ constexpr int kPrepareThreads = 256;
 constexpr int kCounters = 64;        // work counters of a launch
 // Boxes (exact pruning of the predicate, see classify): of every kBoxVecs
 // consecutive delay vectors the smallest and the largest of each of the first
-// kBoxK coordinates, in planes (minimum, maximum of coordinate 0, 1, 2).  Jobs
-// of fewer than kBoxMinTiles column tiles take none: there the predicate is a
-// small part of a tile's time.
+// kBoxK coordinates, in planes (minimum, maximum of coordinate 0, 1, 2).  Which
+// jobs take them: boxes_pay.
 constexpr int kBoxK = 3;
 constexpr int kBoxVecs = 8;
-constexpr int kBoxMinTiles = 128;
 constexpr int kBoxHeader = 64;       // floats before the first plane: the samples' counts
 constexpr int kSamples = 32;         // pieces sampled per k_prepare block (see sample_piece)
 
@@ -756,13 +754,17 @@ __device__ __forceinline__ void make_boxes(float *box, int entries, const float 
         const int k = (int)(t / entries);
         const int64_t q = t - (int64_t)k * entries;
         float lo = INFINITY, hi = -INFINITY;
-        const auto x = glb(s) + (int64_t)k * tau;
+        const int64_t first = q * kBoxVecs, last = (int64_t)count - 1;
+        if (first <= last) {
+            // (past the end: the last vector again, so that no load waits for another)
+            const auto x = glb(s) + (int64_t)k * tau;
+            float v[kBoxVecs];
 #pragma unroll
-        for (int u = 0; u < kBoxVecs; ++u) {
-            const int64_t i = q * kBoxVecs + u;
-            if (i < count) {
-                lo = fminf(lo, x[i]);
-                hi = fmaxf(hi, x[i]);
+            for (int u = 0; u < kBoxVecs; ++u) v[u] = x[first + u < last ? first + u : last];
+#pragma unroll
+            for (int u = 0; u < kBoxVecs; ++u) {
+                lo = fminf(lo, v[u]);
+                hi = fmaxf(hi, v[u]);
             }
         }
         glb(box)[(int64_t)(2 * k) * entries + q] = lo;
@@ -2548,6 +2550,18 @@ int auto_segs_max(int64_t n, int wp, int H, int nstrips, bool fine) {
     return segs;
 }
 
+// Whether a job of these row and column tiles takes boxes.  A run alone of fewer
+// than 128 column tiles does not: its time is a chain of tiles too short to fill
+// the chip, of which the predicate is a small part.  Jobs that may share a launch
+// do from 32 on (190 sine windows of 3,652 points 557 -> 356 us, 200 of 8,000 1.87 ->
+// 1.01 ms, 400 noise windows of 3,000 1.12 -> 1.12; 24 tiles: no gain), and so do tall
+// cross matrices, whose many row tiles fill the chip (200,000 x 8,000 sine 668 -> 598
+// us, Lorenz 750 -> 722; of 50,000 x 8,000, 98,000 tiles, Lorenz gained 1%, noise lost 3).
+bool boxes_pay(const Job &jb, int64_t rtiles, int64_t ctiles) {
+    if (!jb.boxes || jb.mode == kModeMatrix || jb.kp.m > kMaxM || ctiles < 32) return false;
+    return ctiles >= 128 || (jb.mode == kModeAuto ? !jb.fine : rtiles * ctiles >= 131072);
+}
+
 Layout layout_of(const Job &jb) {
     Layout L{};
     const int64_t n = jb.n_vec;
@@ -2625,7 +2639,7 @@ Layout layout_of(const Job &jb) {
     // row coordinates live in registers.
     const int64_t ncols = jb.mode == kModeAuto ? n : jb.n_cols;
     const int64_t ctiles = (ncols - 1) / 64 + 1;
-    if (jb.boxes && jb.mode != kModeMatrix && jb.kp.m <= kMaxM && ctiles >= kBoxMinTiles) {
+    if (boxes_pay(jb, (n - 1) / 64 + 1, ctiles)) {
         L.ncc = (int)((ctiles + kGroup - 1) / kGroup * kGroup * (64 / kBoxVecs));
         L.ncr = jb.mode == kModeAuto ? L.ncc : (int)(((n - 1) / 64 + 1) * (64 / kBoxVecs));
         L.box_floats = kBoxHeader + 2 * std::min(jb.kp.m, kBoxK) *

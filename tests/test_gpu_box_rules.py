@@ -49,3 +49,49 @@ def test_distances_that_overflow(cuda, oracle_lib, norm, eps):
     res = comp(torch.from_numpy(s).to(cuda))
     comp.close()
     check(res, oracle_lib.histograms(s, p.m, p.tau, p.eps, norm, 1), (norm, eps))
+
+
+@pytest.mark.parametrize("n,n2", [(16_500, 8_200), (8_200, 16_500), (270_000, 2_100)])
+def test_classified_tall_cross(cuda, oracle_lib, n, n2):
+    """Boxes of rows and columns that are not the same, over several strips and column
+    segments; 33 column tiles are enough behind 131,072 tiles in all."""
+    import torch
+    from paper_2402_16853_amd import RQA
+    for kind, p in (("sine", Params(m=2, tau=3, eps=0.8, norm=2, theiler=0)),
+                    ("lorenz", Params(m=3, tau=10, eps=0.1, norm=3, theiler=100))):
+        lag = (p.m - 1) * p.tau
+        a, b = series(kind, n + lag, 1), series(kind, n2 + lag, 2)
+        print(f"[case] tall cross {n}x{n2} {kind}", flush=True)
+        comp = RQA.from_params(p)
+        res = comp.cross(torch.from_numpy(a).to(cuda), torch.from_numpy(b).to(cuda))
+        comp.close()
+        check(res, oracle_lib.cross_histograms(a, b, p.m, p.tau, p.eps, p.norm, p.theiler), (n, n2, kind))
+
+
+@pytest.mark.parametrize("kind,p", [("sine", Params(m=3, tau=2, eps=0.3, norm=2, theiler=0)),
+                                    ("lorenz", Params(m=2, tau=5, eps=0.1, norm=3, theiler=70)),
+                                    ("uniform", Params(m=5, tau=1, eps=0.5, norm=1, theiler=1))])
+def test_classified_windows(cuda, oracle_lib, kind, p):
+    """Windows about the 32 column tiles from which those of a batch are classified, and
+    the same lengths as served jobs."""
+    import torch
+    from paper_2402_16853_amd import RQA, Server
+    lag = (p.m - 1) * p.tau
+    ln = np.array([31 * 64, 31 * 64 + 1, 32 * 64, 40 * 64 + 5, 700, 5_000], dtype=np.int64) + lag
+    off = np.arange(len(ln), dtype=np.int64) * 100
+    s = series(kind, int(5_600 + lag), 4)
+    ds = torch.from_numpy(s).to(cuda)
+    ref = [oracle_lib.histograms(s[o:o + k], p.m, p.tau, p.eps, p.norm, p.theiler) for o, k in zip(off, ln)]
+    comp = RQA.from_params(p)
+    for waves in (0, 1, 2, 8):
+        print(f"[case] classified windows {kind} waves={waves}", flush=True)
+        comp.set_tiling(waves, 0)
+        comp.run_batch(ds, off, ln)
+        for w in range(len(ln)):
+            check(comp.result_batch(w), ref[w], (kind, waves, w))
+    comp.close()
+    srv = Server(64 << 20, streams=2)
+    tickets = [srv.submit(p, ds[o:o + k].clone()) for o, k in zip(off, ln)]
+    for w, t in enumerate(tickets):
+        check(srv.wait(t), ref[w], (kind, "served", w))
+    srv.close()
