@@ -495,13 +495,25 @@ int enqueue(rqa_handle *h, const float *d_series, int64_t n_points, const int64_
     return launch(h, jobs, waves, trial, key, sig, stream, batched);
 }
 
+// Waves per workgroup of a full matrix.  The default shape's rule is one for the rows;
+// many cells behind few rows (from 2^27, and 4,096 rows: eight strips of eight waves)
+// take eight waves too, since four leave a CU at 12: uniform cross recurrence of 8,000 x
+// 200,000 1,062 us with four, 905 with eight, of 1,047 x 138,800 292 and 331.  A given
+// matrix, which has no predicate, takes four up to 24,576 rows: half-full ones of 20,000^2
+// 694 us with four, 764 with eight (a tenth full 387, 370), of 30,000^2 1,342 and 1,278.
+int full_waves(const Job &jb) {
+    if (jb.mode == kModeMatrix && jb.n_vec < 24576) return 4;
+    const bool wide = jb.n_vec >= 4096 && jb.n_vec * jb.n_cols >= int64_t(1) << 27;
+    return engine_default_waves(wide ? std::max(jb.n_vec, jb.n_cols) : jb.n_vec);
+}
+
 // One job over a full (not symmetric) matrix: the cross recurrence matrix of
 // (a, b), or a given bit matrix.
 int enqueue_full(rqa_handle *h, Job jb, void *stream) {
     if (jb.n_vec > (int64_t(1) << 31) - 2 || jb.n_cols > (int64_t(1) << 31) - 2)
         return RQA_EINVAL;
     jb.kp = make_kparams(h->p);
-    const int waves = h->waves > 0 ? h->waves : engine_default_waves(jb.n_vec);
+    const int waves = h->waves > 0 ? h->waves : full_waves(jb);
     std::vector<Job> jobs(1, jb);
     uint64_t sig = 1469598103934665603ull;
     sig = fnv(sig, &jb.mode, sizeof jb.mode);

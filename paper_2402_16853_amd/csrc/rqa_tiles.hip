@@ -2507,6 +2507,7 @@ constexpr int kTargetItems = 2048;
 // items; 16,384 items made the given matrix slower again).
 constexpr int kSegItems = 8192;    // (one series alone, one band or several)
 constexpr int kFullItems = 8192;
+constexpr int kFullFineItems = 1024;
 
 // Offset of the first evaluated diagonal of U, max(theiler, 1), clamped to n:
 // every window of n or more masks the whole matrix alike, and the clamp keeps
@@ -2595,7 +2596,11 @@ Layout layout_of(const Job &jb) {
         // A strip of a full matrix walks every column tile; its chain of
         // tiles is cut into column segments walked by different workgroups,
         // enough of them for about kFullItems work items, each at least
-        // max(8, H/64) tiles wide, or a kFineSegs-th of a short chain.
+        // max(8, H/64) tiles wide; in a run alone, narrower where that leaves fewer
+        // than kFullFineItems items, down to a kFineSegs-th of the chain (with no
+        // such bound the 200,000 x 1,000 uniform cross recurrence, 391 strips, was
+        // cut into single tiles: 658 us, 501 in 3 segments, 518 in the 2 wide ones;
+        // a bound of 2,048 items: 531).
         const int64_t nb = jb.n_cols;
         L.nstrips = (int)((n + L.H - 1) / L.H);
         // Row bands as in auto mode: summaries for one band's strips.
@@ -2603,10 +2608,10 @@ Layout layout_of(const Job &jb) {
         L.nbands = (L.nstrips + L.band - 1) / L.band;
         const int T = (int)((nb - 1) / 64 + 1);
         const int wide = std::max(8, L.H / 64);
-        const int min_tiles = jb.fine ? std::max(1, std::min(wide, T / kFineSegs)) : wide;
-        int segs = (int)std::min<int64_t>((kFullItems + L.band - 1) / L.band,
-                                          std::max(1, T / min_tiles));
-        segs = std::max(segs, 1);
+        int segs = std::max(1, std::min((kFullItems + L.band - 1) / L.band, T / wide));
+        if (jb.fine)
+            segs = std::max(segs, std::min((kFullFineItems + L.band - 1) / L.band,
+                                           T / std::max(1, std::min(wide, T / kFineSegs))));
         L.seg_base = 0;
         L.seg_tiles = (T + segs - 1) / segs;
         L.segs = (T + L.seg_tiles - 1) / L.seg_tiles;
