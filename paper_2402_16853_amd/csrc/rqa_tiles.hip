@@ -376,9 +376,11 @@ __device__ __forceinline__ void inner_runs(const Bins &bins, uint64_t t, uint32_
 // Advance the open run `st` of a column over the bits of y inside win (from bit 0;
 // bit p is row base + p of the strip), counting every run that ends there; the
 // strip's first run is recorded in *first (this lane's slot) instead.  Runs of
-// a strip are at most 64 * kMaxWaves = 512 long, so every one has an LDS bin
-// (after a neighbour wait has given up, states are arbitrary: the mask keeps the
-// index inside the bins).
+// a strip are at most 64 * kMaxWaves = 512 long, and no longer than the job's
+// longest line, so every one has an LDS bin.  (After a neighbour wait has given up,
+// states are arbitrary: the mask then keeps the index inside the workgroup's LDS,
+// where a launch of few white bins has the state rings behind them.  The item is
+// flagged as failed, and the rings are set anew for the next.)
 __device__ __forceinline__ void column_runs(const Bins &bins, uint64_t y, uint64_t win, uint32_t base,
                                             Run &st, uint16_t *first, uint32_t lane) {
     uint64_t t = changes(y, win, 0u, st.color);
@@ -454,36 +456,13 @@ typedef const __attribute__((address_space(4))) float *ConstF;
 __device__ __forceinline__ ConstF to_const(const float *p) { return (ConstF)(p); }
 
 // ---------------------------------------------------------------------------
-// Recurrence predicate for one column against the 64 rows of a wave.
+// Recurrence predicate for one column against the 64 rows of a wave, with the
+// first coordinate's difference d0 = col[0] - xr[0] given.
 // Returns a word whose bit 31 is set when the pair is NOT recurrent: the sign of
 // fl(thr - a) is set exactly when a > thr (IEEE subtraction of two finite floats
 // is zero only for equal operands).  a is accumulated in FP32, coordinates in
 // ascending order, no FMA.
 // ---------------------------------------------------------------------------
-template <int NORM, int M>
-__device__ __forceinline__ uint32_t nonrec_sign(ConstF col, int tau, const float *xr, float thr) {
-    float a;
-    if (NORM == RQA_NORM_L1) {
-        a = fabsf(col[0] - xr[0]);
-#pragma unroll
-        for (int k = 1; k < M; ++k) a = a + fabsf(col[k * tau] - xr[k]);
-    } else if (NORM == RQA_NORM_L2) {
-        const float d = col[0] - xr[0];
-        a = d * d;
-#pragma unroll
-        for (int k = 1; k < M; ++k) {
-            const float e = col[k * tau] - xr[k];
-            a = a + e * e;
-        }
-    } else {
-        a = fabsf(col[0] - xr[0]);
-#pragma unroll
-        for (int k = 1; k < M; ++k) a = fmaxf(a, fabsf(col[k * tau] - xr[k]));
-    }
-    return __float_as_uint(thr - a);
-}
-
-// The same, with the first coordinate's difference d0 = col[0] - xr[0] given.
 template <int NORM, int M>
 __device__ __forceinline__ uint32_t nonrec_sign_d0(float d0, ConstF col, int tau, const float *xr,
                                                    float thr) {
@@ -928,6 +907,10 @@ struct StripLds {
     __device__ uint16_t &vs(int c, int lane) { return vst[(c & (kRing - 1)) * 64 + lane]; }
     __device__ uint16_t &ds(int k, int lane) { return dst[(k & (kDiagRing - 1)) * 64 + lane]; }
 };
+
+constexpr int kLeastWhiteBins = 64;   // (white_bins_of)
+static_assert(sizeof(uint32_t) * (kCapV - kLeastWhiteBins) <= sizeof(uint16_t) * 64 * (kRing + kDiagRing),
+              "a masked length past the white bins stays in the state rings");
 
 // Notes on a tile's states as a wave leaves them to the wave below: some column
 // or (outgoing) diagonal run is open and black / white; some column state is not
@@ -2805,7 +2788,7 @@ int prepare_blocks_of(const Job &jb) {
 
 // LDS bins for the white lengths of a job.
 int white_bins_of(const Job &jb) {
-    return (int)std::min<int64_t>(kCapW, (jb.hist_len() + 63) / 64 * 64);
+    return (int)std::min<int64_t>(kCapW, (jb.hist_len() + kLeastWhiteBins - 1) / kLeastWhiteBins * kLeastWhiteBins);
 }
 
 int stitch_blocks_of(const Job &jb) {
