@@ -47,3 +47,21 @@ def test_shape_of_a_given_matrix(cuda, oracle_lib, n, rows):
     comp.close()
     assert plan["strip_rows"] == rows, plan
     check(res, oracle_lib.matrix_histograms(bits, n, nb, P.theiler), n)
+
+
+@pytest.mark.parametrize("waves", [1, 4, 8])
+@pytest.mark.parametrize("eps", [2e-5, 2e-4, 1e-3])
+def test_tiles_of_few_cells(cuda, oracle_lib, eps, waves):
+    """Noise that leaves a tile no cell, a few rows with one, or most rows: one series and
+    a cross pair."""
+    import torch
+    from paper_2402_16853_amd import RQA
+    p = Params(m=1, tau=1, eps=eps, norm=3, theiler=0)
+    a, b = series("uniform", 1_500, 1), series("uniform", 1_111, 2)
+    da, db = torch.from_numpy(a).to(cuda), torch.from_numpy(b).to(cuda)
+    print(f"[case] few cells eps={eps} waves={waves}", flush=True)
+    comp = RQA.from_params(p)
+    comp.set_tiling(waves, 0)
+    check(comp(da), oracle_lib.histograms(a, 1, 1, p.eps, 3, 0), (eps, waves))
+    check(comp.cross(da, db), oracle_lib.cross_histograms(a, b, 1, 1, p.eps, 3, 0), (eps, waves, "cross"))
+    comp.close()
