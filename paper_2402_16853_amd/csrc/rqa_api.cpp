@@ -99,7 +99,8 @@ struct TuneEntry {
 // delay vectors 4 and 2), and the default again, because a signature's first run
 // is a cold one: with one run per shape the 65,521-point Lorenz series settled on
 // 4 waves (640 us) instead of 8 (500 us).  Two waves are never the fastest from
-// 4,096 vectors on.
+// 4,096 vectors on (uniform points with 2 / 4 / 8 waves, us: 4,100: 121 / 115 / 124; 8,100:
+// 191 / 163 / 178; 30,000: 860 / 563 / 495; Lorenz and sine alike).
 void tune_init(TuneEntry &e, int dflt, int64_t nmax) {
     const int other = dflt > 4 ? 4 : (nmax < 4096 ? 2 : 8);
     e.ncand = 3;

@@ -719,7 +719,8 @@ __device__ __forceinline__ void classify(const Boxes &bx, int rb, int cg, int la
 // ---------------------------------------------------------------------------
 // Kernel 1: per-job preparation -- zero the histograms, the statistics and the
 // flag, reset the work counters, look for non-finite input, build the
-// zero-padded tail of the last column tile.  grid = (prepare_blocks, jobs).
+// zero-padded tail of the last column tile and the boxes, and sample what these
+// decide.  grid = (prepare_blocks_of the longest job, jobs).
 // Non-finite input is noted per block (a plain store: the flag itself is being
 // cleared by block 0 of this kernel) and enters the flag in the statistics.
 // ---------------------------------------------------------------------------
@@ -1481,11 +1482,14 @@ __device__ void process_strip(const JobDesc &j, int item, StripLds &L) {
     }
 }
 
-// Whether the tiles of a job are classified: where the boxes decide a sixteenth of
-// its sampled pieces (noise: none, or nearly).  With the classes in its code the L1,
-// m = 5 kernel ran 4.5% slower on uniform noise (400 windows 9.52 -> 9.96 ms).  For
-// each wave to try four groups of its part cost two to four memory latencies an item:
-// 200 noise windows of 9,000 points 3.67 ms, 3.52 this way; the 400 windows 9.58 -> 9.36.
+// Whether the tiles of a job are classified: where the boxes decide a quarter of its
+// sampled pieces (noise: none, or nearly; AR(1) series a few; Lorenz and sine most).
+// With the classes in its code the L1, m = 5 kernel ran 4.5% slower on uniform noise
+// (400 windows 9.52 -> 9.96 ms); classified for a sixteenth, 362 AR(1) windows of 3,831
+// points (m = 5) took 1.43 ms, without 1.39, and 100,000 AR(1) points (m = 3) 2.82, 2.77;
+// a line at three eighths gave the same times.  Counted once per job: for each wave to
+// try four groups of its part cost two to four memory latencies an item (200 noise
+// windows of 9,000 points 3.67 ms, 3.52 this way; the 400 windows 9.58 -> 9.36).
 template <int M, int MODE>
 __device__ __forceinline__ bool use_boxes(const JobDesc &j) {
     if constexpr (MODE == kModeMatrix || M == 0) {
@@ -1496,7 +1500,7 @@ __device__ __forceinline__ bool use_boxes(const JobDesc &j) {
         uint32_t sum = 0;   // two 16-bit halves
 #pragma unroll
         for (int q = 0; q < kPrepareBlocks / 4; ++q) sum += (d[q] & 0x00FF00FFu) + ((d[q] >> 8) & 0x00FF00FFu);
-        return (int)((sum & 0xFFFFu) + (sum >> 16)) >= kSamples / 16 * j.sample_blocks;
+        return (int)((sum & 0xFFFFu) + (sum >> 16)) >= kSamples / 4 * j.sample_blocks;
     }
 }
 
