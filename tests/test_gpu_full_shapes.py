@@ -13,8 +13,8 @@ P = Params(m=1, tau=1, eps=0.02, norm=3, theiler=3)
 
 @pytest.mark.parametrize("n,n2,rows", [
     (200_000, 1_000, 512),      # 391 strips: two wide segments, and 1,024 items ask for three
-    (4_200, 40_000, 512),       # many cells behind few rows: eight waves
-    (4_095, 40_000, 256),       # four
+    (2_048, 66_000, 512),       # many cells behind few rows: eight waves
+    (2_047, 66_000, 256),       # four
     (3_000, 1_300, 256)])       # short chains: a twentieth each
 def test_cut_of_a_cross_matrix(cuda, oracle_lib, n, n2, rows):
     import torch
