@@ -172,9 +172,9 @@ struct JobDesc {
     uint8_t *decided;          // kPrepareBlocks bytes: of k_prepare block b's kSamples pieces, those
                                // that boxes decide (blocks from sample_blocks on sample none)
     int32_t sample_blocks;
-    uint32_t *vmask;           // which summaries were written (process_strip): per column
-    uint32_t *dfmask;          // tile from seg_base on, and per block of 64 diagonals at a strip's top edge and
-    uint32_t *dlmask;          // at its bottom edge, a bit per strip of the row band
+    uint32_t *vmask;           // which summaries were written (process_strip), a bit per strip
+    uint32_t *dfmask;          // of the row band: per column tile from seg_base on, and per block
+    uint32_t *dlmask;          // of 64 diagonals at a strip's top edge and at its bottom edge
     int32_t mask_words;        // words per tile or block
     int32_t kb_off;            // entry of diagonal block 0
     int64_t mask_total;        // words of the three masks, which lie one after the other
@@ -321,10 +321,11 @@ struct Bins {
 // Columns (y) and diagonals (z: the rows rotated right by their number, then
 // transposed) of a tile in which only the rows `rows` have cells: a row's word is
 // the mask of the lanes that get its bit.  Two transposes are ~80 vector
-// instructions and two chains of LDS swizzles; a row costs six here.  400 noise
-// windows with about three recurrences per tile, tiles: 9.28 -> 9.13 ms; smooth
-// series are the same (limits of 8 and 16 rows: 65,521-point Lorenz series 1 and 3%
-// slower, and no gain for the windows).
+// instructions and two chains of LDS swizzles; a row costs six here.  Without it
+// noise and AR(1) series with m = 5, a few recurrences to a tile, are 1-5% slower (300
+// windows of 6,000 points 2,522 -> 2,584 us, 9,000 points 174 -> 183), logistic and
+// sine windows 1-2% faster, others the same; with limits of 2 or 8 rows 32 calls of
+// five kinds of series stayed within 1%.
 __device__ __forceinline__ void gather_rows(uint32_t xlo, uint32_t xhi, uint32_t rows, int base,
                                             uint32_t &y, uint32_t &z) {
     y = z = 0u;
@@ -408,10 +409,10 @@ __device__ __forceinline__ void finish_row(const JobDesc &j, const Bins &bins, u
     }
 }
 
-// As column_runs, for a part of a diagonal: bits of d inside win, from bit lo.  White runs are not counted (and never a first
-// run), so one trip takes a whole black run.  DW: how many lines a diagonal run
-// stands for (2 in the upper triangle of a symmetric matrix, whose mirror
-// diagonal repeats it; 1 in a full matrix).
+// As column_runs, for a part of a diagonal: bits of d inside win, from bit lo.
+// White runs are not counted (and never a first run), so one trip takes a whole
+// black run.  DW: how many lines a diagonal run stands for (2 in the upper triangle
+// of a symmetric matrix, whose mirror diagonal repeats it; 1 in a full matrix).
 template <int DW>
 __device__ __forceinline__ void diagonal_runs(const Bins &bins, uint64_t d, uint64_t win, uint32_t lo,
                                               uint32_t base, Run &st, uint16_t *first, uint32_t lane,
@@ -2664,8 +2665,7 @@ Layout layout_of(const Job &jb) {
     // come the boxes and masks themselves (3 bytes per vector at most, and under 0.2%
     // of the summaries) and what a short run's narrow segments add (8 MiB or 4%): a
     // limit then cuts a run into the row bands that its wide cut needs, and no more.
-    // (Counted, they cut 2,000 points in 100 KiB into 8 bands: 272 us, one band 215
-    // with whole strips.)
+    // (Counted, they cut 2,000 points in 100 KiB into 8 bands: 272 us, one band 74.)
     if (jb.fine) {
         Job wide = jb;
         wide.fine = false;
