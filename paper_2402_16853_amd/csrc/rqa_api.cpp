@@ -95,14 +95,17 @@ struct TuneEntry {
     bool done = false;
 };
 
-// Three trials: the default shape, its neighbour (8 and 4 waves; below 4,096
-// delay vectors 4 and 2), and the default again, because a signature's first run
-// is a cold one: with one run per shape the 65,521-point Lorenz series settled on
-// 4 waves (640 us) instead of 8 (500 us).  Two waves are never the fastest from
-// 4,096 vectors on (uniform points with 2 / 4 / 8 waves, us: 4,100: 121 / 115 / 124; 8,100:
-// 191 / 163 / 178; 30,000: 860 / 563 / 495; Lorenz and sine alike).
-void tune_init(TuneEntry &e, int dflt, int64_t nmax) {
-    const int other = dflt > 4 ? 4 : (nmax < 4096 ? 2 : 8);
+// Three trials: the default shape, its neighbour, and the default again, because a
+// signature's first run is a cold one: with one run per shape the 65,521-point Lorenz
+// series settled on 4 waves (640 us) instead of 8 (500 us).  The neighbour is 4 of 8
+// waves, and 8 of 4, or 2 where the strips are short: below 2,048 delay vectors, and
+// in a launch of few jobs below 4,096.  Runs with 2 / 4 / 8 waves, us: uniform points,
+// 2,000: 92 / 103 / 131, 3,000: 122 / 122 / 149, 4,100: 121 / 115 / 124, 30,000: 860 /
+// 563 / 495; 1,000 windows of 1,200 1,423 / 1,495 / 1,599, of 3,958 (m = 5) 6,276 / 4,128 /
+// 3,677; 300 of 3,000 Lorenz points 626 / 496 / 488; Lorenz and sine runs as uniform ones.
+void tune_init(TuneEntry &e, int dflt, int64_t nmax, int32_t count) {
+    const bool low = nmax < 2048 || (nmax < 4096 && count < 32);
+    const int other = dflt > 4 ? 4 : low ? 2 : 8;
     e.ncand = 3;
     e.cand[0] = e.cand[2] = dflt;
     e.cand[1] = other;
@@ -477,7 +480,7 @@ int enqueue(rqa_handle *h, const float *d_series, int64_t n_points, const int64_
         std::lock_guard<std::mutex> lk(g_tune_mu);
         tune_load_locked();
         TuneEntry &e = g_tune[key];
-        if (!e.done && e.ncand == 0) tune_init(e, engine_default_waves(nmax), nmax);
+        if (!e.done && e.ncand == 0) tune_init(e, engine_default_waves(nmax), nmax, count);
         if (e.done) {
             waves = e.best;
         } else {

@@ -315,6 +315,23 @@ int main() {
     CHECK(rqa_plot_cross(h, kSeries, 5000, kSeries, 640, bits, 10, two) == RQA_OK && plot_boxes);
     rqa_destroy(h);
 
+    // Trials: the neighbour of four waves is eight, but two for short strips, whose
+    // launch has no use for more.
+    struct { int64_t n; int count, other; } shapes[] = {
+        {2000, 1, 2}, {2000, 300, 2}, {3000, 1, 2}, {3000, 31, 2}, {3000, 32, 8}, {3000, 300, 8}, {5000, 1, 8}};
+    for (const auto &s : shapes) {
+        CHECK(rqa_create(&h, 1, 1, 0.5f, 3, 2, 2, 2, 1) == RQA_OK);
+        std::vector<int64_t> off(s.count, 0), len(s.count, s.n);
+        for (int k = 0; k < 3; ++k) {
+            CHECK(rqa_run_batch(h, kSeries, s.n, off.data(), len.data(), s.count, one) == RQA_OK);
+            int32_t waves = 0, graph = 0;
+            CHECK(rqa_last_launch(h, &waves, &graph) == RQA_OK);
+            CHECK(waves == (k == 1 ? s.other : 4));
+            CHECK(rqa_result_batch_all(h, std::vector<rqa_measures>(s.count).data(), nullptr, s.count) == RQA_OK);
+        }
+        rqa_destroy(h);
+    }
+
     CHECK(hipStreamDestroy(one) == hipSuccess && hipStreamDestroy(two) == hipSuccess);
     return 0;
 }
