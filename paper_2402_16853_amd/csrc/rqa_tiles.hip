@@ -2523,23 +2523,38 @@ int default_waves_impl(int64_t n) {
 //    jobs whose first strip has 128 tiles or more (a 199,873-vector served job at
 //    RR 5%: 13.9 ms with 2,048 items, 12.1 with 4,096, 11.5 with 8,192; a
 //    300,000-point Lorenz series 9.2 / 8.3 / 7.8 ms).
-//  * With `fine` (a handle's own run) at least kFineSegs, however narrow: a short
-//    job is its longest chain of tiles (7 us each at RR 12%, for want of other
-//    waves to hide their latency), and cutting it into 16 to 20 costs less in
-//    the stitch than it saves.  Tile kernel + stitch, whole strips -> cut: 500
-//    points 73 -> 41 us, 2,000 (RR 12%) 270 -> 72, 9,973 (AR(1)) 500 -> 149, 20,000
-//    (Lorenz) 254 -> 156; at 65,521 points both rules give about the same.
+//  * With `fine` (a handle's own run) up to kFineSegs, however narrow: a short job is
+//    its longest chain of tiles (7 us each at RR 12%, for want of other waves to
+//    hide their latency), and cutting it into 16 to 20 costs less in the stitch
+//    than it saves.  Tile kernel + stitch, whole strips -> cut: 500 points 73 -> 41
+//    us, 2,000 (RR 12%) 270 -> 72, 9,973 (AR(1)) 500 -> 149, 20,000 (Lorenz) 254 -> 156.
+//    As many of them as give the shortest time if every round of blocks takes
+//    that of a whole segment: 20 are no gain where they begin a round that they leave
+//    half empty.  Uniform points (RR 19%), 20 segments -> this many: 56,761 with 8
+//    waves 3,164 -> 2,850 us (13), 40,000 1,817 -> 1,497 (18), 26,000 with 4 886 -> 788
+//    (14); Lorenz and sine 2-6% there.  (A whole round is 740 of the 768 blocks that
+//    the chip holds: with 768, the blocks that the diagonal cuts short begin another
+//    one, 40,000 points 1,607.)
 //    (A served job keeps the first rule, and its footprint.)
 //  * 1 for jobs of more than kTargetItems / 2 strips (the 1,048,576-point workload
 //    has 2,048): whole strips leave no CU idle there.
 constexpr int kFineSegs = 20;
+constexpr int kRoundBlocks = 740;
 int auto_segs_max(int64_t n, int wp, int H, int nstrips, bool fine) {
     const int T0 = (int)((n - 1) / 64 - wp / 64 + 1);
     if (nstrips < 1 || 2 * nstrips > kTargetItems) return 1;
     int segs = 1;
     if (T0 >= 128)
         segs = (int)std::max<int64_t>(1, std::min<int64_t>((kSegItems + nstrips - 1) / nstrips, T0 / 64));
-    if (fine) segs = std::max(segs, std::min(T0, kFineSegs));
+    if (fine) {
+        const int64_t tiles = (int64_t)nstrips * T0 - (int64_t)nstrips * (nstrips - 1) / 2 * (H / 64);
+        const auto rounds = [&](int t) {   // of blocks, `tiles` in all, a t-th of a strip's T0 each
+            return ((tiles * t + T0 - 1) / T0 + kRoundBlocks - 1) / kRoundBlocks;
+        };
+        const int least = segs, most = std::min(T0, kFineSegs);
+        for (int t = least + 1; t <= most; ++t)
+            if (rounds(t) * segs <= rounds(segs) * t) segs = t;
+    }
     return segs;
 }
 

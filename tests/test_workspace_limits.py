@@ -41,3 +41,15 @@ def test_bound_of_whole_strips(waves, m, tau, theiler):
             q = plan(p, n + (m - 1) * tau, waves, limit)
             assert q["workspace_bytes"] <= limit, (n, k, limit, q)
             assert q["bands"] == 1 or k < S, (n, k, q)
+
+
+@pytest.mark.parametrize("n,waves,segs", [
+    (2_000, 0, 16), (12_000, 4, 20), (30_000, 8, 20),    # less than one round of blocks: as many as there may be
+    (26_000, 4, 14), (40_000, 8, 18), (56_761, 8, 13),   # one round, not one and a half
+    (65_521, 8, 20),                                     # two, and no fewer segments than 64 tiles wide
+    (100_000, 8, 24)])
+def test_short_segments_do_not_begin_a_round(n, waves, segs):
+    q = plan(Params(m=1, tau=1, eps=0.5, norm=3, theiler=1), n, waves, 0)
+    # (tiles shared out evenly: the last segment may vanish)
+    tiles = (n - 1) // 64 + 1
+    assert q["segs"] in (segs, -(-tiles // -(-tiles // segs))), q
