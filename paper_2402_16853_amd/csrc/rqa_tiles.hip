@@ -910,7 +910,7 @@ struct StripLds {
     __device__ uint16_t &ds(int k, int lane) { return dst[(k & (kDiagRing - 1)) * 64 + lane]; }
 };
 
-constexpr int kLeastWhiteBins = 64;   // (white_bins_of)
+constexpr int kLeastWhiteBins = 64;   // (white_bins)
 static_assert(sizeof(uint32_t) * (kCapV - kLeastWhiteBins) <= sizeof(uint16_t) * 64 * (kRing + kDiagRing),
               "a masked length past the white bins stays in the state rings");
 
@@ -2474,6 +2474,7 @@ struct Layout {
     int seg_base;          // first column tile of segment 0
     int64_t hentries;      // row pieces (auto, segs > 1): rows of one band * segs
     int items;             // work items of the largest band: band * segs
+    int64_t blocks;        // its tiles, counted in items of a whole segment
     int dw;                // full matrix: diagonal summary slots per block
     int64_t ventries;      // vertical summary entries per array (first, last), one band
     int64_t dentries;      // diagonal summary entries per array, one band
@@ -2531,15 +2532,19 @@ int default_waves_impl(int64_t n) {
 //    As many of them as give the shortest time if every round of blocks takes
 //    that of a whole segment: 20 are no gain where they begin a round that they leave
 //    half empty.  Uniform points (RR 19%), 20 segments -> this many: 56,761 with 8
-//    waves 3,164 -> 2,850 us (13), 40,000 1,817 -> 1,497 (18), 26,000 with 4 886 -> 788
-//    (14); Lorenz and sine 2-6% there.  (A whole round is 740 of the 768 blocks that
-//    the chip holds: with 768, the blocks that the diagonal cuts short begin another
-//    one, 40,000 points 1,607.)
+//    waves 3,164 -> 2,850 us (13), 40,000 1,817 -> 1,497 (18), 26,000 with 4 886 -> 802
+//    (19); Lorenz and sine 2-6% there.  (A whole round is 740 of the 768 blocks of
+//    eight waves that the chip holds, 988 of the 1,024 of four: with 768, the blocks
+//    that the diagonal cuts short begin another one, 40,000 points 1,607.)
 //    (A served job keeps the first rule, and its footprint.)
 //  * 1 for jobs of more than kTargetItems / 2 strips (the 1,048,576-point workload
 //    has 2,048): whole strips leave no CU idle there.
 constexpr int kFineSegs = 20;
-constexpr int kRoundBlocks = 740;
+constexpr int kRoundBlocks = 740, kRoundBlocks4 = 988;
+// Tiles of the first nstrips strips, of T0 tiles and H/64 fewer each.
+int64_t strip_tiles(int T0, int H, int nstrips) {
+    return (int64_t)nstrips * T0 - (int64_t)nstrips * (nstrips - 1) / 2 * (H / 64);
+}
 int auto_segs_max(int64_t n, int wp, int H, int nstrips, bool fine) {
     const int T0 = (int)((n - 1) / 64 - wp / 64 + 1);
     if (nstrips < 1 || 2 * nstrips > kTargetItems) return 1;
@@ -2547,9 +2552,10 @@ int auto_segs_max(int64_t n, int wp, int H, int nstrips, bool fine) {
     if (T0 >= 128)
         segs = (int)std::max<int64_t>(1, std::min<int64_t>((kSegItems + nstrips - 1) / nstrips, T0 / 64));
     if (fine) {
-        const int64_t tiles = (int64_t)nstrips * T0 - (int64_t)nstrips * (nstrips - 1) / 2 * (H / 64);
+        const int64_t tiles = strip_tiles(T0, H, nstrips);
+        const int whole = H > 64 * 4 ? kRoundBlocks : kRoundBlocks4;   // (white_bins)
         const auto rounds = [&](int t) {   // of blocks, `tiles` in all, a t-th of a strip's T0 each
-            return ((tiles * t + T0 - 1) / T0 + kRoundBlocks - 1) / kRoundBlocks;
+            return ((tiles * t + T0 - 1) / T0 + whole - 1) / whole;
         };
         const int least = segs, most = std::min(T0, kFineSegs);
         for (int t = least + 1; t <= most; ++t)
@@ -2599,6 +2605,7 @@ Layout layout_of(const Job &jb) {
             L.dentries = L.ventries;
             L.hentries = 0;
         }
+        L.blocks = L.band > 0 ? strip_tiles(T0, L.H, L.band) * L.segs / T0 : 0;
     } else {
         // A strip of a full matrix walks every column tile; its chain of
         // tiles is cut into column segments walked by different workgroups,
@@ -2628,6 +2635,7 @@ Layout layout_of(const Job &jb) {
         L.hentries = 0;
     }
     L.items = L.band * L.segs;
+    if (jb.mode != kModeAuto) L.blocks = L.items;
     if (L.ventries < 1) L.ventries = 1;
     if (L.dentries < 1) L.dentries = 1;
     L.tail_len = jb.mode == kModeMatrix ? 0 : 64 + (int64_t)(jb.kp.m - 1) * jb.kp.tau;
@@ -2804,9 +2812,18 @@ int prepare_blocks_of(const Job &jb) {
     return (int)std::max<int64_t>(4, std::min<int64_t>(kPrepareBlocks, (most + kPrepareThreads - 1) / kPrepareThreads));
 }
 
-// LDS bins for the white lengths of a job.
-int white_bins_of(const Job &jb) {
-    return (int)std::min<int64_t>(kCapW, (jb.hist_len() + kLeastWhiteBins - 1) / kLeastWhiteBins * kLeastWhiteBins);
+// LDS bins for the white lengths of a launch of that many blocks, whose longest line
+// has `len` - 1.  Six thousand let three workgroups share a CU.  Of those of up to four
+// waves there may be four, with fewer bins, where there are blocks for them: 12 waves
+// hide too little (200 windows of 8,000 points, L1, m = 5, 3.82 -> 3.34 ms, sine 1.38 ->
+// 1.20, 1,800 x 80,000 uniform cross recurrence 228 -> 206 us).  Blocks of less than a
+// round they would pack onto fewer CUs (16,000 uniform points 399 -> 468 us).
+constexpr int kCapW4 = 4992;
+static_assert(3 * strip_lds_bytes(kCapW) <= 160 * 1024 && 4 * strip_lds_bytes(kCapW4) <= 160 * 1024,
+              "workgroups per CU");
+int white_bins(int waves, int64_t blocks, int64_t len) {
+    return (int)std::min<int64_t>(waves <= 4 && blocks > kRoundBlocks ? kCapW4 : kCapW,
+                                  (len + kLeastWhiteBins - 1) / kLeastWhiteBins * kLeastWhiteBins);
 }
 
 int stitch_blocks_of(const Job &jb) {
@@ -2948,6 +2965,7 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
     int stat_grid = 1, prepare_grid = 1;
     int ngroups = 0;
     int strip_acc = 0;
+    int64_t blocks = 0, longest = 0;   // of the group
     for (int r = 0; r < njobs; ++r) {
         // A job launched with others keeps whole strips: the launch has work
         // items enough, and its scratch is sized for any choice.
@@ -2962,9 +2980,12 @@ int engine_launch(const std::vector<Job> &jobs_in, void *launch_scratch, void *s
             hgroups[ngroups] = GroupDesc{r, r + 1, 0, 0};   // items, capw: below
             ++ngroups;
             strip_acc = 0;
+            blocks = longest = 0;
         }
         hgroups[ngroups - 1].job1 = r + 1;
-        hgroups[ngroups - 1].capw = std::max(hgroups[ngroups - 1].capw, white_bins_of(jb));
+        blocks += lay.blocks;
+        longest = std::max(longest, jb.hist_len());
+        hgroups[ngroups - 1].capw = white_bins(jb.waves, blocks, longest);
         JobDesc d = make_desc(jb, lay, strip_acc, stitch_blocks);
         stat_grid = std::max(stat_grid, (int)d.stat_blocks);
         prepare_grid = std::max(prepare_grid, prepare_blocks_of(jb));
@@ -3090,7 +3111,7 @@ int engine_launch_static(Job jb, void *scratch, hipStream_t st) {
     jb.scratch = base + engine_launch_scratch_bytes(1) + a256(kInfoBytes);
     const Layout lay = layout_of(jb);
     const JobDesc d = make_desc(jb, lay, 0, 0);
-    const GroupDesc g{0, 1, lay.items, white_bins_of(jb)};
+    const GroupDesc g{0, 1, lay.items, white_bins(jb.waves, lay.blocks, jb.hist_len())};
     hipLaunchKernelGGL(k_prepare_one, dim3(prepare_blocks_of(jb)), dim3(kPrepareThreads), 0, st, d, g,
                        ddesc, dgroups, dcounters);
     if (lay.items > 0) {

@@ -45,7 +45,7 @@ def test_bound_of_whole_strips(waves, m, tau, theiler):
 
 @pytest.mark.parametrize("n,waves,segs", [
     (2_000, 0, 16), (12_000, 4, 20), (30_000, 8, 20),    # less than one round of blocks: as many as there may be
-    (26_000, 4, 14), (40_000, 8, 18), (56_761, 8, 13),   # one round, not one and a half
+    (26_000, 4, 19), (40_000, 8, 18), (56_761, 8, 13),   # one round, not one and a half
     (65_521, 8, 20),                                     # two, and no fewer segments than 64 tiles wide
     (100_000, 8, 24)])
 def test_short_segments_do_not_begin_a_round(n, waves, segs):
