@@ -501,10 +501,10 @@ int enqueue(rqa_handle *h, const float *d_series, int64_t n_points, const int64_
 
 // Waves per workgroup of a full matrix.  The default shape's rule is one for the rows;
 // many cells behind few rows (from 2^27, and 2,048 rows: four strips of eight waves)
-// take eight waves too, since four leave a CU at 12: cross recurrence of uniform points,
-// 8,000 x 200,000, 1,062 us with four and 905 with eight, 3,388 x 100,000 335 and 291,
-// 2,048 x 70,000 219 and 191.  Fewer rows lose some series more than they win others
-// (1,800 x 80,000: logistic 274 and 310, uniform 222 and 214, sine 182 and 162).  A given
+// take eight waves too, 24 instead of 16 on a CU.  Cross recurrence with four and with
+// eight, us: uniform points (m = 5) 8,000 x 200,000 1,152 and 1,060, 3,388 x 94,121 350 and
+// 341; Lorenz 222 and 211 there, logistic 2,560 x 60,000 298 and 317.  Fewer rows lose
+// more (1,800 x 80,000: logistic 257 and 314, uniform 244 and 250, sine 177 and 164).  A given
 // matrix, which has no predicate, takes four up to 24,576 rows: half-full ones of 20,000^2
 // 694 us with four, 764 with eight (a tenth full 387, 370), of 30,000^2 1,342 and 1,278.
 int full_waves(const Job &jb) {
